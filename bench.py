@@ -11,10 +11,14 @@ Default workload: N = 8 workers, c = 64 chunks, d = 1,414,647,808 fp32
 (Pythia-1.4B-shaped gradients with log-normal per-tensor scales), plan from
 the condition-number-constrained design with kappa_max = 1e3.
 
-The timed steps are single cerar_ring_simulate calls.  A second loop makes
-the same launches through the per-step entry points with HIP events between
-the phases on the launch stream; those events give each kernel's average
-duration.  The fp64 CPU oracle is timed on sampled positions of the same
+The timed steps go through the per-step entry points (cerar_encode_round for
+steps 0..L, then cerar_decode): there every message is read back from memory
+in the round after it was written, as on a ring of several devices, so the
+algorithmic bytes are the bytes moved.  A second loop makes the same calls
+with HIP events between the phases on the launch stream; those events give
+each kernel's average duration.  The single-call forms, which hand the
+messages over on chip where one device holds all workers, are reported beside
+them (one_pass, fused_variant) and never as the value.  The fp64 CPU oracle is timed on sampled positions of the same
 workload and plan (cpu_baseline), and the timed run's outputs are compared
 with its results (parity_vs_oracle).
 """
@@ -535,22 +539,21 @@ def main():
             ev[L + 2].record()
 
     for _ in range(args.warmup):
-        C.ring_simulate(plan, d, grads, work, ws, out)
+        step()
     torch.cuda.synchronize()
-    # the timed steps: one cerar_ring_simulate call each (encode, rounds 1..L
+    # the timed steps: the step calls of one all-reduce (encode, rounds 1..L
     # and decode for all workers), with nothing else on the stream
     t0 = time.perf_counter()
     for _ in range(args.steps):
-        C.ring_simulate(plan, d, grads, work, ws, out)
+        step()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     ms_per_step = (t1 - t0) * 1e3 / args.steps
     log(f"timed {args.steps} steps: {ms_per_step:.3f} ms/step")
 
-    # per-kernel durations: the same launches through the per-step entry
-    # points, with HIP events between the phases on the launch stream (each
-    # event adds a few microseconds to the stream, so these steps are not the
-    # timed ones)
+    # per-kernel durations: the same calls with HIP events between the phases
+    # on the launch stream (each event adds a few microseconds to the stream,
+    # so these steps are not the timed ones)
     step()
     events = [[torch.cuda.Event(enable_timing=True) for _ in range(L + 3)] for _ in range(args.steps)]
     torch.cuda.synchronize()
@@ -560,7 +563,22 @@ def main():
     torch.cuda.synchronize()
     ms_events = (time.perf_counter() - t2) * 1e3 / args.steps
 
-    # the single-GPU fused variant (reported beside the ring, never as the value)
+    # the single call (cerar_ring_simulate): the same outputs and buffers, with
+    # the messages handed over on chip where the one-pass kernel takes the plan
+    C.ring_simulate(plan, d, grads, work, ws, out)
+    torch.cuda.synchronize()
+    t5 = time.perf_counter()
+    for _ in range(args.steps):
+        C.ring_simulate(plan, d, grads, work, ws, out)
+    torch.cuda.synchronize()
+    ms_o = (time.perf_counter() - t5) * 1e3 / args.steps
+    one_pass = {"ms_per_step": round(ms_o, 4),
+                "moved_gbps": round(N * p * 4 * (3 * c + N) / (ms_o * 1e-3) / 1e9, 1),
+                "note": "cerar_ring_simulate: gradients read, encoded chunks kept on chip, every observation and "
+                        "output written once (3c + N rows per worker); not the counted ring path"}
+    log(f"single call: {ms_o:.3f} ms/step")
+
+    # the outputs alone (cerar_ring_simulate_fused), reported beside the ring, never as the value
     fused = None
     if c % 16 == 0 and c <= 64 and (N <= 8 or c <= 32) and d % 4 == 0:
         C.ring_simulate_fused(plan, d, grads, out)
@@ -732,6 +750,7 @@ def main():
         "ms_per_step_with_events": round(ms_events, 4),
         "step_ms_events": step_spans,
         "bucketed": bucketed,
+        "one_pass": one_pass,
         "fused_variant": fused,
         "in_place_encode": in_place,
         "encode_spread": spread,

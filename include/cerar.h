@@ -240,7 +240,15 @@ int cerar_decode(const cerar_plan *plan, size_t d, const float *work, size_t ld_
                  const void *ws, float *out, size_t ld_out, cerar_stream stream);
 
 /* Encode, L rounds and decode for all N workers: the whole approximate
- * all-reduce, enqueued on `stream` (L + 1 kernel launches: round L has none). */
+ * all-reduce, enqueued on `stream`.  Where the plan fits the one-pass kernel
+ * (N <= 8 with c <= 64, or N <= 16 with c <= 32) it is one launch that takes
+ * a block of positions through the whole protocol on chip; otherwise the
+ * launches of the step calls.  Either way `out`, `work` and the workspace
+ * end as the step calls leave them: every message is written to the slot
+ * that cerar_slot_map names (it is an observation of the worker that receives
+ * it), so cerar_decode may be called on them again.  What the one-pass launch
+ * leaves out is reading messages back between rounds, which a ring over
+ * several devices cannot leave out: to time that path, use the step calls. */
 int cerar_ring_simulate(const cerar_plan *plan, size_t d,
                         const float *grads, size_t ld_grads,
                         float *work, size_t ld_work, void *ws,
@@ -270,18 +278,11 @@ int cerar_ring_simulate_noalloc(const cerar_plan *plan, size_t d,
                                 float *work, size_t ld_work,
                                 float *out, size_t ld_out, cerar_stream stream);
 
-/* Single-GPU fused variant (not a ring implementation): the same result as
- * cerar_ring_simulate up to rounding order, computed by one kernel that runs
- * the encode, the L rounds of Algorithm 1 and the decode for all N workers
- * on one 64-position block at a time, with the encoded chunks, messages and
- * observations on chip (LDS and registers); only grads are read and only out
- * is written (no work or ws).  It shows what sharing one device allows and is
- * reported beside the ring, never in its place: a real ring must move every
- * message through memory.  For N in {2, 4, 8} the messages pass between
- * lanes with no workgroup barrier per round.
- * Needs c in {16, 32, 48, 64}, N <= 8 (or N <= 16 with c <= 32), at most
- * 160 KiB of LDS (N (c + 6) 256 bytes; for N in {2, 4, 8} also
- * N max(64 c, 256 ceil((c + N - 1) / 4)) 4 bytes), and 16-byte aligned rows
+/* The one-pass kernel without the ring's state: only grads are read and only
+ * out is written (no work or ws), with the same outputs as
+ * cerar_ring_simulate.  For callers that want the sums alone.
+ * Needs c in {16, 32, 48, 64}, N <= 8 (or N <= 16 with c <= 32),
+ * N (c + 6) 256 bytes of at most 160 KiB, and 16-byte aligned rows
  * (ld % 4 == 0).  Errors: E_INVAL. */
 int cerar_ring_simulate_fused(const cerar_plan *plan, size_t d, const float *grads, size_t ld_grads,
                               float *out, size_t ld_out, cerar_stream stream);
@@ -291,11 +292,10 @@ int cerar_ring_simulate_fused(const cerar_plan *plan, size_t d, const float *gra
  * bucket_off[b] + bucket_len[b]) of every worker's gradient and gets its own
  * p_b (cerar_chunk_len of bucket_len[b]).  work holds, per worker, the buckets' c*p_b
  * slots back to back (stride ld_work >= sum_b c*p_b); ws is
- * cerar_bucketed_workspace_bytes.  Enqueued on `stream`: every bucket's
- * encode, then each round as one launch for up to 64 buckets and all
- * workers, then every bucket's decode.  With c <= 64 and 16-byte aligned
- * rows in every bucket, the encode and the decode are batched as well (up to
- * 32 buckets per launch); otherwise each bucket gets its own launches.
+ * cerar_bucketed_workspace_bytes.  Enqueued on `stream`: where the plan fits
+ * the one-pass kernel (cerar_ring_simulate), one launch for up to 32 buckets;
+ * otherwise every bucket's encode, then each round as one launch for up to 64
+ * buckets and all workers, then every bucket's decode.
  * bucket_off/bucket_len are host arrays; buckets may not overlap in out.
  * Errors: E_INVAL (NULL plan or buffers, nbuckets < 1, an empty bucket,
  * overlapping buckets, ld_work below the slot total, ld_grads or ld_out below

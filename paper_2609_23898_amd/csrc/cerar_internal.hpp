@@ -56,6 +56,7 @@ struct DeviceCopy {
     float *dec_frag = nullptr;       // N x MT x KSd x 64 fp32 fragments of R_i
     int *ycols = nullptr;            // N x (L+1) slot ids
     RoundOp *rounds = nullptr;       // (L+1) x N
+    int cus = 0;                     // compute units of the device
 };
 
 }  // namespace cerar

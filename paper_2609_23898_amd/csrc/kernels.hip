@@ -13,6 +13,10 @@
 //  k_norms   (K5)  per-worker squared error against S = sum_w g_w, fp64,
 //                  and on sampled positions against given reference values.
 //  k_copy          plain streaming copy (bandwidth reference).
+//
+// The whole-ring entry points take the one-pass kernel (ring_pass.hip) where
+// it fits the plan; the kernels here are the step calls, and the whole ring
+// for the other plans.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,6 +28,8 @@
 #include <vector>
 
 #include "cerar_internal.hpp"
+#include "device_util.hpp"
+#include "ring_pass.hpp"
 
 namespace cerar {
 namespace {
@@ -134,15 +140,6 @@ __device__ inline void nt_store(float *ptr, v4f v) { __builtin_nontemporal_store
 // per lane instead of a 64-bit pointer per row.  opaque() hides the offset's
 // loop invariance (it emits no instruction), so the compiler cannot hoist
 // base + offset into one live 64-bit pointer per row across the block loop.
-__device__ inline uint32_t opaque(uint32_t x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-// The same for a wave-uniform value (kept in scalar registers).
-__device__ inline size_t opaque_s(size_t x) {
-    asm volatile("" : "+s"(x));
-    return x;
-}
 // The encode reads the gradient with ordinary loads: measured faster than
 // streaming loads for its c-row access pattern (the decode and the rounds
 // stream with non-temporal loads, which measured faster for them).
@@ -282,18 +279,6 @@ struct EncParams {
 // instance q owns workgroups [wg0_q, wg0_{q+1}) of the grid and brings its
 // own buffers, chunk length and block range; the rest is shared.
 constexpr int kMaxInst = 32;
-
-// Index of the last instance whose first workgroup is at or before `block`.
-template <class Inst>
-__device__ inline int instance_of(const Inst *in, int n, unsigned block) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (in[mid].wg0 <= block) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
 
 struct EncInst {
     const float *grads;
@@ -583,18 +568,6 @@ constexpr int kRoundThreads = 256;
 
 // One workgroup's share of a round for one worker: positions
 // [wg, wg + 1) x 1024 (vector layout) or a grid-stride loop (scalar layout).
-// The next message of a round N <= k < c, x = recv - delta_j + delta_{k+1},
-// rounded to fp32 once: the three fp32 terms are combined in fp64 (the
-// difference of two fp32 values is exact there unless their exponents are
-// more than 29 apart), so a message carries one rounding per round instead
-// of two.  A message keeps the rounding error of every earlier round (the
-// returning own term cancels, its rounding does not), and the decode
-// amplifies those errors by up to kappa_2(M_i), so this is the round's
-// share of the final error.
-__device__ inline float combine3(float recv, float sub, float add) {
-    return (float)(((double)recv - (double)sub) + (double)add);
-}
-
 // V 16-byte elements per thread in the vector layout: workgroup wg covers
 // [wg V, (wg + 1) V) x 1024 floats, V consecutive 1 KiB runs per wave.
 template <int MODE, bool VEC, int V = 1>
@@ -1351,297 +1324,6 @@ constexpr size_t kSplitEncLds = (size_t)8 * kSplitKC * 3 * 64 * 8 * sizeof(__bf1
 constexpr size_t kSplitDecLds = (size_t)8 * (kSplitKC * 3 * 64 * 8 + 3 * 64 * 4) * sizeof(__bf16) +
                                 (size_t)(32 * kSplitKC + 16) * sizeof(float *);
 
-// ---- single-GPU fused variant (not the counted path) ---------------------------
-// The whole all-reduce for one 64-position block of every worker in one
-// workgroup of N waves (wave w = worker w): the MFMA encode of the block,
-// the L rounds of Algorithm 1 with every worker's encoded chunks and the
-// messages in LDS (one position per lane), and the decode accumulated on
-// MFMA four observations at a time.  Only the gradients are read and only
-// the outputs written, so it moves about a quarter of the counted path's
-// bytes; it exists only where all workers share one device, so it is a
-// reported variant beside the ring, not a replacement for it.
-
-struct FusedParams {
-    const float *grads;
-    size_t ld_g;
-    size_t d;
-    float *out;
-    size_t ld_o;
-    const float *efrag;     // N x MT x KSe x 64
-    const float *dfrag;     // N x MT x KSd x 64
-    size_t p;
-    int N, c, L, KSd;
-    size_t blk0, blk1;
-};
-
-template <int MTC, bool FAST, int MAXT>
-__global__ __launch_bounds__(MAXT) void k_fused(FusedParams a) {
-    constexpr int KSE = 4 * MTC;                 // c = 16 MTC
-    constexpr int C = 16 * MTC;
-    extern __shared__ float sm[];
-    const int N = a.N, L = a.L;
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 15, krow = lane >> 4;
-    float *delta = sm;                                   // [N][C][64]
-    float *msg = delta + (size_t)N * C * 64;             // [2][N][64]
-    float *stage = msg + (size_t)2 * N * 64;             // [N][4][64]
-    float *mydelta = delta + (size_t)w * C * 64;
-    float *mystage = stage + (size_t)w * 256;
-    const float *src = a.grads + (size_t)w * a.ld_g;
-    float *out = a.out + (size_t)w * a.ld_o;
-    const float *ef = a.efrag + (size_t)w * MTC * KSE * 64;
-    const float *df = a.dfrag + (size_t)w * MTC * a.KSd * 64;
-    const size_t p = a.p;
-    v4f b[KSE];                                          // this block's gradient rows
-    auto load_block = [&](size_t bq) {
-        const size_t e0 = bq * 64;
-        if (FAST) {
-            const uint32_t lane_in = opaque((uint32_t)(((size_t)krow * p + 4 * (size_t)col) * sizeof(float)));
-#pragma unroll
-            for (int ks = 0; ks < KSE; ++ks) b[ks] = load_off(src + e0 + (size_t)(4 * ks) * p, lane_in);
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < KSE; ++ks) {
-                const size_t l = (size_t)(4 * ks + krow);
-                b[ks] = load_tile<true>(src + l * p, l * p, e0, col, p, a.d);
-            }
-        }
-    };
-    if (a.blk0 + blockIdx.x < a.blk1) load_block(a.blk0 + blockIdx.x);
-    for (size_t blk = a.blk0 + blockIdx.x; blk < a.blk1; blk += gridDim.x) {
-        const size_t e0 = blk * 64;
-        // encode: delta_w = U_w^T G_w^T on this block (MFMA, A fragments from L2)
-#pragma unroll 1
-        for (int mt = 0; mt < MTC; ++mt) {                // one M-tile at a time: its A fragments only
-            v4f acc[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KSE; ++ks) {
-                const float av = ef[((size_t)mt * KSE + ks) * 64 + lane];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b[ks][t], acc[t], 0, 0, 0);
-            }
-            // D fragment: register r of lane (krow, col) is chunk 16 mt + 4 krow + r, positions 4 col + t
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-                *reinterpret_cast<v4f *>(mydelta + (size_t)(16 * mt + 4 * krow + r) * 64 + 4 * col) = v;
-            }
-        }
-        __syncthreads();
-        // rounds: lane = position; x_{w,1} = delta_{w,1}
-        msg[(size_t)w * 64 + lane] = mydelta[lane];
-        v4f dacc[MTC][4];
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) dacc[mt][t] = v4f{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();
-        const int prev = (w + N - 1) % N;
-        int col_y = 0;                                   // next observation column (0..L)
-        // decode coefficients of the next K-step, fetched one K-step (four
-        // rounds) ahead so that their latency hides behind the rounds
-        float dnext[MTC];
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt) dnext[mt] = df[(size_t)mt * a.KSd * 64 + lane];
-        // the next block's gradient rows load during this block's rounds and decode
-        if (blk + gridDim.x < a.blk1) load_block(blk + gridDim.x);
-        auto observe = [&](float y) {                    // append column col_y of Y_w
-            mystage[(col_y & 3) * 64 + lane] = y;
-            if ((col_y & 3) == 3 || col_y == L) {
-                for (int r = (col_y & 3) + 1; r < 4; ++r) mystage[r * 64 + lane] = 0.f;   // zero rows past L
-                __builtin_amdgcn_wave_barrier();          // LDS runs a wave's accesses in order
-                const v4f yb = *reinterpret_cast<const v4f *>(mystage + krow * 64 + 4 * col);
-                const int ks = col_y >> 2;
-                float dcur[MTC];
-#pragma unroll
-                for (int mt = 0; mt < MTC; ++mt) dcur[mt] = dnext[mt];
-                if (ks + 1 < a.KSd) {
-#pragma unroll
-                    for (int mt = 0; mt < MTC; ++mt) dnext[mt] = df[((size_t)mt * a.KSd + ks + 1) * 64 + lane];
-                }
-#pragma unroll
-                for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        dacc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(dcur[mt], yb[t], dacc[mt][t], 0, 0, 0);
-            }
-            ++col_y;
-        };
-        for (int k = 1; k <= L; ++k) {
-            const float recv = msg[(size_t)((k - 1) & 1) * N * 64 + (size_t)prev * 64 + lane];   // x_{w-1,k}
-            observe(recv);                                // B_{w,k} (k < N) or D_{w,k-N+1}
-            if (k < L) {
-                float x;
-                if (k <= N - 1) {
-                    x = recv + mydelta[(size_t)k * 64 + lane];                   // + delta_{w,k+1}
-                } else {
-                    const int j = k - N + 1;
-                    const float sub = mydelta[(size_t)(j - 1) * 64 + lane];      // - delta_{w,j}
-                    x = k + 1 <= C ? combine3(recv, sub, mydelta[(size_t)k * 64 + lane])   // + delta_{w,k+1}
-                                   : recv - sub;
-                }
-                msg[(size_t)(k & 1) * N * 64 + (size_t)w * 64 + lane] = x;
-            }
-            __syncthreads();
-        }
-        observe(mydelta[(size_t)(C - 1) * 64 + lane]);   // column L: D_{w,c} = delta_{w,c}
-        // outputs: register r of lane (krow, col) is output chunk 16 mt + 4 krow + r
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = 16 * mt + 4 * krow + r;
-                const v4f v = {dacc[mt][0][r], dacc[mt][1][r], dacc[mt][2][r], dacc[mt][3][r]};
-                if (FAST) *reinterpret_cast<v4f *>(out + (size_t)m * p + e0 + 4 * col) = v;
-                else store_tile<true>(out + (size_t)m * p, (size_t)m * p, e0, col, p, a.d, v);
-            }
-        __syncthreads();                                  // LDS reused by the next block
-    }
-}
-
-
-// Fused variant for N in {2, 4, 8}: the rounds run without workgroup
-// barriers.  One workgroup of N waves takes one 64-position block:
-//  1. encode: wave w = worker w, MFMA, delta_w into LDS as [C][64];
-//  2. rounds: lane (rw, rq) of wave v owns worker rw = lane / (64/N) at block
-//     position v (64/N) + rq; it holds that position's c encoded chunks in
-//     registers, receives x_{rw-1,k} from the lane of worker rw-1 at the same
-//     position by a lane permute, and appends each observation to Y_rw in LDS
-//     (the LDS of step 1, free once the chunks are in registers);
-//  3. decode: wave w = worker w, MFMA over Y_w's K observation rows.
-// Three workgroup barriers per block, against one per round in k_fused.
-template <int MTC, int NW, bool FAST>
-__global__ __launch_bounds__(64 * NW) void k_fused_lanes(FusedParams a) {
-    constexpr int C = 16 * MTC, KSE = 4 * MTC, L = C + NW - 2, K = L + 1;
-    constexpr int KSD = (K + 3) / 4;
-    constexpr int PW = 64 / NW;                      // block positions per wave in the rounds
-    constexpr int DS = C * 64 + 8;                   // LDS floats per worker: delta [C][64] (+8: banks)
-    constexpr int YS = 4 * KSD * 64 + 8;             // LDS floats per worker: Y [4 KSD][64]
-    extern __shared__ float sm[];
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 15, krow = lane >> 4;
-    const int rw = lane / PW, rpos = w * PW + lane % PW;          // this lane's worker and position in the rounds
-    const int prev_addr = ((((rw + NW - 1) % NW) * PW + lane % PW)) * 4;   // lane of worker rw-1, same position
-    const float *src = a.grads + (size_t)w * a.ld_g;
-    float *out = a.out + (size_t)w * a.ld_o;
-    const float *ef = a.efrag + (size_t)w * MTC * KSE * 64;
-    const float *df = a.dfrag + (size_t)w * MTC * KSD * 64;
-    const size_t p = a.p;
-    v4f b[KSE];                                          // this block's gradient rows
-    auto load_block = [&](size_t bq) {
-        const size_t e0 = bq * 64;
-        if (FAST) {
-            const uint32_t lane_in = opaque((uint32_t)(((size_t)krow * p + 4 * (size_t)col) * sizeof(float)));
-#pragma unroll
-            for (int ks = 0; ks < KSE; ++ks) b[ks] = load_off(src + e0 + (size_t)(4 * ks) * p, lane_in);
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < KSE; ++ks) {
-                const size_t l = (size_t)(4 * ks + krow);
-                b[ks] = load_tile<true>(src + l * p, l * p, e0, col, p, a.d);
-            }
-        }
-    };
-    if (a.blk0 + blockIdx.x < a.blk1) load_block(a.blk0 + blockIdx.x);
-    for (size_t blk = a.blk0 + blockIdx.x; blk < a.blk1; blk += gridDim.x) {
-        const size_t e0 = blk * 64;
-        // 1. encode: delta_w = U_w^T G_w^T on this block
-        float *mydelta = sm + (size_t)w * DS;
-        float anext[KSE];                                // A fragments of the next M-tile, one tile ahead
-#pragma unroll
-        for (int ks = 0; ks < KSE; ++ks) anext[ks] = ef[(size_t)ks * 64 + lane];
-#pragma unroll 1
-        for (int mt = 0; mt < MTC; ++mt) {
-            float av[KSE];
-#pragma unroll
-            for (int ks = 0; ks < KSE; ++ks) av[ks] = anext[ks];
-            if (mt + 1 < MTC) {
-#pragma unroll
-                for (int ks = 0; ks < KSE; ++ks) anext[ks] = ef[((size_t)(mt + 1) * KSE + ks) * 64 + lane];
-            }
-            v4f acc[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KSE; ++ks) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks], b[ks][t], acc[t], 0, 0, 0);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-                *reinterpret_cast<v4f *>(mydelta + (size_t)(16 * mt + 4 * krow + r) * 64 + 4 * col) = v;
-            }
-        }
-        __syncthreads();
-        // 2. rounds, one (worker, position) per lane
-        float dl[C];
-#pragma unroll
-        for (int j = 0; j < C; ++j) dl[j] = sm[(size_t)rw * DS + (size_t)j * 64 + rpos];
-        // the next block's gradient rows load during the rounds and the decode
-        if (blk + gridDim.x < a.blk1) load_block(blk + gridDim.x);
-        __syncthreads();                                 // every lane has its chunks: LDS now holds Y
-        float *Y = sm + (size_t)rw * YS + rpos;          // column k of Y_rw at Y[64 k]
-        float x = dl[0];                                 // x_{rw,1} = delta_{rw,1}
-#pragma unroll
-        for (int k = 1; k <= L; ++k) {
-            const float recv = __int_as_float(__builtin_amdgcn_ds_bpermute(prev_addr, __float_as_int(x)));
-            Y[(size_t)(k - 1) * 64] = recv;              // x_{rw-1,k}: B_{rw,k} (k < N) or D_{rw,k-N+1}
-            if (k < L) {
-                if (k <= NW - 1) {
-                    x = recv + dl[k];                    // + delta_{rw,k+1}
-                } else if (k + 1 <= C) {
-                    x = combine3(recv, dl[k - NW], dl[k]);   // - delta_{rw,k-N+1} + delta_{rw,k+1}
-                } else {
-                    x = recv - dl[k - NW];               // - delta_{rw,k-N+1}
-                }
-            }
-        }
-        Y[(size_t)L * 64] = dl[C - 1];                   // column L: D_{rw,c} = delta_{rw,c}
-#pragma unroll
-        for (int k = K; k < 4 * KSD; ++k) Y[(size_t)k * 64] = 0.f;   // rows past L meet zero coefficients
-        __syncthreads();
-        // 3. decode: ghat_w = Y_w R_w, output chunk 16 mt + 4 krow + r in register r
-        const float *Yw = sm + (size_t)w * YS;
-        v4f dacc[MTC][4];
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) dacc[mt][t] = v4f{0.f, 0.f, 0.f, 0.f};
-        float dnext[MTC];
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt) dnext[mt] = df[(size_t)mt * KSD * 64 + lane];
-#pragma unroll 2
-        for (int ks = 0; ks < KSD; ++ks) {
-            float dcur[MTC];
-#pragma unroll
-            for (int mt = 0; mt < MTC; ++mt) dcur[mt] = dnext[mt];
-            if (ks + 1 < KSD) {
-#pragma unroll
-                for (int mt = 0; mt < MTC; ++mt) dnext[mt] = df[((size_t)mt * KSD + ks + 1) * 64 + lane];
-            }
-            const v4f yb = *reinterpret_cast<const v4f *>(Yw + (size_t)(4 * ks + krow) * 64 + 4 * col);
-#pragma unroll
-            for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    dacc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(dcur[mt], yb[t], dacc[mt][t], 0, 0, 0);
-        }
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = 16 * mt + 4 * krow + r;
-                const v4f v = {dacc[mt][0][r], dacc[mt][1][r], dacc[mt][2][r], dacc[mt][3][r]};
-                if (FAST) *reinterpret_cast<v4f *>(out + (size_t)m * p + e0 + 4 * col) = v;
-                else store_tile<true>(out + (size_t)m * p, (size_t)m * p, e0, col, p, a.d, v);
-            }
-        __syncthreads();                                  // LDS reused by the next block
-    }
-}
-
 // ---- K5: error norms ---------------------------------------------------------
 
 constexpr int kNormWorkers = 8;
@@ -1775,7 +1457,10 @@ int device_copy(const cerar_plan *plan, const DeviceCopy **out) {
     }
     // The map entry comes first: once device memory is held, nothing here throws.
     DeviceCopy &dc = plan->dev[dev];
-    int st = upload(&dc.enc_frag, plan->enc_frag.data(), plan->enc_frag.size());
+    int st = CERAR_OK;
+    if (hipError_t e = hipDeviceGetAttribute(&dc.cus, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess)
+        st = hip_fail(e, "hipDeviceGetAttribute");
+    if (!st) st = upload(&dc.enc_frag, plan->enc_frag.data(), plan->enc_frag.size());
     if (!st) st = upload(&dc.dec_frag, plan->dec_frag.data(), plan->dec_frag.size());
     if (!st) st = upload(&dc.ycols, plan->tab.ycols.data(), plan->tab.ycols.size());
     if (!st) st = upload(&dc.rounds, plan->tab.rounds.data(), plan->tab.rounds.size());
@@ -2215,6 +1900,48 @@ int enqueue_decode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry 
     return CERAR_OK;
 }
 
+// The fields of a one-pass launch that its instances share.
+PassParams pass_params(const cerar_plan *plan, const DeviceCopy *dc, size_t ld_grads, size_t ld_work, size_t ld_out) {
+    PassParams a;
+    a.ld_g = ld_grads;
+    a.ld_o = ld_out;
+    a.ld_w = ld_work;
+    a.efrag = dc->enc_frag;
+    a.dfrag = dc->dec_frag;
+    a.N = plan->N;
+    a.c = plan->c;
+    a.KSe = plan->KSe;
+    a.KSd = plan->KSd;
+    a.n = 0;
+    a.nblk = 0;
+    a.ragged = ld_grads % 32 != 0 || ld_out % 32 != 0;
+    return a;
+}
+
+void add_instance(PassParams &a, int P, const PassInst &in) {
+    a.in[a.n] = in;
+    a.in[a.n++].blk0 = a.nblk;
+    a.nblk += (unsigned)((in.p + P - 1) / P);
+    if (((uintptr_t)in.grads | (uintptr_t)in.out) % 128) a.ragged = 1;
+}
+
+// Encode, rounds and decode of one instance: one pass where the one-pass
+// kernel takes the plan, else the launches of the step calls.
+int enqueue_ring(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g, size_t d, const float *grads,
+                 size_t ld_grads, float *work, size_t ld_work, void *ws, float *out, size_t ld_out, hipStream_t s) {
+    if (const int P = pass_positions(plan->N, plan->c)) {
+        PassParams a = pass_params(plan, dc, ld_grads, ld_work, ld_out);
+        add_instance(a, P, PassInst{grads, out, work, (float *)ws, d, g.p, g.pool_stride, 0});
+        launch_ring_pass(a, dc->cus, s);
+        HIP_TRY(hipGetLastError(), "launch ring pass");
+        return CERAR_OK;
+    }
+    int st = enqueue_encode(plan, dc, g, d, grads, ld_grads, work, ld_work, ws, s);
+    for (int k = 1; k <= plan->L && !st; ++k) st = enqueue_round(plan, dc, g, k, work, ld_work, ws, s);
+    if (!st) st = enqueue_decode(plan, dc, g, d, work, ld_work, ws, out, ld_out, s);
+    return st;
+}
+
 int check_grads(const cerar_plan *plan, size_t d, const float *grads, size_t ld_grads, const float *work,
                 size_t ld_work, const void *ws, const Geometry &g) {
     if (!grads) return fail(CERAR_E_INVAL, "grads is NULL");
@@ -2404,10 +2131,8 @@ static int ring_simulate_impl(const cerar_plan *plan, size_t d, const float *gra
     const DeviceCopy *dc;
     st = device_copy(plan, &dc);
     if (st) return st;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    st = enqueue_encode(plan, dc, g, d, grads, ld_grads, work, ld_work, ws, s);
-    for (int k = 1; k <= plan->L && !st; ++k) st = enqueue_round(plan, dc, g, k, work, ld_work, ws, s);
-    if (!st) st = enqueue_decode(plan, dc, g, d, work, ld_work, ws, out, ld_out, s);
+    st = enqueue_ring(plan, dc, g, d, grads, ld_grads, work, ld_work, ws, out, ld_out,
+                      reinterpret_cast<hipStream_t>(stream));
     if (st) return st;
     std::lock_guard<std::mutex> lk(g_cursor_mu);
     g_cursor[ws] = Cursor{plan, plan->L + 1, d};
@@ -2450,10 +2175,8 @@ static int ring_simulate_noalloc_impl(const cerar_plan *plan, size_t d, const fl
     if (st) return st;
     st = check_out(plan, d, work, ld_work, ws, out, ld_out, g);
     if (st) return st;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    st = enqueue_encode(plan, dc, g, d, grads, ld_grads, work, ld_work, ws, s);
-    for (int k = 1; k <= plan->L && !st; ++k) st = enqueue_round(plan, dc, g, k, work, ld_work, ws, s);
-    if (!st) st = enqueue_decode(plan, dc, g, d, work, ld_work, ws, out, ld_out, s);
+    st = enqueue_ring(plan, dc, g, d, grads, ld_grads, work, ld_work, ws, out, ld_out,
+                      reinterpret_cast<hipStream_t>(stream));
     return st;
 }
 
@@ -2465,60 +2188,6 @@ extern "C" int cerar_ring_simulate_noalloc(const cerar_plan *plan, size_t d, con
         return ring_simulate_noalloc_impl(plan, d, grads, ld_grads, work, ld_work, out, ld_out, stream);
     });
 }
-
-namespace {
-// N <= 8 workers: up to 512 threads, so up to 256 registers per lane;
-// 8 < N <= 16 (then c <= 32 by the LDS bound): 1024 threads, 128 registers.
-template <int MTC, int MAXT>
-void launch_fused(const FusedParams &a, const BlockSplit &bs, size_t lds, hipStream_t s) {
-    FusedParams f = a;
-    const unsigned threads = 64u * (unsigned)a.N;
-    if (bs.interior > 0) {
-        f.blk0 = 0;
-        f.blk1 = bs.interior;
-        hipLaunchKernelGGL((k_fused<MTC, true, MAXT>), dim3((unsigned)std::min<size_t>(bs.interior, 2048)),
-                           dim3(threads), lds, s, f);
-    }
-    if (bs.total > bs.interior) {
-        f.blk0 = bs.interior;
-        f.blk1 = bs.total;
-        hipLaunchKernelGGL((k_fused<MTC, false, MAXT>), dim3((unsigned)std::min<size_t>(bs.total - bs.interior, 2048)),
-                           dim3(threads), lds, s, f);
-    }
-}
-// N in {2, 4, 8}: k_fused_lanes, N waves per workgroup.
-template <int MTC, int NW>
-int launch_fused_lanes(const FusedParams &a, const BlockSplit &bs, hipStream_t s) {
-    constexpr int C = 16 * MTC, K = C + NW - 1, KSD = (K + 3) / 4;
-    const size_t lds = sizeof(float) * (size_t)NW * std::max<size_t>((size_t)C * 64 + 8, (size_t)4 * KSD * 64 + 8);
-    if (lds > 160 * 1024) return fail(CERAR_E_INVAL, "N=%d, c=%d needs %zu bytes of LDS", NW, C, lds);
-    if (a.KSd != KSD) return fail(CERAR_E_INVAL, "decode K-steps %d != %d", a.KSd, KSD);
-    FusedParams f = a;
-    if (bs.interior > 0) {
-        f.blk0 = 0;
-        f.blk1 = bs.interior;
-        hipLaunchKernelGGL((k_fused_lanes<MTC, NW, true>), dim3((unsigned)std::min<size_t>(bs.interior, 2048)),
-                           dim3(64 * NW), lds, s, f);
-    }
-    if (bs.total > bs.interior) {
-        f.blk0 = bs.interior;
-        f.blk1 = bs.total;
-        hipLaunchKernelGGL((k_fused_lanes<MTC, NW, false>),
-                           dim3((unsigned)std::min<size_t>(bs.total - bs.interior, 2048)), dim3(64 * NW), lds, s, f);
-    }
-    return CERAR_OK;
-}
-
-template <int NW>
-int launch_fused_lanes_c(const FusedParams &a, const BlockSplit &bs, hipStream_t s) {
-    switch (a.c / 16) {
-        case 1: return launch_fused_lanes<1, NW>(a, bs, s);
-        case 2: return launch_fused_lanes<2, NW>(a, bs, s);
-        case 3: return launch_fused_lanes<3, NW>(a, bs, s);
-        default: return launch_fused_lanes<4, NW>(a, bs, s);
-    }
-}
-}  // namespace
 
 static int ring_simulate_fused_impl(const cerar_plan *plan, size_t d, const float *grads, size_t ld_grads,
                                     float *out, size_t ld_out, cerar_stream stream) {
@@ -2541,38 +2210,10 @@ static int ring_simulate_fused_impl(const cerar_plan *plan, size_t d, const floa
     const DeviceCopy *dc;
     st = device_copy(plan, &dc);
     if (st) return st;
-    FusedParams a;
-    a.grads = grads;
-    a.ld_g = ld_grads;
-    a.d = d;
-    a.out = out;
-    a.ld_o = ld_out;
-    a.efrag = dc->enc_frag;
-    a.dfrag = dc->dec_frag;
-    a.p = p;
-    a.N = N;
-    a.c = c;
-    a.L = plan->L;
-    a.KSd = plan->KSd;
-    const BlockSplit bs = split_blocks(plan, p, d, true);
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (N == 2 || N == 4 || N == 8) {
-        st = N == 2 ? launch_fused_lanes_c<2>(a, bs, s)
-                    : (N == 4 ? launch_fused_lanes_c<4>(a, bs, s) : launch_fused_lanes_c<8>(a, bs, s));
-        if (st) return st;
-    } else if (N <= 8) {
-        switch (c / 16) {
-            case 1: launch_fused<1, 512>(a, bs, lds, s); break;
-            case 2: launch_fused<2, 512>(a, bs, lds, s); break;
-            case 3: launch_fused<3, 512>(a, bs, lds, s); break;
-            default: launch_fused<4, 512>(a, bs, lds, s); break;
-        }
-    } else if (c <= 32) {
-        if (c == 16) launch_fused<1, 1024>(a, bs, lds, s);
-        else launch_fused<2, 1024>(a, bs, lds, s);
-    } else {
-        return fail(CERAR_E_INVAL, "the fused variant needs c <= 32 when N > 8");
-    }
+    if (N > 8 && c > 32) return fail(CERAR_E_INVAL, "the fused variant needs c <= 32 when N > 8");
+    PassParams a = pass_params(plan, dc, ld_grads, 0, ld_out);
+    add_instance(a, pass_positions(N, c), PassInst{grads, out, nullptr, nullptr, d, p, 0, 0});
+    launch_ring_pass(a, dc->cus, reinterpret_cast<hipStream_t>(stream));
     HIP_TRY(hipGetLastError(), "launch fused");
     return CERAR_OK;
 }
@@ -2843,6 +2484,20 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
     st = device_copy(plan, &dc);
     if (st) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (const int P = pass_positions(plan->N, plan->c)) {
+        // every bucket's encode, rounds and decode in one launch for up to
+        // kPassInst buckets
+        for (int b0 = 0; b0 < nbuckets; b0 += kPassInst) {
+            PassParams a = pass_params(plan, dc, ld_grads, ld_work, ld_out);
+            for (int b = b0; b < std::min(nbuckets, b0 + kPassInst); ++b)
+                add_instance(a, P, PassInst{grads + bucket_off[b], out + bucket_off[b], work + lay[b].work_off,
+                                            (float *)((char *)ws + lay[b].ws_off), bucket_len[b], lay[b].p,
+                                            lay[b].stride, 0});
+            launch_ring_pass(a, dc->cus, s);
+            HIP_TRY(hipGetLastError(), "launch ring pass");
+        }
+        return CERAR_OK;
+    }
     std::vector<Geometry> geo(nbuckets);
     bool all_vec = true;
     for (int b = 0; b < nbuckets; ++b) {

@@ -1,0 +1,430 @@
+// The whole all-reduce in one pass over the positions (k_ring_pass).
+//
+// Every step of the protocol acts on each position by itself, so a workgroup
+// that holds one block of positions of all N workers can encode it, run the
+// L rounds of Algorithm 1 and decode it without leaving the chip.  The call
+// leaves the same bytes in `work`, the workspace and `out` as the step calls
+// do: every message is still written to the slot that the ownership table
+// names for it, because it is an observation of the worker that receives it;
+// what falls away is reading it back.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+
+#include "cerar_internal.hpp"
+#include "device_util.hpp"
+#include "ring_pass.hpp"
+
+namespace cerar {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// V floats of one row; rows may start at any float, so the accesses claim
+// four-byte alignment only.
+template <int V>
+struct Vec {
+    typedef float T __attribute__((ext_vector_type(V)));
+    typedef float U __attribute__((ext_vector_type(V), aligned(4)));
+};
+template <int V>
+__device__ inline typename Vec<V>::T gload(const float *ubase, uint32_t lane_bytes) {
+    typedef __attribute__((address_space(1))) const typename Vec<V>::U GU;
+    typedef __attribute__((address_space(1))) const char GC;
+    return *(GU *)((GC *)ubase + lane_bytes);
+}
+template <int V>
+__device__ inline void gstore(float *ubase, uint32_t lane_bytes, typename Vec<V>::T v) {
+    typedef __attribute__((address_space(1))) typename Vec<V>::U GU;
+    typedef __attribute__((address_space(1))) char GC;
+    __builtin_nontemporal_store((typename Vec<V>::U)v, (GU *)((GC *)ubase + lane_bytes));
+}
+template <int V>
+__device__ inline void gstore_cached(float *ubase, uint32_t lane_bytes, typename Vec<V>::T v) {
+    typedef __attribute__((address_space(1))) typename Vec<V>::U GU;
+    typedef __attribute__((address_space(1))) char GC;
+    *(GU *)((GC *)ubase + lane_bytes) = v;
+}
+__device__ inline float gload1(const float *ptr) { return *(__attribute__((address_space(1))) const float *)ptr; }
+__device__ inline void gstore1(float *ptr, float v) { *(__attribute__((address_space(1))) float *)ptr = v; }
+
+// ptr + floats for a wave-uniform ptr, kept from being rewritten as base +
+// row x p: one live scalar pointer that steps from row to row instead of one
+// per row.
+template <class T>
+__device__ inline T *step(T *ptr, size_t floats) {
+    const size_t v = reinterpret_cast<size_t>(ptr + floats);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<T *>(opaque_s((size_t)hi << 32 | lo));
+}
+
+// Rows up to this length have the byte offsets of 13 rows in 32 bits (a
+// scalar base and a 32-bit lane offset); longer ones take the masked
+// accesses, which address each float in 64 bits.
+constexpr size_t kNarrow = (size_t)1 << 26;
+
+// The coefficients of a 16-row tile as MFMA A operands, one float per lane
+// and K-step; K-steps past the plan's repeat its last one (the B operands
+// there are zero).
+template <int KS>
+__device__ inline void load_frags(float (&f)[KS], const float *frag, int KSx, int lane) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) f[ks] = gload1(frag + (size_t)min(ks, KSx - 1) * 64 + lane);
+}
+
+// This lane's message in the next round: lane for worker w and position e
+// receives from the lane of worker w - 1 at the same position.  NX = N where
+// the N workers of a position sit in adjacent lanes and the exchange is a
+// data-parallel move within rows of 16 lanes; NX = 0: any N, worker by
+// worker across the wave, through ds_bpermute.
+template <int NX>
+__device__ inline float from_prev(float x, int prev_addr, bool first) {
+    const int v = __float_as_int(x);
+    if constexpr (NX == 2) return __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xB1, 15, 15, true));   // quad_perm 1,0,3,2
+    if constexpr (NX == 4) return __int_as_float(__builtin_amdgcn_mov_dpp(v, 0x93, 15, 15, true));   // quad_perm 3,0,1,2
+    if constexpr (NX == 8) {
+        const int a = __builtin_amdgcn_mov_dpp(v, 0x121, 15, 15, true);   // row_ror:1
+        const int b = __builtin_amdgcn_mov_dpp(v, 0x129, 15, 15, true);   // row_ror:9, the wrap within 8 lanes
+        return __int_as_float(first ? b : a);
+    }
+    if constexpr (NX == 16) return __int_as_float(__builtin_amdgcn_mov_dpp(v, 0x121, 15, 15, true));
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(prev_addr, v));
+}
+
+// The rounds of Algorithm 1 for the positions of one block.  rows: N regions
+// of WS floats, worker by worker, each c rows of P encoded chunks followed by
+// N - 1 free rows.  Afterwards row kk - (N - 1) holds Y column kk >= N - 1
+// (the chunk last used in round kk frees its row for it) and row c + kk
+// column kk < N - 1; the last column, delta_{.,c}, is already in its row.
+// stale: where delta_{.,c-1} of this block goes (no observation, but the step
+// calls leave it in its chunk's slot), or nullptr.
+template <int NX, int P>
+__device__ __forceinline__ void rounds(float *rows, int WS, int N, int c, int wave, int lane0, float *stale,
+                                       size_t ld_w, size_t left) {
+    const int lane = (int)opaque((uint32_t)lane0);        // the lane's place is worked out per block, not held
+    const int K = c + N - 1;
+    const int PW = NX ? 64 / (NX ? NX : 1) : 64 / N;      // positions per wave
+    const int rw = NX ? lane % (NX ? NX : 1) : lane / PW, rp = NX ? lane / (NX ? NX : 1) : lane - rw * PW;
+    const int prev_addr = NX ? 0 : 4 * (rw == 0 ? lane + (N - 1) * PW : lane - PW);
+    const bool first = rw == 0;
+    for (int base = wave * PW; base < P; base += N * PW) {
+        const int pos = base + rp;
+        if (rw >= N || pos >= P) continue;                // whole positions drop out: all N lanes of one
+        float *S = rows + rw * WS + pos;
+        float x = S[0];                                   // x_{rw,1} = delta_{rw,1}
+        if (stale && (size_t)pos < left) gstore1(stale + (size_t)rw * ld_w + pos, S[(c - 2) * P]);
+        for (int k = 1; k < N; ++k) {
+            const float add = S[k * P];
+            const float recv = from_prev<NX>(x, prev_addr, first);
+            S[(c + k - 1) * P] = recv;                    // B_{rw,k}
+            x = recv + add;
+        }
+        int k = N;
+        constexpr int U = 4;                              // chunks read one group of rounds ahead
+        if (k + U <= c) {
+            float add[U], sub[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                add[u] = S[(k + u) * P];
+                sub[u] = S[(k + u - N) * P];
+            }
+            for (; k + U <= c; k += U) {
+                float nadd[U], nsub[U];
+                const int kn = min(k + U, K - U);         // rows of the next group, or some that exist
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    nadd[u] = S[(kn + u) * P];
+                    nsub[u] = S[(kn + u - N) * P];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const float recv = from_prev<NX>(x, prev_addr, first);
+                    S[(k + u - N) * P] = recv;            // D_{rw,k+u-N+1}
+                    x = combine3(recv, sub[u], add[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    add[u] = nadd[u];
+                    sub[u] = nsub[u];
+                }
+            }
+        }
+        for (; k < c; ++k) {
+            const float sub = S[(k - N) * P], add = S[k * P];
+            const float recv = from_prev<NX>(x, prev_addr, first);
+            S[(k - N) * P] = recv;
+            x = combine3(recv, sub, add);
+        }
+        for (; k < K - 1; ++k) {                          // L = K - 1
+            const float sub = S[(k - N) * P];
+            const float recv = from_prev<NX>(x, prev_addr, first);
+            S[(k - N) * P] = recv;
+            x = recv - sub;
+        }
+        S[(c - 2) * P] = from_prev<NX>(x, prev_addr, first);   // round L stores D_{rw,c-1}; D_{rw,c} is delta_{rw,c}
+    }
+}
+
+// c <= 16 MTC chunks (EXC: c = 16 MTC), K <= 4 KSD observations, blocks of
+// P = 16 V positions, one wave per worker; persistent workgroups.
+//
+// What bounds it: the memory system on 100-200 rows per worker, 100s of MB
+// apart.  The same loads and stores alone, with neither rounds nor
+// contraction, take 2.66 of 2.78 ms at N = 8, c = 32, d = 124M (4.8 TB/s) and
+// 0.36 of 0.38 ms at c = 16, d = 2^24; at c = 64 the rounds and the fp32 MFMAs
+// add up (they exclude each other on this chip) and bound it.
+//  - The coefficients stay in registers over the whole sweep: a fragment
+//    load after the stores would wait for all of them to drain (memory
+//    operations of a wave complete in order).
+//  - The next block's gradient rows are loaded before the rounds and arrive
+//    while this block is in its rounds and its decode.
+//  - V = 4 (256-byte pieces of a row) where two workgroups of that size fit a
+//    CU, c <= 32; V = 2 above that (c = 64: 10.4 ms against 14.3 with V = 4,
+//    whose coefficients spill).
+template <int MTC, int KSD, int V, bool EXC, int MAXT, int WPE>
+__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) void k_ring_pass(PassParams a) {
+    typedef typename Vec<V>::T VT;
+    constexpr int KSE = 4 * MTC, P = 16 * V;
+    extern __shared__ __align__(16) float sm[];
+    const int N = a.N, c = EXC ? 16 * MTC : a.c, K = c + N - 1;
+    const int KSd = a.KSd;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, krow = lane >> 4;
+    const int WS = pass_region(N, K, P);
+    const int pv = w == 0 ? N - 1 : w - 1;                // the worker whose messages w receives
+    float *mine = sm + w * WS;
+
+    VT b[KSE];
+    auto load = [&](const PassInst &I, size_t e0) {
+        const size_t p = opaque_s(I.p), d = I.d;
+        const float *src = I.grads + (size_t)w * a.ld_g;
+        if (p < kNarrow && e0 + P <= p && (size_t)(c - 1) * p + e0 + P <= d) {   // every row of the block lies inside the gradient
+            const uint32_t lane_in = opaque((uint32_t)(((size_t)krow * p + V * (size_t)col) * sizeof(float)));
+            const float *row = src + e0;
+#pragma unroll
+            for (int ks = 0; ks < KSE; ++ks) {
+                if (EXC || 4 * ks + 3 < (int)opaque_s(c)) {
+                    b[ks] = gload<V>(row, lane_in);
+                } else {
+                    b[ks] = (VT)0.f;
+                    if (4 * ks + (int)opaque((uint32_t)krow) < c) b[ks] = gload<V>(row, lane_in);
+                }
+                row = step(row, 4 * p);
+            }
+        } else {
+            const int lrow = (int)opaque((uint32_t)krow), lcol = V * (int)opaque((uint32_t)col);
+#pragma unroll
+            for (int ks = 0; ks < KSE; ++ks) {
+                const int l = 4 * ks + lrow;
+                const size_t pos = e0 + lcol, flat = (size_t)l * p + pos;
+#pragma unroll
+                for (int t = 0; t < V; ++t) {
+                    b[ks][t] = 0.f;
+                    if (l < c && pos + t < p && flat + t < d) b[ks][t] = gload1(src + flat + t);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    float uf[MTC][KSE], rf[MTC][KSD];
+    // delta_w = U_w^T G_w^T on this block, rows j of P positions into LDS
+    auto encode = [&]() {
+#pragma unroll
+        for (int mt = 0; mt < MTC; ++mt) {
+            v4f acc[V];
+#pragma unroll
+            for (int t = 0; t < V; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KSE; ++ks)
+                if (EXC || 4 * ks < (int)opaque_s(c))
+#pragma unroll
+                    for (int t = 0; t < V; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(uf[mt][ks], b[ks][t], acc[t], 0, 0, 0);
+            // register r of lane (krow, col) is chunk 16 mt + 4 krow + r at positions V col + t
+            const int lrow = 16 * mt + 4 * (int)opaque((uint32_t)krow);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                VT v;
+#pragma unroll
+                for (int t = 0; t < V; ++t) v[t] = acc[t][r];
+                if (EXC || lrow + r < c) *reinterpret_cast<VT *>(mine + (lrow + r) * P + V * col) = v;
+            }
+        }
+    };
+
+    int q = 0;                                            // instance of the block in b
+    auto locate = [&](unsigned g) {
+        while (q + 1 < a.n && a.in[q + 1].blk0 <= g) ++q;
+    };
+    // Workgroups go to the 8 XCDs in turn.  Where rows do not start on a line
+    // (a.ragged), each XCD takes a contiguous run of blocks within one sweep of
+    // the grid, and the outputs are stored through the L2: the lines that two
+    // blocks share are then put together there instead of going to memory in
+    // parts (N = 8, c = 16, d = 28.5M, rows 96 bytes off: 603 -> 488 us; c = 64,
+    // odd d: 2.62 -> 2.09 ms).  With rows on lines the plain order and
+    // streaming stores are faster (c = 32: 2.70 against 2.74 ms).
+    unsigned g = a.ragged && gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
+    if (g >= a.nblk) return;
+    locate(g);
+    load(a.in[q], (size_t)(g - a.in[q].blk0) * P);
+#pragma unroll
+    for (int mt = 0; mt < MTC; ++mt) load_frags(uf[mt], a.efrag + ((size_t)w * MTC + mt) * a.KSe * 64, a.KSe, lane);
+#pragma unroll
+    for (int mt = 0; mt < MTC; ++mt) load_frags(rf[mt], a.dfrag + ((size_t)w * MTC + mt) * KSd * 64, KSd, lane);
+    encode();
+    for (;;) {
+        const PassInst &I = a.in[q];
+        const size_t p = I.p, d = I.d, ps = I.pool_stride;
+        const size_t e0 = (size_t)(g - I.blk0) * P;
+        const bool state = I.work != nullptr, full = p < kNarrow && e0 + P <= p;
+        g += gridDim.x;
+        const bool more = g < a.nblk;
+        if (more) {                                       // in flight during the rounds and the decode
+            locate(g);
+            load(a.in[q], (size_t)(g - a.in[q].blk0) * P);
+        }
+        __syncthreads();
+        {
+            float *stale = state ? I.work + (size_t)(c - 2) * p + e0 : nullptr;
+            const size_t left = p - e0;
+            if (N == 8) rounds<8, P>(sm, WS, 8, c, w, lane, stale, a.ld_w, left);
+            else if (N == 4) rounds<4, P>(sm, WS, 4, c, w, lane, stale, a.ld_w, left);
+            else if (N == 2) rounds<2, P>(sm, WS, 2, c, w, lane, stale, a.ld_w, left);
+            else if (MAXT > 512 && N == 16) rounds<16, P>(sm, WS, 16, c, w, lane, stale, a.ld_w, left);
+            else rounds<0, P>(sm, WS, N, c, w, lane, stale, a.ld_w, left);
+        }
+        __syncthreads();
+        // decode: ghat_w = Y_w R_w; the observations to their slots: column kk
+        // of Y_w is message kk + 1 of worker pv, in pv's pool for kk < N and
+        // in pv's freed chunks after that; the last column is w's own last chunk
+        v4f dacc[MTC][V];
+#pragma unroll
+        for (int mt = 0; mt < MTC; ++mt)
+#pragma unroll
+            for (int t = 0; t < V; ++t) dacc[mt][t] = v4f{0.f, 0.f, 0.f, 0.f};
+        float *own = I.work + (size_t)w * a.ld_w + (size_t)(c - 1) * p + e0;
+        float *rcv = I.work + (size_t)pv * a.ld_w + e0;
+        float *pool = I.pool + (size_t)pv * N * ps + e0;
+        const uint32_t lane_row = opaque((uint32_t)(((size_t)krow * p + V * (size_t)col) * sizeof(float)));
+        float *row4 = step(rcv, (size_t)0) - (size_t)N * p;   // column 4 ks, for 4 ks >= N
+        const float *yin = mine + (krow - (N - 1)) * P + V * col;
+#pragma unroll
+        for (int ks = 0; ks < KSD; ++ks) {
+            const int Nq = (int)opaque_s(N), Kq = (int)opaque_s(K);   // compared here, not held as masks
+            VT y = (VT)0.f;                               // rows past L meet zero coefficients
+            if (4 * ks >= Nq && 4 * ks + 3 < Kq - 1) {      // most K-steps lie in the columns N..K-2 as a whole
+                y = *reinterpret_cast<const VT *>(yin + 4 * ks * P);
+                if (state && full) gstore<V>(row4, lane_row, y);
+            } else if (4 * ks < Kq) {
+                const int kk = 4 * ks + (int)opaque((uint32_t)krow);
+                if (kk < K) y = *reinterpret_cast<const VT *>(mine + (kk - (N - 1) + (kk < N - 1 ? K : 0)) * P + V * col);
+                if (state && full && kk < K) {
+                    float *row = kk < N ? pool + (size_t)kk * ps : (kk < K - 1 ? rcv + (size_t)(kk - N) * p : own);
+                    gstore<V>(row, (uint32_t)(V * col * sizeof(float)), y);
+                }
+            }
+            row4 = step(row4, 4 * p);
+            if (4 * ks < Kq)
+#pragma unroll
+                for (int mt = 0; mt < MTC; ++mt)
+#pragma unroll
+                    for (int t = 0; t < V; ++t)
+                        dacc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(rf[mt][ks], y[t], dacc[mt][t], 0, 0, 0);
+        }
+        if (state && !full) {                             // the last block of a row where p is no multiple of P
+            for (int kk = krow; kk < K; kk += 4) {
+                const float *yr = mine + (kk - (N - 1) + (kk < N - 1 ? K : 0)) * P + V * col;
+                float *row = kk < N ? pool + (size_t)kk * ps : (kk < K - 1 ? rcv + (size_t)(kk - N) * p : own);
+                for (int t = 0; t < V; ++t)
+                    if (e0 + V * col + t < p) gstore1(row + V * col + t, yr[t]);
+            }
+        }
+        float *out = I.out + (size_t)w * a.ld_o;
+        if (full && (size_t)(c - 1) * p + e0 + P <= d) {
+            const uint32_t lane_out = opaque((uint32_t)(((size_t)(4 * krow) * p + V * (size_t)col) * sizeof(float)));
+            float *row = out + e0;
+            const bool ragged = a.ragged;
+#pragma unroll
+            for (int mt = 0; mt < MTC; ++mt) {
+                const int lrow = EXC ? 0 : 4 * (int)opaque((uint32_t)krow);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    VT v;
+#pragma unroll
+                    for (int t = 0; t < V; ++t) v[t] = dacc[mt][t][r];
+                    if (EXC || 16 * mt + lrow + r < c) {
+                        if (ragged) gstore_cached<V>(row, lane_out, v);
+                        else gstore<V>(row, lane_out, v);
+                    }
+                    row = step(row, r < 3 ? p : 13 * p);
+                }
+            }
+        } else {
+            const size_t pq = opaque_s(p);
+            const int lrow = 4 * (int)opaque((uint32_t)krow), lcol = V * (int)opaque((uint32_t)col);
+#pragma unroll
+            for (int mt = 0; mt < MTC; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = 16 * mt + lrow + r;
+                    const size_t pos = e0 + lcol, flat = (size_t)m * pq + pos;
+#pragma unroll
+                    for (int t = 0; t < V; ++t)
+                        if (m < c && pos + t < pq && flat + t < d) gstore1(out + flat + t, dacc[mt][t][r]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        }
+        if (!more) break;
+        encode();                                         // reads and writes this wave's own rows only
+    }
+}
+
+// Workgroups of a kernel that one CU holds at a time.
+template <class Kernel>
+int per_cu(Kernel k, int N, size_t lds) {
+    static const int waves = [&] {                        // wavefronts per SIMD that its registers allow
+        hipFuncAttributes at;
+        if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(k)) != hipSuccess) return 1;
+        return std::max(1, std::min(8, 512 / std::max(8, (at.numRegs + 7) / 8 * 8)));
+    }();
+    return std::max(1, std::min((int)(kPassLds / lds), 4 * waves / N));
+}
+
+template <int MTC, int KSD, int V, int MAXT, int WPE>
+void go(const PassParams &a, int cus, hipStream_t s) {
+    const size_t lds = pass_lds(a.N, a.c, V);
+    auto start = [&](auto kernel) {
+        const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
+        const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * per_cu(kernel, a.N, lds)));
+        hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64u * (unsigned)a.N), lds, s, a);
+    };
+    if (a.c == 16 * MTC) start(k_ring_pass<MTC, KSD, V, true, MAXT, WPE>);
+    else start(k_ring_pass<MTC, KSD, V, false, MAXT, WPE>);
+}
+
+}  // namespace
+
+// N <= 8: c <= 64; 8 < N <= 16: c <= 32, where sixteen waves leave each half
+// the registers.
+int pass_positions(int N, int c) {
+    if (N > 16 || c > (N > 8 ? 32 : 64)) return 0;
+    return N > 8 ? 32 : (c <= 32 ? 64 : 32);
+}
+
+void launch_ring_pass(const PassParams &a, int cus, hipStream_t s) {
+    const int mt = (a.c + 15) / 16;
+    if (a.N > 8) {
+        if (mt == 1) go<1, 8, 2, 1024, 4>(a, cus, s);
+        else go<2, 12, 2, 1024, 4>(a, cus, s);
+        return;
+    }
+    switch (mt) {
+        case 1: go<1, 6, 4, 512, 4>(a, cus, s); break;
+        case 2: go<2, 10, 4, 512, 4>(a, cus, s); break;
+        case 3: go<3, 14, 2, 512, 2>(a, cus, s); break;
+        default: go<4, 18, 2, 512, 2>(a, cus, s); break;
+    }
+}
+
+}  // namespace cerar

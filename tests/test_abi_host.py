@@ -402,3 +402,22 @@ def test_als_restarts_keep_the_least_phi():
     with pytest.raises(C.CerarError) as ei:
         C.Plan(N, c, "kappa", kmax, seed=5, als_restarts=65)
     assert ei.value.status == -1
+
+
+@pytest.mark.parametrize("N", [2, 3, 4, 7, 8, 9, 16])
+@pytest.mark.parametrize("extra", [0, 1, 2, 15, 50])
+def test_observations_lie_where_the_one_pass_kernel_writes_them(N, extra):
+    """Column k of Y_i after round L: message k + 1 of worker i - 1, in that
+    worker's pool for k < N and in its chunk k - N after that; the last column
+    is worker i's own last chunk.  The one slot per worker that is no
+    observation is its chunk c - 2 (delta_{.,c-1})."""
+    c = N + extra
+    plan = C.Plan.explicit(np.stack([np.eye(c)] * N), np.zeros((N, c + N - 1, c)))
+    sm, K, used = plan.slot_map(plan.L), c + N - 1, set()
+    for i in range(N):
+        pv = (i - 1) % N
+        cols = [sm[i, c + j] for j in range(N - 1)] + [sm[i, j] for j in range(c)]
+        assert cols == [N * c + pv * N + k if k < N else (pv * c + k - N if k < K - 1 else i * c + c - 1)
+                        for k in range(K)]
+        used |= set(cols)
+    assert set(range(N * (c + N))) - used == {i * c + c - 2 for i in range(N)}

@@ -1,0 +1,116 @@
+"""The one-pass kernel behind ring_simulate, its no-alloc, bucketed and fused
+forms, against the step calls: they run the same arithmetic in the same
+order, so the outputs, every slot of `work` and every message slot of the
+workspace must hold the same bits.  Shapes sit at the edges of its tiles (16
+chunks, blocks of 64 or 32 positions), its rules (N = 8 | 9, c = 32 | 33 and
+64 | 65) and its rows (any row start, odd lengths, pads of several chunks)."""
+
+import numpy as np
+import pytest
+
+from paper_2609_23898_amd import cerar as C
+
+from gpu_util import buffers, host_grads, orthogonal_plan, to_device, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # N, c, d, row offset in floats (misaligned rows), extra row stride
+    (2, 2, 2 * 64, 0, 0), (2, 3, 1, 0, 0), (2, 15, 15 * 96 + 1, 0, 0), (3, 16, 16 * 64, 0, 0),
+    (4, 12, 12 * 4096 + 7, 1, 1), (5, 17, 17 * 130 - 3, 0, 3), (6, 31, 31 * 64 - 40, 0, 0), (7, 32, 32 * 95, 3, 2),
+    (8, 8, 8 * 65, 0, 0), (8, 20, 20 * 640 + 13, 0, 0), (8, 32, 32 * 64 * 9 + 5, 0, 0), (8, 33, 33 * 97, 1, 0),
+    (3, 47, 47 * 32 - 1, 0, 0), (8, 48, 48 * 160 - 65, 0, 1), (2, 49, 49 * 33, 0, 0), (4, 63, 63 * 64 + 2, 2, 0),
+    (8, 64, 64 * 333 + 9, 0, 0), (7, 64, 64 * 64, 0, 0), (8, 64, 5, 0, 0),
+    (9, 16, 16 * 97, 0, 0), (9, 9, 9 * 64 + 1, 0, 0), (13, 17, 17 * 64 - 5, 1, 1), (16, 16, 16 * 65, 0, 0),
+    (16, 32, 32 * 321 - 7, 0, 0), (9, 33, 33 * 64, 0, 0), (8, 65, 65 * 64 - 1, 0, 0),
+]
+
+
+def _state(plan, d, work, ws):
+    """All N (c + N) slots' p floats: the workers' chunks, then the messages."""
+    torch, _ = torch_dev()
+    p, stride = plan.chunk_len(d)
+    pool = ws.view(torch.float32).view(plan.N * plan.N, stride)[:, :p]
+    return work[:, :plan.c * p].clone(), pool.clone()
+
+
+def _steps(plan, d, grads, work, ws, out):
+    for k in range(plan.L + 1):
+        C.encode_round(plan, k, d, grads, work, ws)
+    C.decode(plan, d, work, ws, out)
+
+
+@pytest.mark.parametrize("N,c,d,off,extra", SHAPES)
+def test_one_pass_leaves_the_step_calls_bits(N, c, d, off, extra):
+    torch, _ = torch_dev()
+    U, R = orthogonal_plan(N, c, seed=N * 100 + c) if c > N else (
+        np.stack([np.linalg.qr(np.random.default_rng(c + k).standard_normal((c, c)))[0] for k in range(N)]),
+        np.random.default_rng(c).standard_normal((N, c + N - 1, c)))
+    plan = C.Plan.explicit(U, R)
+    p, _ = plan.chunk_len(d)
+    grads = to_device(host_grads(N, d, seed=c + d), ld=d + extra, align_elems=off)
+    got, want = (buffers(plan, d, ld_work=c * p + extra, ld_out=d + extra, work_offset=off, out_offset=off)
+                 for _ in range(2))
+    C.ring_simulate(plan, d, grads, *got)
+    _steps(plan, d, grads, *want)
+    torch.cuda.synchronize()
+    assert torch.equal(got[2][:, :d], want[2][:, :d])
+    assert bool(torch.isnan(got[2][:, d:]).all()) and bool(torch.isnan(got[0][:, c * p:]).all())
+    for a, b in zip(_state(plan, d, got[0], got[1]), _state(plan, d, want[0], want[1])):
+        assert torch.equal(a, b)
+    again = got[2].clone()
+    got[2].fill_(float("nan"))
+    C.decode(plan, d, got[0], got[1], got[2])       # the observations decode again
+    torch.cuda.synchronize()
+    assert torch.equal(got[2][:, :d], again[:, :d])
+
+
+@pytest.mark.parametrize("N,c,lens", [(8, 20, [20 * 64 * 5 + 3, 1, 20 * 63, 7777]), (3, 64, [64 * 33, 64 * 31 + 5]),
+                                      (4, 12, [97 * (b + 1) for b in range(33)])])
+def test_buckets_equal_calls_of_their_own(N, c, lens):
+    """Odd offsets and lengths, more buckets than one launch takes: each bucket
+    has the bits of its own call."""
+    torch, dev = torch_dev()
+    U, R = orthogonal_plan(N, c, seed=c)
+    plan = C.Plan.explicit(U, R)
+    offs = np.concatenate([[0], np.cumsum(lens)[:-1]]).tolist()
+    d = sum(lens)
+    grads = to_device(host_grads(N, d, seed=c))
+    wf, wsb = plan.bucketed_sizes(lens)
+    work = torch.full((N, wf), float("nan"), dtype=torch.float32, device=dev)
+    ws = torch.zeros(wsb, dtype=torch.uint8, device=dev)
+    out = torch.full((N, d), float("nan"), dtype=torch.float32, device=dev)
+    C.ring_simulate_bucketed(plan, list(zip(offs, lens)), grads, work, ws, out)
+    at = 0
+    for o, n in zip(offs, lens):
+        one = buffers(plan, n)
+        C.ring_simulate(plan, n, grads[:, o:o + n], *one)
+        torch.cuda.synchronize()
+        cp = c * plan.chunk_len(n)[0]
+        assert torch.equal(out[:, o:o + n], one[2]), (o, n)
+        assert torch.equal(work[:, at:at + cp], one[0]), (o, n)
+        at += cp
+
+
+@pytest.mark.parametrize("seed", [0, 1])
+def test_infinities_and_nan_stay_in_their_columns(seed):
+    """A position whose gradients hold an infinity or NaN gives the step calls'
+    results, and no other position sees it (zero padding of the tiles and the
+    rows past K meets no such value)."""
+    torch, _ = torch_dev()
+    N, c = (8, 20) if seed == 0 else (3, 33)
+    d = c * 192 - 11
+    U, R = orthogonal_plan(N, c, seed=5)
+    plan = C.Plan.explicit(U, R)
+    p, _ = plan.chunk_len(d)
+    g = host_grads(N, d, seed=6)
+    bad = [3, 70, 131]
+    g[0, bad[0]], g[1, p + bad[1]], g[N - 1, (c - 2) * p + bad[2]] = np.inf, -np.inf, np.nan
+    got, want = buffers(plan, d), buffers(plan, d)
+    C.ring_simulate(plan, d, to_device(g), *got)
+    _steps(plan, d, to_device(g), *want)
+    torch.cuda.synchronize()
+    a, b = got[2].cpu().numpy(), want[2].cpu().numpy()
+    np.testing.assert_array_equal(a, b)
+    clean = ~np.isin(np.arange(d) % p, bad)
+    assert np.all(np.isfinite(a[:, clean]))
