@@ -1937,7 +1937,15 @@ int enqueue_ring(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g
         return CERAR_OK;
     }
     int st = enqueue_encode(plan, dc, g, d, grads, ld_grads, work, ld_work, ws, s);
-    for (int k = 1; k <= plan->L && !st; ++k) st = enqueue_round(plan, dc, g, k, work, ld_work, ws, s);
+    if (const int P = rounds_positions(plan->N)) {
+        if (st) return st;
+        PassParams a = pass_params(plan, dc, ld_work, ld_work, ld_work);
+        add_instance(a, P, PassInst{work, work, work, (float *)ws, d, g.p, g.pool_stride, 0});
+        launch_rounds_pass(a, dc->cus, s);
+        HIP_TRY(hipGetLastError(), "launch rounds pass");
+    } else {
+        for (int k = 1; k <= plan->L && !st; ++k) st = enqueue_round(plan, dc, g, k, work, ld_work, ws, s);
+    }
     if (!st) st = enqueue_decode(plan, dc, g, d, work, ld_work, ws, out, ld_out, s);
     return st;
 }
@@ -2526,7 +2534,18 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
     for (int b = 0; b < nbuckets && !st && !batched; ++b)
         st = enqueue_encode(plan, dc, geo[b], bucket_len[b], grads + bucket_off[b], ld_grads, work + lay[b].work_off,
                             ld_work, (char *)ws + lay[b].ws_off, s);
-    for (int k = 1; k < plan->L && !st; ++k) {
+    const int P = rounds_positions(plan->N);
+    for (int b0 = 0; b0 < nbuckets && P && !st; b0 += kPassInst) {
+        PassParams a = pass_params(plan, dc, ld_work, ld_work, ld_work);
+        for (int b = b0; b < std::min(nbuckets, b0 + kPassInst); ++b) {
+            float *wb = work + lay[b].work_off;
+            add_instance(a, P, PassInst{wb, wb, wb, (float *)((char *)ws + lay[b].ws_off), bucket_len[b], lay[b].p,
+                                        lay[b].stride, 0});
+        }
+        launch_rounds_pass(a, dc->cus, s);
+        HIP_TRY(hipGetLastError(), "launch rounds pass");
+    }
+    for (int k = 1; k < plan->L && !st && !P; ++k) {
         for (int b0 = 0; b0 < nbuckets;) {
             BatchRoundParams a;
             a.ops = dc->rounds + (size_t)k * N;

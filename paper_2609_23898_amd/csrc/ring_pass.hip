@@ -380,6 +380,119 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
     }
 }
 
+// All rounds of Algorithm 1 in one launch, for the plans the kernel above does
+// not take: encoded chunks from `work`, observations to their slots.  N
+// waves; each loads its worker's chunk rows (four rows of 64 positions per
+// instruction) and stores the observations of the worker it receives for.
+//
+// Streams rows through LDS in groups of R rounds: a region of N + R rows per
+// worker holds the chunks of the last N rounds (still to be subtracted) and
+// of the group; the observation of round k takes the row of chunk k - N, is
+// stored after the group, and the group after next loads into it.
+//
+// Bound by memory: reads every chunk and writes every observation once (2c + N
+// rows per worker) where one launch per round moves 4c + 2N.
+constexpr int kGroup = 16;
+
+template <int NX>
+__device__ __forceinline__ void group_rounds(float *rows, int WS, int N, int c, int wave, int lane0, int k0, int k1,
+                                             float (&x)[2]) {
+    constexpr int P = 64;
+    const int lane = (int)opaque((uint32_t)lane0);
+    const int PW = NX ? 64 / (NX ? NX : 1) : 64 / N;
+    const int rw = NX ? lane % (NX ? NX : 1) : lane / PW, rp = NX ? lane / (NX ? NX : 1) : lane - rw * PW;
+    const int prev_addr = NX ? 0 : 4 * (rw == 0 ? lane + (N - 1) * PW : lane - PW);
+    const bool first = rw == 0;
+    const int C = N + kGroup;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int pos = (wave + h * N) * PW + rp;
+        if ((wave + h * N) * PW >= P) break;
+        if (rw >= N || pos >= P) continue;                // whole positions drop out: all N lanes of one
+        float *S = rows + rw * WS + pos;
+        int k = k0;
+        if (k == 0) {
+            x[h] = S[0];                                  // x_{rw,1} = delta_{rw,1}
+            k = 1;
+        }
+        int sa = k % C, sy = (k + kGroup) % C;            // rows of chunk k and of chunk k - N
+        for (; k < k1; ++k) {
+            const float add = S[sa * P], sub = S[sy * P];
+            const float recv = from_prev<NX>(x[h], prev_addr, first);
+            S[sy * P] = recv;
+            if (k < N) x[h] = recv + add;
+            else if (k < c) x[h] = combine3(recv, sub, add);
+            else x[h] = recv - sub;
+            sa = sa + 1 == C ? 0 : sa + 1;
+            sy = sy + 1 == C ? 0 : sy + 1;
+        }
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_rounds_pass(PassParams a) {
+    typedef Vec<4>::T VT;
+    constexpr int P = 64, R = kGroup, Q = R / 4;
+    extern __shared__ __align__(16) float sm[];
+    const int N = a.N, c = a.c, K = c + N - 1, C = N + R;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, krow = lane >> 4;
+    const int WS = pass_region(N, C, P);
+    const int pv = w == 0 ? N - 1 : w - 1;                // the worker whose messages w receives
+    float *mine = sm + w * WS + 4 * col;
+    int q = 0;
+    unsigned g = a.ragged && gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
+    for (; g < a.nblk; g += gridDim.x) {
+        while (q + 1 < a.n && a.in[q + 1].blk0 <= g) ++q;
+        const PassInst &I = a.in[q];
+        const size_t p = I.p, ps = I.pool_stride;
+        const size_t e = (size_t)(g - I.blk0) * P + 4 * col;
+        const bool in = e < p;                            // p is a multiple of 32: a lane's four positions are in or out
+        const float *src = I.work + (size_t)w * a.ld_w + e;
+        float *rcv = I.work + (size_t)pv * a.ld_w + e;
+        float *pool = I.pool + (size_t)pv * N * ps + e;
+        VT b[Q];
+        auto load = [&](int r0) {                         // chunks r0 .. r0 + R - 1 of worker w
+#pragma unroll
+            for (int u = 0; u < Q; ++u) {
+                const int r = r0 + 4 * u + krow;
+                b[u] = (VT)0.f;
+                if (in && r < c) b[u] = gload<4>(src + (size_t)r * p, 0);
+            }
+        };
+        auto put = [&](int r0) {
+#pragma unroll
+            for (int u = 0; u < Q; ++u) *reinterpret_cast<VT *>(mine + (r0 + 4 * u + krow) % C * P) = b[u];
+        };
+        float x[2] = {0.f, 0.f};
+        __syncthreads();                                  // the block before is out of LDS
+        load(0);
+        put(0);
+        load(R);
+        for (int k0 = 0; k0 < K; k0 += R) {
+            const int k1 = min(K, k0 + R);
+            __syncthreads();
+            if (N == 8) group_rounds<8>(sm, WS, 8, c, w, lane, k0, k1, x);
+            else if (N == 4) group_rounds<4>(sm, WS, 4, c, w, lane, k0, k1, x);
+            else if (N == 2) group_rounds<2>(sm, WS, 2, c, w, lane, k0, k1, x);
+            else if (N == 16) group_rounds<16>(sm, WS, 16, c, w, lane, k0, k1, x);
+            else group_rounds<0>(sm, WS, N, c, w, lane, k0, k1, x);
+            __syncthreads();
+            // round k's observation is column k - 1 of Y_w: message k of worker pv
+#pragma unroll
+            for (int u = 0; u < Q; ++u) {
+                const int k = k0 + 4 * u + krow;
+                const VT y = *reinterpret_cast<const VT *>(mine + (k + R) % C * P);
+                if (in && k >= 1 && k < k1)
+                    gstore<4>(k <= N ? pool + (size_t)(k - 1) * ps : rcv + (size_t)(k - 1 - N) * p, 0, y);
+            }
+            if (k0 + R < K) {
+                put(k0 + R);
+                load(k0 + 2 * R);
+            }
+        }
+    }
+}
+
 // Workgroups of a kernel that one CU holds at a time.
 template <class Kernel>
 int per_cu(Kernel k, int N, size_t lds) {
@@ -410,6 +523,15 @@ void go(const PassParams &a, int cus, hipStream_t s) {
 int pass_positions(int N, int c) {
     if (N > 16 || c > (N > 8 ? 32 : 64)) return 0;
     return N > 8 ? 32 : (c <= 32 ? 64 : 32);
+}
+
+int rounds_positions(int N) { return N <= 16 ? 64 : 0; }
+
+void launch_rounds_pass(const PassParams &a, int cus, hipStream_t s) {
+    const size_t lds = (size_t)a.N * pass_region(a.N, a.N + kGroup, 64) * sizeof(float);
+    const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
+    const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * per_cu(k_rounds_pass, a.N, lds)));
+    hipLaunchKernelGGL(k_rounds_pass, dim3(wgs), dim3(64u * (unsigned)a.N), lds, s, a);
 }
 
 void launch_ring_pass(const PassParams &a, int cus, hipStream_t s) {

@@ -40,4 +40,9 @@ int pass_positions(int N, int c);
 // One launch; cus: compute units of the current device.
 void launch_ring_pass(const PassParams &a, int cus, hipStream_t s);
 
+// The rounds alone, for the other plans: reads the encoded chunks in `work`
+// (grads and out unused); 0 where N is too large for it.
+int rounds_positions(int N);
+void launch_rounds_pass(const PassParams &a, int cus, hipStream_t s);
+
 }  // namespace cerar

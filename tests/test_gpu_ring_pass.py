@@ -22,7 +22,10 @@ SHAPES = [
     (3, 47, 47 * 32 - 1, 0, 0), (8, 48, 48 * 160 - 65, 0, 1), (2, 49, 49 * 33, 0, 0), (4, 63, 63 * 64 + 2, 2, 0),
     (8, 64, 64 * 333 + 9, 0, 0), (7, 64, 64 * 64, 0, 0), (8, 64, 5, 0, 0),
     (9, 16, 16 * 97, 0, 0), (9, 9, 9 * 64 + 1, 0, 0), (13, 17, 17 * 64 - 5, 1, 1), (16, 16, 16 * 65, 0, 0),
-    (16, 32, 32 * 321 - 7, 0, 0), (9, 33, 33 * 64, 0, 0), (8, 65, 65 * 64 - 1, 0, 0),
+    (16, 32, 32 * 321 - 7, 0, 0),
+    # the rounds pass between the step calls' encode and decode
+    (9, 33, 33 * 64, 0, 0), (8, 65, 65 * 64 - 1, 0, 0), (2, 128, 128 * 96, 1, 1), (12, 90, 90 * 97 - 3, 0, 0),
+    (16, 128, 128 * 160 + 1, 0, 0), (13, 33, 7, 0, 0), (5, 80, 80 * 64 * 3, 3, 0), (17, 40, 40 * 64, 0, 0),
 ]
 
 
@@ -66,7 +69,8 @@ def test_one_pass_leaves_the_step_calls_bits(N, c, d, off, extra):
 
 
 @pytest.mark.parametrize("N,c,lens", [(8, 20, [20 * 64 * 5 + 3, 1, 20 * 63, 7777]), (3, 64, [64 * 33, 64 * 31 + 5]),
-                                      (4, 12, [97 * (b + 1) for b in range(33)])])
+                                      (4, 12, [97 * (b + 1) for b in range(33)]),
+                                      (8, 70, [70 * 64 + 1, 70 * 200, 9]), (16, 64, [64 * 96] * 3)])
 def test_buckets_equal_calls_of_their_own(N, c, lens):
     """Odd offsets and lengths, more buckets than one launch takes: each bucket
     has the bits of its own call."""
