@@ -32,9 +32,10 @@
  *    that share buffers must be ordered by the caller (one stream does
  *    that).
  *  - Data on the device (gradients, encoded chunks, messages, outputs) is
- *    IEEE fp32.  The encode and decode contractions accumulate in fp32; at
- *    c = 128 their fp32 operands are split exactly into three bf16 terms and
- *    six of the nine term products are summed on the bf16 matrix cores
+ *    IEEE fp32.  The encode and decode contractions accumulate in fp32; where
+ *    c > 32 and the plan is beyond the one-pass kernel (cerar_ring_simulate)
+ *    their fp32 operands are split exactly into three bf16 terms and six of
+ *    the nine term products are summed on the bf16 matrix cores
  *    (within two units of fp32 rounding per product).  A round forms
  *    recv - delta_j + delta_{k+1} in fp64 and rounds the message to fp32
  *    once.  The error norms accumulate in fp64.  Plan construction is host

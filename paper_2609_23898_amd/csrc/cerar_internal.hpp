@@ -1,6 +1,7 @@
 // Internal structures shared by the host plan code and the HIP launchers.
 #pragma once
 
+#include <cstdint>
 #include <exception>
 #include <map>
 #include <mutex>
@@ -47,6 +48,18 @@ struct RingTables {
     int pool_slots() const { return N * N; }
 };
 
+// Chunks of 32 K-steps of the split contraction (bf16 matrix cores, six
+// products), or 0 where c <= 32 and the fp32 one stays: 2, 3 or 4 for the
+// encode, and that many and a 16-step tail for the decode where its K = c + N -
+// 1 observations fit them.
+inline int split_chunks(int c) { return c <= 32 ? 0 : (c <= 64 ? 2 : (c <= 96 ? 3 : 4)); }
+inline bool split_decode_fits(int N, int c) { return c > 32 && c + N - 1 <= 32 * split_chunks(c) + 16; }
+// bf16 of one 16-row tile of a worker's split operands: per chunk and term 64
+// lanes of 8, and for the decode per term 64 lanes of 4 of the tail.  A worker
+// has 2 KC tiles (zero beyond c rows).
+constexpr int split_tile_encode(int KC) { return KC * 3 * 64 * 8; }
+constexpr int split_tile_decode(int KC) { return KC * 3 * 64 * 8 + 3 * 64 * 4; }
+
 // Builds the tables and checks that no launch reads a slot another worker
 // writes in the same launch.  Returns an empty string or a diagnostic.
 std::string build_ring_tables(int N, int c, RingTables &t);
@@ -56,6 +69,8 @@ struct DeviceCopy {
     float *dec_frag = nullptr;       // N x MT x KSd x 64 fp32 fragments of R_i
     int *ycols = nullptr;            // N x (L+1) slot ids
     RoundOp *rounds = nullptr;       // (L+1) x N
+    uint16_t *enc_split = nullptr;   // the split operands of U_i and R_i (plans with KC > 0)
+    uint16_t *dec_split = nullptr;
     int cus = 0;                     // compute units of the device
 };
 
@@ -72,6 +87,8 @@ struct cerar_plan {
     cerar::RingTables tab;
     int MT = 0, KSe = 0, KSd = 0;    // M-tiles, encode K-steps, decode K-steps
     std::vector<float> enc_frag, dec_frag;
+    int KC = 0;                      // 32-step chunks of the split contraction, 0 where it is not used
+    std::vector<uint16_t> enc_split, dec_split;   // bf16 bits, see split_tile_encode / split_tile_decode
     mutable std::mutex dev_mu;
     mutable std::map<int, cerar::DeviceCopy> dev;   // per HIP device ordinal
 };

@@ -2,14 +2,13 @@
 //
 //  k_encode  (K1)  delta_{i,j} = sum_l U_i[l][j] chunk_l(g_i), all workers,
 //                  as fp32 MFMA 16x16x4 tiles: delta^T = U^T G^T, positions
-//                  on the MFMA N axis, coefficients (A operand) from LDS; at
-//                  c = 128 on bf16 MFMAs with fp32 operands split exactly
-//                  into three bf16 terms (k_encode_split).
+//                  on the MFMA N axis, coefficients (A operand) from LDS (plans
+//                  with c > 32 beyond the one-pass kernel: split.hip).
 //  k_round   (K2/K3) one ring round for all workers: next message =
 //                  received (- returning own term) (+ next own term).
 //  k_decode  (K4)  g_hat_i = Y_i R_i, the same MFMA tiling over the L+1
 //                  stored observations, gathered through the slot table
-//                  (k_decode_split at c = 128).
+//                  (split.hip as above).
 //  k_norms   (K5)  per-worker squared error against S = sum_w g_w, fp64,
 //                  and on sampled positions against given reference values.
 //  k_copy          plain streaming copy (bandwidth reference).
@@ -145,9 +144,6 @@ __device__ inline void nt_store(float *ptr, v4f v) { __builtin_nontemporal_store
 // stream with non-temporal loads, which measured faster for them).
 __device__ inline v4f load_off(const float *ubase, uint32_t lane_bytes) {
     return *reinterpret_cast<const v4f *>(reinterpret_cast<const char *>(ubase) + lane_bytes);
-}
-__device__ inline v2f load2_off(const float *ubase, uint32_t lane_bytes) {
-    return *reinterpret_cast<const v2f *>(reinterpret_cast<const char *>(ubase) + lane_bytes);
 }
 __device__ inline v2f nt_load2_g(const float *ptr) {
     typedef __attribute__((address_space(1))) const v2f global_cv2f;
@@ -311,29 +307,22 @@ struct EncBatch {
     }
 };
 
-// FAST: interior blocks only (full rows, no masks, non-temporal 16-byte
-// accesses); otherwise the masked path for tails and the scalar layout.
-template <int KS, bool VEC, bool AREG, bool FAST>
+// Masked encode: tails, c no multiple of 16, and the scalar layout.
+template <int KS, bool VEC>
 __device__ __forceinline__ void k_encode_body(const EncParams &a, unsigned bid) {
-    extern __shared__ float sfrag[];
     const int worker = bid % a.N;           // workers interleaved across the grid
     const int wg = bid / a.N;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, krow = lane >> 4;
     const int nmt = a.mt1 - a.mt0;
-    const int KSx = a.KSe, KS4 = (KSx + 3) / 4;
+    const int KSx = a.KSe;
     const float *gfrag = a.frag + ((size_t)worker * a.MT + a.mt0) * KSx * 64;
-    float av[AREG ? kMaxRegTiles : 1][KS];
-    if (AREG) {
+    float av[kMaxRegTiles][KS];
 #pragma unroll
-        for (int mt = 0; mt < kMaxRegTiles; ++mt)
+    for (int mt = 0; mt < kMaxRegTiles; ++mt)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                av[mt][ks] = (mt < nmt && ks < KSx) ? gfrag[((size_t)mt * KSx + ks) * 64 + lane] : 0.f;
-    } else {
-        stage_fragments(sfrag, gfrag, nmt, KSx);
-        __syncthreads();
-    }
+        for (int ks = 0; ks < KS; ++ks)
+            av[mt][ks] = (mt < nmt && ks < KSx) ? gfrag[((size_t)mt * KSx + ks) * 64 + lane] : 0.f;
     const float *src = a.grads + (size_t)worker * a.ld_g;
     float *dst = a.sb.work + (size_t)worker * a.sb.ld_work;
     float *x1 = a.sb.pool + (size_t)worker * a.N * a.sb.pool_stride;   // worker's first pool slot
@@ -342,37 +331,24 @@ __device__ __forceinline__ void k_encode_body(const EncParams &a, unsigned bid) 
     for (size_t blk = first + wave; blk < end; blk += kWaves) {
         const size_t e0 = blk * 64;
         v4f b[KS];
-        if (FAST) {
-            // K-steps past c/4 re-read the last real one; their coefficients are zero
-            const uint32_t lane_in = opaque((uint32_t)(((size_t)krow * p + 4 * (size_t)col) * sizeof(float)));
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                b[ks] = load_off(src + e0 + (size_t)(4 * min(ks, KSx - 1)) * p, lane_in);
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int l = ks * 4 + krow;
-                b[ks] = (ks < KSx && l < a.c) ? load_tile<VEC>(src + (size_t)l * p, (size_t)l * p, e0, col, p, a.d)
-                                              : v4f{0.f, 0.f, 0.f, 0.f};
-            }
+        for (int ks = 0; ks < KS; ++ks) {
+            const int l = ks * 4 + krow;
+            b[ks] = (ks < KSx && l < a.c) ? load_tile<VEC>(src + (size_t)l * p, (size_t)l * p, e0, col, p, a.d)
+                                          : v4f{0.f, 0.f, 0.f, 0.f};
         }
-        const uint32_t lane_out = opaque((uint32_t)(((size_t)(krow * 4) * p + 4 * (size_t)col) * sizeof(float)));
 #pragma unroll
-        for (int mt = 0; mt < (AREG ? kMaxRegTiles : 1); ++mt) {
-            for (int m2 = mt; m2 < (AREG ? mt + 1 : nmt); ++m2) {
-                if (m2 >= nmt) break;
+        for (int mt = 0; mt < kMaxRegTiles; ++mt) {
+            if (mt < nmt) {
                 v4f acc[4];
-                mtile_mma<KS, AREG>(acc, b, av[AREG ? mt : 0], sfrag + (size_t)m2 * KS4 * 256, KSx, lane);
+                mtile_mma<KS, true>(acc, b, av[mt], nullptr, KSx, lane);
                 // D fragment: lane (krow, col), register r holds output row 4 krow + r.
-                const int jt = (a.mt0 + m2) * 16;
+                const int jt = (a.mt0 + mt) * 16;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int j = jt + krow * 4 + r;
                     const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-                    if (FAST) {
-                        nt_store_off(dst + e0 + (size_t)(jt + r) * p, lane_out, v);   // j < c: 16 | c
-                        if (j == 0) nt_store_off(x1 + e0, (uint32_t)(4 * col * sizeof(float)), v);
-                    } else if (j < a.c) {
+                    if (j < a.c) {
                         store_tile<VEC>(dst + (size_t)j * p, 0, e0, col, p, p, v);
                         if (j == 0) store_tile<VEC>(x1, 0, e0, col, p, p, v);
                     }
@@ -382,14 +358,14 @@ __device__ __forceinline__ void k_encode_body(const EncParams &a, unsigned bid) 
     }
 }
 
-template <int KS, bool VEC, bool AREG, bool FAST>
-__global__ __launch_bounds__(kThreads) void k_encode(EncParams a) { k_encode_body<KS, VEC, AREG, FAST>(a, blockIdx.x); }
+template <int KS, bool VEC>
+__global__ __launch_bounds__(kThreads) void k_encode(EncParams a) { k_encode_body<KS, VEC>(a, blockIdx.x); }
 
-template <int KS, bool VEC, bool AREG, bool FAST>
+template <int KS, bool VEC>
 __global__ __launch_bounds__(kThreads) void k_encode_batch(EncBatch b) {
     unsigned bid;
     const EncParams a = b.at(bid);
-    k_encode_body<KS, VEC, AREG, FAST>(a, bid);
+    k_encode_body<KS, VEC>(a, bid);
 }
 
 // Pipelined interior encode for c <= 64 (up to 4 M-tiles): the coefficients
@@ -991,339 +967,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     }
 }
 
-// ---- c = 128: the contraction on bf16 MFMAs at fp32 accuracy -----------------
-// At c = 128 the encode and decode do 32 flop per algorithmic byte, and the
-// fp32 MFMA rate bounds them: with the contraction taken out, the same loads
-// and stores take two thirds of the time.  Here every fp32 operand x is
-// split exactly into three bf16 terms, x = h + m + l: h is x rounded to bf16
-// (round to nearest even), m the remainder rounded to bf16, l the rest, which
-// bf16 holds exactly (8 significant bits).  Of the nine products of two split
-// operands the six with h h, h m, m h, h l, m m, l h are kept; each is exact
-// in fp32, and since |m| <= 2^-8 |x| (1 + 2^-8) and |l| <= 2^-16 |x|, the
-// dropped m l, l m and l l sum to less than 2^-23 |a||b|, two units of fp32
-// rounding, so a product is fp32-accurate (the six-product scheme of Henry, Tang
-// and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype
-// for higher-precision computations", ARITH 2019).  The 16x16x32 bf16 MFMA
-// does 32 K-steps in half the cycles the fp32 one takes for 4, so the six
-// products cost 3/8 of the fp32 MFMA time.  Values must lie in bf16's range
-// (|x| < 3.39e38); terms below fp32's normal range lose their low bits.
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-
-constexpr int kSplitWaves = 8;                 // 512-thread workgroups, one per CU (LDS)
-constexpr int kSplitKC = 4;                    // c = 128: four chunks of 32 K-steps
-
-__device__ inline void split3(float x, __bf16 &h, __bf16 &m, __bf16 &l) {
-    h = (__bf16)x;
-    const float r = x - (float)h;                 // exact
-    m = (__bf16)r;
-    l = (__bf16)(r - (float)m);                   // exact
-}
-
-template <class V>
-struct Split3 { V h, m, l; };
-
-// acc += A B for split A and B with the six kept products, the small ones first.
-__device__ inline v4f mma_split32(const Split3<v8bf> &a, const Split3<v8bf> &b, v4f acc) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.m, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.l, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.m, acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.h, acc, 0, 0, 0);
-}
-__device__ inline v4s as_v4s(v4bf v) { return __builtin_bit_cast(v4s, v); }
-__device__ inline v4f mma_split16(const Split3<v4bf> &a, const Split3<v4bf> &b, v4f acc) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_v4s(a.l), as_v4s(b.h), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_v4s(a.m), as_v4s(b.m), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_v4s(a.h), as_v4s(b.l), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_v4s(a.m), as_v4s(b.h), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_v4s(a.h), as_v4s(b.m), acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_v4s(a.h), as_v4s(b.h), acc, 0, 0, 0);
-}
-
-// The A operands in LDS, split: for M-tile mt and 32-step chunk kc, the
-// three terms of lane l are 8 bf16 at [((mt KC + kc) 3 + term) 64 + l] x 16 B,
-// holding A[row 16 mt + l % 16][k = 32 kc + 8 (l / 16) + s], s = 0..7; a
-// 16-step tail (decode) follows at [(mt 3 + term) 64 + l] x 8 B with
-// k = 32 KC + 4 (l / 16) + s, s = 0..3.  The fp32 fragment of (row, k) is
-// gfrag[((mt KSx + k / 4) 64 + 16 (k % 4) + row % 16], zero beyond 4 KSx.
-template <int MTC, int KC, bool TAIL>
-__device__ inline void stage_split_fragments(__bf16 *sa, const float *gfrag, int KSx) {
-    constexpr int KT = 32 * KC + (TAIL ? 16 : 0);
-    auto coef = [&](int mt, int row, int k) {
-        return k < 4 * KSx ? gfrag[((size_t)mt * KSx + k / 4) * 64 + 16 * (k % 4) + row] : 0.0f;
-    };
-    for (int idx = threadIdx.x; idx < MTC * KT * 16; idx += 64 * kSplitWaves) {
-        const int mt = idx / (KT * 16), rem = idx % (KT * 16);
-        if (rem < 32 * KC * 16) {
-            const int s = rem & 7, lane = (rem >> 3) & 63, kc = rem >> 9;
-            const int row = lane & 15, k = 32 * kc + 8 * (lane >> 4) + s;
-            __bf16 *base = sa + (((size_t)(mt * KC + kc) * 3) * 64 + lane) * 8 + s;
-            split3(coef(mt, row, k), base[0], base[64 * 8], base[2 * 64 * 8]);
-        } else {
-            const int r2 = rem - 32 * KC * 16;
-            const int s = r2 & 3, lane = r2 >> 2;
-            const int row = lane & 15, k = 32 * KC + 4 * (lane >> 4) + s;
-            __bf16 *base = sa + (size_t)MTC * KC * 3 * 64 * 8 + ((size_t)(mt * 3) * 64 + lane) * 4 + s;
-            split3(coef(mt, row, k), base[0], base[64 * 4], base[2 * 64 * 4]);
-        }
-    }
-}
-
-template <int MTC, int KC>
-__device__ inline Split3<v8bf> lds_split32(const __bf16 *sa, int mt, int kc, uint32_t lane8) {
-    const __bf16 *b = sa + ((size_t)(mt * KC + kc) * 3) * 64 * 8 + lane8;
-    return {*reinterpret_cast<const v8bf *>(b), *reinterpret_cast<const v8bf *>(b + 64 * 8),
-            *reinterpret_cast<const v8bf *>(b + 2 * 64 * 8)};
-}
-template <int MTC, int KC>
-__device__ inline Split3<v4bf> lds_split16(const __bf16 *sa, int mt, uint32_t lane4) {
-    const __bf16 *b = sa + (size_t)MTC * KC * 3 * 64 * 8 + (size_t)(mt * 3) * 64 * 4 + lane4;
-    return {*reinterpret_cast<const v4bf *>(b), *reinterpret_cast<const v4bf *>(b + 64 * 4),
-            *reinterpret_cast<const v4bf *>(b + 2 * 64 * 4)};
-}
-
-// One half-block (32 positions) of B operands, split: lane (col, g) holds rows
-// 32 kc + 8 g + s (s = 0..7) and 32 KC + 4 g + s (tail, s = 0..3) at
-// positions 2 col and 2 col + 1 (component q).
-template <int KC, bool TAIL>
-struct SplitB {
-    Split3<v8bf> b[KC][2];
-    Split3<v4bf> t[2];
-};
-
-// Two values at once (one packed conversion per term); returns the three
-// terms as packed bf16 pairs.
-__device__ inline void split3_pair(v2f x, uint32_t &h, uint32_t &m, uint32_t &l) {
-    const v2bf xh = __builtin_convertvector(x, v2bf);
-    const v2f r = x - __builtin_convertvector(xh, v2f);        // exact
-    const v2bf xm = __builtin_convertvector(r, v2bf);
-    const v2bf xl = __builtin_convertvector(r - __builtin_convertvector(xm, v2f), v2bf);   // exact
-    h = __builtin_bit_cast(uint32_t, xh);
-    m = __builtin_bit_cast(uint32_t, xm);
-    l = __builtin_bit_cast(uint32_t, xl);
-}
-
-template <int KC, bool TAIL>
-__device__ inline void split_operands(SplitB<KC, TAIL> &S, const v2f (&x)[KC][8], const v2f (&xt)[4]) {
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            v4u h, m, l;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                uint32_t th, tm, tl;
-                split3_pair(v2f{x[kc][2 * w][q], x[kc][2 * w + 1][q]}, th, tm, tl);
-                h[w] = th;
-                m[w] = tm;
-                l[w] = tl;
-            }
-            S.b[kc][q] = {__builtin_bit_cast(v8bf, h), __builtin_bit_cast(v8bf, m), __builtin_bit_cast(v8bf, l)};
-        }
-    if constexpr (TAIL)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            v2u h, m, l;
-#pragma unroll
-            for (int w = 0; w < 2; ++w) {
-                uint32_t th, tm, tl;
-                split3_pair(v2f{xt[2 * w][q], xt[2 * w + 1][q]}, th, tm, tl);
-                h[w] = th;
-                m[w] = tm;
-                l[w] = tl;
-            }
-            S.t[q] = {__builtin_bit_cast(v4bf, h), __builtin_bit_cast(v4bf, m), __builtin_bit_cast(v4bf, l)};
-        }
-}
-
-// M-tiles mt and mt + 1 of one half-block: four independent MFMA chains.
-// The LDS offsets come through opaque(), so that the coefficient loads,
-// which do not change from one half-block to the next, are not hoisted out
-// of the block loop (all of them would not fit the registers).
-template <int MTC, int KC, bool TAIL>
-__device__ inline void mtile2_split(v4f (&acc)[2][2], const SplitB<KC, TAIL> &S, const __bf16 *sa, int mt, int lane) {
-    const uint32_t lane8 = opaque((uint32_t)lane * 8), lane4 = (uint32_t)lane * 4;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) acc[m][0] = acc[m][1] = v4f{0.f, 0.f, 0.f, 0.f};
-    // one chunk's coefficients in flight ahead of the MFMAs; the scheduling
-    // barriers keep the compiler from issuing more of them earlier
-    Split3<v8bf> a0 = lds_split32<MTC, KC>(sa, mt, 0, lane8), a1 = lds_split32<MTC, KC>(sa, mt + 1, 0, lane8);
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-        Split3<v8bf> n0 = a0, n1 = a1;
-        if (kc + 1 < KC) {
-            n0 = lds_split32<MTC, KC>(sa, mt, kc + 1, lane8);
-            n1 = lds_split32<MTC, KC>(sa, mt + 1, kc + 1, lane8);
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            acc[0][q] = mma_split32(a0, S.b[kc][q], acc[0][q]);
-            acc[1][q] = mma_split32(a1, S.b[kc][q], acc[1][q]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        a0 = n0;
-        a1 = n1;
-    }
-    if constexpr (TAIL) {
-        const uint32_t l4 = opaque(lane4);
-        const Split3<v4bf> a0 = lds_split16<MTC, KC>(sa, mt, l4), a1 = lds_split16<MTC, KC>(sa, mt + 1, l4);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            acc[0][q] = mma_split16(a0, S.t[q], acc[0][q]);
-            acc[1][q] = mma_split16(a1, S.t[q], acc[1][q]);
-        }
-    }
-}
-
-// Encode at c = 128 on split operands.  Each wave splits its half-block's 128
-// rows once into registers, issues the next half-block's loads into the fp32
-// registers that just became free, and then runs the 8 M-tiles.  The loop
-// header sits after the split, where on every path the last vector-memory
-// operations issued are those loads, so waiting for them never drains the
-// stores of the half-block before.
-template <int MTC>
-__global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_encode_split(EncParams a) {
-    static_assert(MTC % 2 == 0, "M-tiles run in pairs");
-    constexpr int KC = kSplitKC;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    __bf16 *sa = reinterpret_cast<__bf16 *>(smem_raw);
-    const int worker = blockIdx.x % a.N;           // workers interleaved across the grid
-    const int wg = blockIdx.x / a.N;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 15, g = lane >> 4;
-    stage_split_fragments<MTC, KC, false>(sa, a.frag + (size_t)worker * a.MT * a.KSe * 64, a.KSe);
-    __syncthreads();
-    const float *src = a.grads + (size_t)worker * a.ld_g;
-    float *dst = a.sb.work + (size_t)worker * a.sb.ld_work;
-    float *x1 = a.sb.pool + (size_t)worker * a.N * a.sb.pool_stride;
-    const size_t p = a.sb.p;
-    const size_t first = 2 * (a.blk0 + (size_t)wg * a.blk_per_wg),
-                 end = 2 * min(a.blk1, a.blk0 + ((size_t)wg + 1) * a.blk_per_wg);
-    size_t hb = first + wave;
-    if (hb >= end) return;
-    const uint32_t lane_in = opaque((uint32_t)(((size_t)(8 * g) * p + 2 * (size_t)col) * sizeof(float)));
-    v2f x[KC][8], xt[4];
-    // the row offsets are recomputed from a laundered stride in every
-    // half-block: held across the loop, 64 of them would not fit the scalar
-    // registers
-    auto load = [&](size_t h) {
-        const size_t ps = opaque_s(p);
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-            for (int s = 0; s < 8; ++s) x[kc][s] = load2_off(src + h * 32 + (size_t)(32 * kc + s) * ps, lane_in);
-    };
-    SplitB<KC, false> S;
-    load(hb);
-    split_operands<KC, false>(S, x, xt);
-    size_t next = hb + kSplitWaves;
-    if (next < end) load(next);
-    while (true) {
-        const size_t e0 = hb * 32;
-        const uint32_t lane_out = opaque((uint32_t)(((size_t)(g * 4) * p + 2 * (size_t)col) * sizeof(float)));
-#pragma unroll
-        for (int mt = 0; mt < MTC; mt += 2) {
-            v4f acc[2][2];
-            mtile2_split<MTC, KC, false>(acc, S, sa, mt, lane);
-            const size_t ps = opaque_s(p);
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const v2f v = {acc[m][0][r], acc[m][1][r]};
-                    nt_store2_off(dst + e0 + (size_t)((mt + m) * 16 + r) * ps, lane_out, v);
-                    if (mt + m == 0 && g * 4 + r == 0) nt_store2_off(x1 + e0, (uint32_t)(2 * col * sizeof(float)), v);
-                }
-        }
-        if (next >= end) break;
-        hb = next;
-        split_operands<KC, false>(S, x, xt);
-        __builtin_amdgcn_sched_barrier(0);
-        next = hb + kSplitWaves;
-        if (next < end) load(next);
-    }
-}
-
-// Decode at c = 128 (K = L + 1 <= 144 observations: four 32-step chunks and a
-// 16-step tail) on split operands, in the same order as k_encode_split.
-template <int MTC>
-__global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decode_split(DecParams a) {
-    static_assert(MTC % 2 == 0, "M-tiles run in pairs");
-    constexpr int KC = kSplitKC, KROWS = 32 * KC + 16;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    __bf16 *sa = reinterpret_cast<__bf16 *>(smem_raw);
-    const float **srow = reinterpret_cast<const float **>(smem_raw + (size_t)MTC * (KC * 3 * 64 * 8 + 3 * 64 * 4) * 2);
-    const int worker = blockIdx.x % a.N;           // workers interleaved across the grid
-    const int wg = blockIdx.x / a.N;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 15, g = lane >> 4;
-    stage_split_fragments<MTC, KC, true>(sa, a.frag + (size_t)worker * a.MT * a.KSd * 64, a.KSd);
-    // rows K..KROWS-1 repeat row K-1, whose coefficients there are zero
-    for (int t = threadIdx.x; t < KROWS; t += 64 * kSplitWaves)
-        srow[t] = a.sb.ptr(a.ycols[(size_t)worker * a.K + min(t, a.K - 1)]);
-    __syncthreads();
-    float *out = a.out + (size_t)worker * a.ld_o;
-    const size_t p = a.sb.p;
-    const size_t first = 2 * (a.blk0 + (size_t)wg * a.blk_per_wg),
-                 end = 2 * min(a.blk1, a.blk0 + ((size_t)wg + 1) * a.blk_per_wg);
-    size_t hb = first + wave;
-    if (hb >= end) return;
-    v2f x[KC][8], xt[4];
-    // the row pointers are read from LDS in every half-block (laundered
-    // index): held across the loop, 36 per lane would not fit the registers
-    auto load = [&](size_t h) {
-        const float *const *r8 = srow + opaque((uint32_t)(8 * g));
-        const float *const *r4 = srow + 32 * KC + opaque((uint32_t)(4 * g));
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) x[kc][s] = nt_load2_g(r8[32 * kc + s] + h * 32 + 2 * col);
-            __builtin_amdgcn_sched_barrier(0);        // a chunk's row pointers at a time
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) xt[s] = nt_load2_g(r4[s] + h * 32 + 2 * col);
-    };
-    SplitB<KC, true> S;
-    load(hb);
-    split_operands<KC, true>(S, x, xt);
-    size_t next = hb + kSplitWaves;
-    if (next < end) load(next);
-    while (true) {
-        const size_t e0 = hb * 32;
-        const uint32_t lane_out = opaque((uint32_t)(((size_t)(g * 4) * p + 2 * (size_t)col) * sizeof(float)));
-#pragma unroll
-        for (int mt = 0; mt < MTC; mt += 2) {
-            v4f acc[2][2];
-            mtile2_split<MTC, KC, true>(acc, S, sa, mt, lane);
-            const size_t ps = opaque_s(p);
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const v2f v = {acc[m][0][r], acc[m][1][r]};
-                    nt_store2_off(out + e0 + (size_t)((mt + m) * 16 + r) * ps, lane_out, v);
-                }
-        }
-        if (next >= end) break;
-        hb = next;
-        split_operands<KC, true>(S, x, xt);
-        __builtin_amdgcn_sched_barrier(0);
-        next = hb + kSplitWaves;
-        if (next < end) load(next);
-    }
-}
-
-// LDS of the split kernels: the split A operands, then (decode) the row table.
-constexpr size_t kSplitEncLds = (size_t)8 * kSplitKC * 3 * 64 * 8 * sizeof(__bf16);
-constexpr size_t kSplitDecLds = (size_t)8 * (kSplitKC * 3 * 64 * 8 + 3 * 64 * 4) * sizeof(__bf16) +
-                                (size_t)(32 * kSplitKC + 16) * sizeof(float *);
-
 // ---- K5: error norms ---------------------------------------------------------
 
 constexpr int kNormWorkers = 8;
@@ -1462,11 +1105,15 @@ int device_copy(const cerar_plan *plan, const DeviceCopy **out) {
         st = hip_fail(e, "hipDeviceGetAttribute");
     if (!st) st = upload(&dc.enc_frag, plan->enc_frag.data(), plan->enc_frag.size());
     if (!st) st = upload(&dc.dec_frag, plan->dec_frag.data(), plan->dec_frag.size());
+    if (!st && !plan->enc_split.empty()) st = upload(&dc.enc_split, plan->enc_split.data(), plan->enc_split.size());
+    if (!st && !plan->dec_split.empty()) st = upload(&dc.dec_split, plan->dec_split.data(), plan->dec_split.size());
     if (!st) st = upload(&dc.ycols, plan->tab.ycols.data(), plan->tab.ycols.size());
     if (!st) st = upload(&dc.rounds, plan->tab.rounds.data(), plan->tab.rounds.size());
     if (st) {
         (void)hipFree(dc.enc_frag);
         (void)hipFree(dc.dec_frag);
+        (void)hipFree(dc.enc_split);
+        (void)hipFree(dc.dec_split);
         (void)hipFree(dc.ycols);
         (void)hipFree(dc.rounds);
         plan->dev.erase(dev);
@@ -1537,16 +1184,6 @@ void wg_for(size_t nblk, int &wg_per_worker, size_t &blk_per_wg) {
     blk_per_wg = (nblk + w * kWaves - 1) / (w * kWaves) * kWaves;
 }
 
-// Workgroups of the c = 128 split kernels: one fits a CU (LDS), so each
-// worker gets about 1024 / N of them, about four per CU in all, and each
-// stages its split coefficients once for a long run of blocks.
-void wg_for_split(size_t nblk, int N, int &wg_per_worker, size_t &blk_per_wg) {
-    size_t w = std::max<size_t>(1, (1024 + (size_t)N - 1) / (size_t)N);
-    w = std::min(w, std::max<size_t>(1, (nblk + kWaves - 1) / kWaves));
-    blk_per_wg = (nblk + w * kWaves - 1) / (w * kWaves) * kWaves;
-    wg_per_worker = (int)((nblk + blk_per_wg - 1) / blk_per_wg);
-}
-
 // Launch flavours: interior blocks (FAST), masked 16-byte layout, scalar layout.
 enum class Path { kFast, kMaskedVec, kScalar };
 
@@ -1571,10 +1208,10 @@ void go_encode_dbuf(const P &a, dim3 g, size_t l, hipStream_t s) {
     if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_encode_dbuf_batch<KS, MTC>), g, dim3(kThreads), l, s, a);
     else hipLaunchKernelGGL((k_encode_dbuf<KS, MTC>), g, dim3(kThreads), l, s, a);
 }
-template <int KS, bool VEC, bool AREG, bool FAST, class P>
-void go_encode(const P &a, dim3 g, size_t l, hipStream_t s) {
-    if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_encode_batch<KS, VEC, AREG, FAST>), g, dim3(kThreads), l, s, a);
-    else hipLaunchKernelGGL((k_encode<KS, VEC, AREG, FAST>), g, dim3(kThreads), l, s, a);
+template <int KS, bool VEC, class P>
+void go_encode(const P &a, dim3 g, hipStream_t s) {
+    if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_encode_batch<KS, VEC>), g, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_encode<KS, VEC>), g, dim3(kThreads), 0, s, a);
 }
 template <int KS, int MTMAX, int NB, class P>
 void go_decode_pipe(const P &a, dim3 g, size_t l, hipStream_t s) {
@@ -1592,10 +1229,10 @@ void go_decode(const P &a, dim3 g, size_t l, hipStream_t s) {
     else hipLaunchKernelGGL((k_decode<KS, VEC, AREG, FAST>), g, dim3(kThreads), l, s, a);
 }
 
-template <int KS, bool AREG, class P>
-void launch_encode_ks(const P &a, Path path, size_t lds, hipStream_t s, dim3 grid) {
+template <int KS, class P>
+void launch_encode_ks(const P &a, Path path, hipStream_t s, dim3 grid) {
     const EncParams &sh = shared_of(a);
-    if constexpr (AREG && KS >= 4) {
+    if constexpr (KS >= 4) {
         if (path == Path::kFast) {
             if constexpr (KS == 16) {
                 if (sh.MT == 4 && sh.mt0 == 0 && sh.mt1 == 4) {   // c = 64: double-buffered
@@ -1617,14 +1254,9 @@ void launch_encode_ks(const P &a, Path path, size_t lds, hipStream_t s, dim3 gri
             return;
         }
     }
-    if constexpr (!AREG) {
-        if (path == Path::kFast) {
-            go_encode<KS, true, AREG, true>(a, grid, lds, s);
-            return;
-        }
-    }
-    if (path == Path::kMaskedVec) go_encode<KS, true, AREG, false>(a, grid, lds, s);
-    else go_encode<KS, false, AREG, false>(a, grid, lds, s);
+    // (the interior blocks of a plan have c % 16 == 0, so KS >= 4)
+    if (path == Path::kMaskedVec) go_encode<KS, true>(a, grid, s);
+    else go_encode<KS, false>(a, grid, s);
 }
 
 template <int KS, class P>
@@ -1708,10 +1340,10 @@ int launch_split(Params a, const BlockSplit &bs, size_t lds, hipStream_t s, int 
     return CERAR_OK;
 }
 
-template <int KS, bool AREG>
-int encode_ks(const EncParams &a, const BlockSplit &bs, size_t lds, hipStream_t s, int N) {
-    return launch_split(a, bs, lds, s, N, [](const EncParams &x, Path path, size_t l, hipStream_t st, dim3 g) {
-        launch_encode_ks<KS, AREG>(x, path, l, st, g);
+template <int KS>
+int encode_ks(const EncParams &a, const BlockSplit &bs, hipStream_t s, int N) {
+    return launch_split(a, bs, 0, s, N, [](const EncParams &x, Path path, size_t, hipStream_t st, dim3 g) {
+        launch_encode_ks<KS>(x, path, st, g);
     });
 }
 
@@ -1751,8 +1383,59 @@ void with_decode_ks(int ks, F f) {
 
 constexpr size_t kDecodeRowsBytes = (size_t)4 * kMaxDecodeKS * sizeof(float *) + 16;
 
+// The fields of a launch that its instances share.
+PassParams pass_params(const cerar_plan *plan, const DeviceCopy *dc, size_t ld_grads, size_t ld_work, size_t ld_out) {
+    PassParams a;
+    a.ld_g = ld_grads;
+    a.ld_o = ld_out;
+    a.ld_w = ld_work;
+    a.efrag = dc->enc_frag;
+    a.dfrag = dc->dec_frag;
+    a.N = plan->N;
+    a.c = plan->c;
+    a.KSe = plan->KSe;
+    a.KSd = plan->KSd;
+    a.esplit = dc->enc_split;
+    a.dsplit = dc->dec_split;
+    a.run = 0;
+    a.n = 0;
+    a.nblk = 0;
+    a.ragged = ld_grads % 32 != 0 || ld_out % 32 != 0;
+    return a;
+}
+
+void add_instance(PassParams &a, size_t P, const PassInst &in) {
+    a.in[a.n] = in;
+    a.in[a.n++].blk0 = a.nblk;
+    a.nblk += (unsigned)((in.p + P - 1) / P);
+    if (((uintptr_t)in.grads | (uintptr_t)in.out) % 128) a.ragged = 1;
+}
+
+// Whether the encode (decode) of the step calls runs on split operands.  Plans
+// of the one-pass kernel keep the fp32 contraction, so that the step calls give
+// its bits.
+bool split_encode(const cerar_plan *plan) { return plan->KC > 0 && !pass_positions(plan->N, plan->c); }
+bool split_decode(const cerar_plan *plan) { return split_encode(plan) && !plan->dec_split.empty(); }
+
+// One launch of the split encode or decode for up to kPassInst instances.
+template <class Launch>
+int split_launch(const cerar_plan *plan, const DeviceCopy *dc, PassParams a, const PassInst *in, int n, Launch launch,
+                 hipStream_t s) {
+    size_t half_blocks = 0;
+    for (int q = 0; q < n; ++q) half_blocks += in[q].p / 32;
+    a.run = split_run(plan->N, plan->KC, dc->cus, half_blocks);
+    for (int q = 0; q < n; ++q) add_instance(a, 32 * a.run, in[q]);
+    launch(a, plan->KC, s);
+    HIP_TRY(hipGetLastError(), "launch split contraction");
+    return CERAR_OK;
+}
+
 int enqueue_encode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g, size_t d,
                    const float *grads, size_t ld_grads, float *work, size_t ld_work, void *ws, hipStream_t s) {
+    if (split_encode(plan)) {
+        const PassInst in{grads, nullptr, work, (float *)ws, d, g.p, g.pool_stride, 0};
+        return split_launch(plan, dc, pass_params(plan, dc, ld_grads, ld_work, ld_work), &in, 1, launch_encode_split, s);
+    }
     EncParams a;
     a.grads = grads;
     a.ld_g = ld_grads;
@@ -1768,35 +1451,8 @@ int enqueue_encode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry 
     const int N = plan->N, ks = plan->KSe;
     a.mt0 = 0;
     a.mt1 = plan->MT;
-    if (plan->MT <= kMaxRegTiles) {                  // c <= 64: coefficients in registers
-        with_encode_ks(ks, [&](auto K) { encode_ks<decltype(K)::value, true>(a, bs, 0, s, N); });
-    } else {
-        // All M-tiles in one launch (c <= 128 fits the LDS budget), which an
-        // in-place encode needs: every input row is read before any is written.
-        if (mtiles_per_launch(plan->MT, ks, 0) < plan->MT)
-            return fail(CERAR_E_INVAL, "c=%d exceeds the encode's LDS budget", plan->c);
-        const size_t lds = (size_t)plan->MT * ((ks + 3) / 4) * 256 * sizeof(float);
-        if (plan->c == 128 && bs.interior > 0) {
-            // c = 128: interior blocks on the wide kernel, the tail on the generic one
-            EncParams w = a;
-            w.blk0 = 0;
-            w.blk1 = bs.interior;
-            wg_for_split(bs.interior, N, w.wg_per_worker, w.blk_per_wg);
-            hipLaunchKernelGGL((k_encode_split<8>), dim3((unsigned)(N * w.wg_per_worker)), dim3(64 * kSplitWaves),
-                               kSplitEncLds, s, w);
-            if (bs.total > bs.interior) {
-                EncParams t = a;
-                t.blk0 = bs.interior;
-                t.blk1 = bs.total;
-                wg_for(bs.total - bs.interior, t.wg_per_worker, t.blk_per_wg);
-                launch_encode_ks<32, false>(t, bs.tail, lds, s, dim3((unsigned)(N * t.wg_per_worker)));
-            }
-        } else if (ks <= 24) {
-            encode_ks<24, false>(a, bs, lds, s, N);
-        } else {
-            encode_ks<32, false>(a, bs, lds, s, N);
-        }
-    }
+    // c <= 64 here: coefficients in registers
+    with_encode_ks(ks, [&](auto K) { encode_ks<decltype(K)::value>(a, bs, s, N); });
     HIP_TRY(hipGetLastError(), "launch encode");
     return CERAR_OK;
 }
@@ -1852,6 +1508,10 @@ int enqueue_round(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &
 
 int enqueue_decode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g, size_t d,
                    const float *work, size_t ld_work, const void *ws, float *out, size_t ld_out, hipStream_t s) {
+    if (split_decode(plan)) {
+        const PassInst in{nullptr, out, const_cast<float *>(work), (float *)const_cast<void *>(ws), d, g.p, g.pool_stride, 0};
+        return split_launch(plan, dc, pass_params(plan, dc, ld_out, ld_work, ld_out), &in, 1, launch_decode_split, s);
+    }
     DecParams a;
     a.sb = slot_base(plan, g, const_cast<float *>(work), ld_work, const_cast<void *>(ws));
     a.ycols = dc->ycols;
@@ -1877,12 +1537,10 @@ int enqueue_decode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry 
         w.mt1 = 8;
         w.blk0 = 0;
         w.blk1 = bs.interior;
-        if (ks <= 36) wg_for_split(bs.interior, N, w.wg_per_worker, w.blk_per_wg);
-        else wg_for(bs.interior, w.wg_per_worker, w.blk_per_wg);
+        wg_for(bs.interior, w.wg_per_worker, w.blk_per_wg);
         const dim3 grid((unsigned)(N * w.wg_per_worker));
         auto lds_for = [](int K4) { return (size_t)8 * (K4 / 4) * 256 * sizeof(float) + (size_t)4 * K4 * sizeof(float *); };
-        if (ks <= 36) hipLaunchKernelGGL((k_decode_split<8>), grid, dim3(64 * kSplitWaves), kSplitDecLds, s, w);
-        else if (ks <= 40) hipLaunchKernelGGL((k_decode_wide<40, 8>), grid, dim3(kThreads), lds_for(40), s, w);
+        if (ks <= 40) hipLaunchKernelGGL((k_decode_wide<40, 8>), grid, dim3(kThreads), lds_for(40), s, w);
         else if (ks <= 44) hipLaunchKernelGGL((k_decode_wide<44, 8>), grid, dim3(kThreads), lds_for(44), s, w);
         else hipLaunchKernelGGL((k_decode_wide<48, 8>), grid, dim3(kThreads), lds_for(48), s, w);
         HIP_TRY(hipGetLastError(), "launch decode");
@@ -1900,29 +1558,18 @@ int enqueue_decode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry 
     return CERAR_OK;
 }
 
-// The fields of a one-pass launch that its instances share.
-PassParams pass_params(const cerar_plan *plan, const DeviceCopy *dc, size_t ld_grads, size_t ld_work, size_t ld_out) {
-    PassParams a;
-    a.ld_g = ld_grads;
-    a.ld_o = ld_out;
-    a.ld_w = ld_work;
-    a.efrag = dc->enc_frag;
-    a.dfrag = dc->dec_frag;
-    a.N = plan->N;
-    a.c = plan->c;
-    a.KSe = plan->KSe;
-    a.KSd = plan->KSd;
-    a.n = 0;
-    a.nblk = 0;
-    a.ragged = ld_grads % 32 != 0 || ld_out % 32 != 0;
-    return a;
-}
-
-void add_instance(PassParams &a, int P, const PassInst &in) {
-    a.in[a.n] = in;
-    a.in[a.n++].blk0 = a.nblk;
-    a.nblk += (unsigned)((in.p + P - 1) / P);
-    if (((uintptr_t)in.grads | (uintptr_t)in.out) % 128) a.ragged = 1;
+// All rounds of up to kPassInst instances in one launch.
+int enqueue_rounds(const cerar_plan *plan, const DeviceCopy *dc, const PassInst *in, int n, size_t ld_work,
+                   hipStream_t s) {
+    PassParams a = pass_params(plan, dc, ld_work, ld_work, ld_work);
+    for (int q = 0; q < n; ++q) {
+        PassInst r = in[q];
+        r.grads = r.out = r.work;
+        add_instance(a, rounds_positions(plan->N), r);
+    }
+    launch_rounds_pass(a, dc->cus, s);
+    HIP_TRY(hipGetLastError(), "launch rounds pass");
+    return CERAR_OK;
 }
 
 // Encode, rounds and decode of one instance: one pass where the one-pass
@@ -1937,12 +1584,9 @@ int enqueue_ring(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g
         return CERAR_OK;
     }
     int st = enqueue_encode(plan, dc, g, d, grads, ld_grads, work, ld_work, ws, s);
-    if (const int P = rounds_positions(plan->N)) {
-        if (st) return st;
-        PassParams a = pass_params(plan, dc, ld_work, ld_work, ld_work);
-        add_instance(a, P, PassInst{work, work, work, (float *)ws, d, g.p, g.pool_stride, 0});
-        launch_rounds_pass(a, dc->cus, s);
-        HIP_TRY(hipGetLastError(), "launch rounds pass");
+    if (rounds_positions(plan->N)) {
+        const PassInst in{grads, out, work, (float *)ws, d, g.p, g.pool_stride, 0};
+        if (!st) st = enqueue_rounds(plan, dc, &in, 1, ld_work, s);
     } else {
         for (int k = 1; k <= plan->L && !st; ++k) st = enqueue_round(plan, dc, g, k, work, ld_work, ws, s);
     }
@@ -1989,6 +1633,8 @@ void release_device(cerar_plan *plan) {
         if (have) (void)hipSetDevice(kv.first);
         (void)hipFree(kv.second.enc_frag);
         (void)hipFree(kv.second.dec_frag);
+        (void)hipFree(kv.second.enc_split);
+        (void)hipFree(kv.second.dec_split);
         (void)hipFree(kv.second.ycols);
         (void)hipFree(kv.second.rounds);
     }
@@ -2398,7 +2044,7 @@ int enqueue_encode_buckets(const cerar_plan *plan, const DeviceCopy *dc, const s
     int st = CERAR_OK;
     with_encode_ks(plan->KSe, [&](auto K) {
         st = launch_bucket_batches(plan, bk, b, set, [&](const EncBatch &x, Path path, dim3 grid) {
-            launch_encode_ks<decltype(K)::value, true>(x, path, 0, s, grid);
+            launch_encode_ks<decltype(K)::value>(x, path, s, grid);
         });
     });
     return st;
@@ -2522,29 +2168,32 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
     // With c <= 64 and 16-byte rows everywhere, the encode and the decode are
     // batched too (interior blocks of up to kMaxInst buckets per launch, then
     // their tails); otherwise each bucket gets its own launches.
-    bool batched = all_vec && plan->MT <= kMaxRegTiles && ld_grads % 4 == 0 && ld_out % 4 == 0 &&
+    bool batched = all_vec && plan->KC == 0 && ld_grads % 4 == 0 && ld_out % 4 == 0 &&
                    mtiles_per_launch(plan->MT, plan->KSd, kDecodeRowsBytes) == plan->MT;
     std::vector<BucketRef> bk(nbuckets);
+    std::vector<PassInst> inst(nbuckets);
     for (int b = 0; b < nbuckets; ++b) {
         bk[b] = BucketRef{grads + bucket_off[b], out + bucket_off[b], work + lay[b].work_off,
                           (char *)ws + lay[b].ws_off, bucket_len[b], lay[b].p, lay[b].stride};
         batched = batched && aligned16(bk[b].grads) && aligned16(bk[b].out);
+        inst[b] = PassInst{bk[b].grads, bk[b].out, bk[b].work, (float *)bk[b].ws, bk[b].d, bk[b].p, bk[b].pool_stride, 0};
     }
-    if (batched) st = enqueue_encode_buckets(plan, dc, bk, ld_grads, ld_work, s);
-    for (int b = 0; b < nbuckets && !st && !batched; ++b)
-        st = enqueue_encode(plan, dc, geo[b], bucket_len[b], grads + bucket_off[b], ld_grads, work + lay[b].work_off,
-                            ld_work, (char *)ws + lay[b].ws_off, s);
+    // f(first, count) for every launch's share of the buckets
+    auto each_launch = [&](auto f) {
+        for (int b0 = 0; b0 < nbuckets && !st; b0 += kPassInst) st = f(&inst[b0], std::min(nbuckets - b0, kPassInst));
+    };
+    if (split_encode(plan))
+        each_launch([&](const PassInst *in, int n) {
+            return split_launch(plan, dc, pass_params(plan, dc, ld_grads, ld_work, ld_out), in, n, launch_encode_split, s);
+        });
+    else if (batched) st = enqueue_encode_buckets(plan, dc, bk, ld_grads, ld_work, s);
+    else
+        for (int b = 0; b < nbuckets && !st; ++b)
+            st = enqueue_encode(plan, dc, geo[b], bucket_len[b], grads + bucket_off[b], ld_grads,
+                                work + lay[b].work_off, ld_work, (char *)ws + lay[b].ws_off, s);
     const int P = rounds_positions(plan->N);
-    for (int b0 = 0; b0 < nbuckets && P && !st; b0 += kPassInst) {
-        PassParams a = pass_params(plan, dc, ld_work, ld_work, ld_work);
-        for (int b = b0; b < std::min(nbuckets, b0 + kPassInst); ++b) {
-            float *wb = work + lay[b].work_off;
-            add_instance(a, P, PassInst{wb, wb, wb, (float *)((char *)ws + lay[b].ws_off), bucket_len[b], lay[b].p,
-                                        lay[b].stride, 0});
-        }
-        launch_rounds_pass(a, dc->cus, s);
-        HIP_TRY(hipGetLastError(), "launch rounds pass");
-    }
+    if (P)
+        each_launch([&](const PassInst *in, int n) { return enqueue_rounds(plan, dc, in, n, ld_work, s); });
     for (int k = 1; k < plan->L && !st && !P; ++k) {
         for (int b0 = 0; b0 < nbuckets;) {
             BatchRoundParams a;
@@ -2585,10 +2234,16 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
             HIP_TRY(hipGetLastError(), "launch bucket round");
         }
     }
-    if (batched && !st) st = enqueue_decode_buckets(plan, dc, bk, ld_work, ld_out, s);
-    for (int b = 0; b < nbuckets && !st && !batched; ++b)
-        st = enqueue_decode(plan, dc, geo[b], bucket_len[b], work + lay[b].work_off, ld_work,
-                            (char *)ws + lay[b].ws_off, out + bucket_off[b], ld_out, s);
+    if (st) return st;
+    if (split_decode(plan))
+        each_launch([&](const PassInst *in, int n) {
+            return split_launch(plan, dc, pass_params(plan, dc, ld_grads, ld_work, ld_out), in, n, launch_decode_split, s);
+        });
+    else if (batched) st = enqueue_decode_buckets(plan, dc, bk, ld_work, ld_out, s);
+    else
+        for (int b = 0; b < nbuckets && !st; ++b)
+            st = enqueue_decode(plan, dc, geo[b], bucket_len[b], work + lay[b].work_off, ld_work,
+                                (char *)ws + lay[b].ws_off, out + bucket_off[b], ld_out, s);
     return st;
 }
 

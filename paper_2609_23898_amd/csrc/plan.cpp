@@ -489,6 +489,47 @@ std::string build_ring_tables(int N, int c, RingTables &t) {
     return "";
 }
 
+namespace {
+
+// x rounded to bf16 (round to nearest even), as its 16 bits; x finite.
+uint16_t bf16_bits(float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, sizeof u);
+    return (uint16_t)((u + 0x7fff + (u >> 16 & 1)) >> 16);
+}
+float bf16_value(uint16_t b) {
+    const uint32_t u = (uint32_t)b << 16;
+    float x;
+    std::memcpy(&x, &u, sizeof x);
+    return x;
+}
+
+// The A operands of the bf16 MFMAs, each fp32 coefficient as the sum of three
+// bf16 terms: for chunk kc, term t and lane l, A[row = l % 16][k = 32 kc +
+// 8 (l / 16) + s], s = 0..7, and of the tail A[row][k = 32 KC + 4 (l / 16) + s],
+// s = 0..3.  coef(row, k) gives the fp32 coefficient of the tile.
+template <class Coef>
+void split_tile(uint16_t *tile, int KC, bool tail, Coef coef) {
+    auto put = [&](uint16_t *at, size_t term, float x) {
+        const uint16_t h = bf16_bits(x);
+        const float r = x - bf16_value(h);
+        const uint16_t m = bf16_bits(r);
+        at[0] = h;
+        at[term] = m;
+        at[2 * term] = bf16_bits(r - bf16_value(m));
+    };
+    for (int kc = 0; kc < KC; ++kc)
+        for (int lane = 0; lane < 64; ++lane)
+            for (int s = 0; s < 8; ++s)
+                put(tile + ((size_t)kc * 3 * 64 + lane) * 8 + s, 64 * 8, coef(lane % 16, 32 * kc + 8 * (lane / 16) + s));
+    if (tail)
+        for (int lane = 0; lane < 64; ++lane)
+            for (int s = 0; s < 4; ++s)
+                put(tile + (size_t)KC * 3 * 64 * 8 + lane * 4 + s, 64 * 4, coef(lane % 16, 32 * KC + 4 * (lane / 16) + s));
+}
+
+}  // namespace
+
 void build_fragments(cerar_plan *p) {
     const int N = p->N, c = p->c, L = p->L;
     p->MT = ceil_div(c, kTileM);
@@ -517,6 +558,22 @@ void build_fragments(cerar_plan *p) {
                     if (m < c && k <= L) v = (float)p->R[((size_t)i * (L + 1) + k) * c + m];
                     p->dec_frag[(((size_t)i * p->MT + mt) * p->KSd + ks) * kLanes + lane] = v;
                 }
+    const int KC = p->KC = split_chunks(c);
+    if (!KC) return;
+    const size_t te = split_tile_encode(KC), td = split_tile_decode(KC);
+    p->enc_split.assign((size_t)N * 2 * KC * te, 0);
+    if (split_decode_fits(N, c)) p->dec_split.assign((size_t)N * 2 * KC * td, 0);
+    for (int i = 0; i < N; ++i)
+        for (int mt = 0; mt < 2 * KC; ++mt) {
+            split_tile(&p->enc_split[((size_t)i * 2 * KC + mt) * te], KC, false, [&](int row, int k) {
+                const int j = 16 * mt + row;
+                return j < c && k < c ? (float)p->U[((size_t)i * c + k) * c + j] : 0.0f;
+            });
+            if (!p->dec_split.empty()) split_tile(&p->dec_split[((size_t)i * 2 * KC + mt) * td], KC, true, [&](int row, int k) {
+                const int m = 16 * mt + row;
+                return m < c && k <= L ? (float)p->R[((size_t)i * (L + 1) + k) * c + m] : 0.0f;
+            });
+        }
 }
 
 }  // namespace cerar

@@ -15,54 +15,12 @@
 #include "cerar_internal.hpp"
 #include "device_util.hpp"
 #include "ring_pass.hpp"
+#include "rows.hpp"
 
 namespace cerar {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
-
-// V floats of one row; rows may start at any float, so the accesses claim
-// four-byte alignment only.
-template <int V>
-struct Vec {
-    typedef float T __attribute__((ext_vector_type(V)));
-    typedef float U __attribute__((ext_vector_type(V), aligned(4)));
-};
-template <int V>
-__device__ inline typename Vec<V>::T gload(const float *ubase, uint32_t lane_bytes) {
-    typedef __attribute__((address_space(1))) const typename Vec<V>::U GU;
-    typedef __attribute__((address_space(1))) const char GC;
-    return *(GU *)((GC *)ubase + lane_bytes);
-}
-template <int V>
-__device__ inline void gstore(float *ubase, uint32_t lane_bytes, typename Vec<V>::T v) {
-    typedef __attribute__((address_space(1))) typename Vec<V>::U GU;
-    typedef __attribute__((address_space(1))) char GC;
-    __builtin_nontemporal_store((typename Vec<V>::U)v, (GU *)((GC *)ubase + lane_bytes));
-}
-template <int V>
-__device__ inline void gstore_cached(float *ubase, uint32_t lane_bytes, typename Vec<V>::T v) {
-    typedef __attribute__((address_space(1))) typename Vec<V>::U GU;
-    typedef __attribute__((address_space(1))) char GC;
-    *(GU *)((GC *)ubase + lane_bytes) = v;
-}
-__device__ inline float gload1(const float *ptr) { return *(__attribute__((address_space(1))) const float *)ptr; }
-__device__ inline void gstore1(float *ptr, float v) { *(__attribute__((address_space(1))) float *)ptr = v; }
-
-// ptr + floats for a wave-uniform ptr, kept from being rewritten as base +
-// row x p: one live scalar pointer that steps from row to row instead of one
-// per row.
-template <class T>
-__device__ inline T *step(T *ptr, size_t floats) {
-    const size_t v = reinterpret_cast<size_t>(ptr + floats);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<T *>(opaque_s((size_t)hi << 32 | lo));
-}
-
-// Rows up to this length have the byte offsets of 13 rows in 32 bits (a
-// scalar base and a 32-bit lane offset); longer ones take the masked
-// accesses, which address each float in 64 bits.
-constexpr size_t kNarrow = (size_t)1 << 26;
 
 // The coefficients of a 16-row tile as MFMA A operands, one float per lane
 // and K-step; K-steps past the plan's repeat its last one (the B operands
@@ -199,7 +157,9 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
     auto load = [&](const PassInst &I, size_t e0) {
         const size_t p = opaque_s(I.p), d = I.d;
         const float *src = I.grads + (size_t)w * a.ld_g;
-        if (p < kNarrow && e0 + P <= p && (size_t)(c - 1) * p + e0 + P <= d) {   // every row of the block lies inside the gradient
+        // every row of the block lies inside the gradient
+        const bool inside = e0 + P <= p && (size_t)(c - 1) * p + e0 + P <= d;
+        if (inside && p < kNarrow) {
             const uint32_t lane_in = opaque((uint32_t)(((size_t)krow * p + V * (size_t)col) * sizeof(float)));
             const float *row = src + e0;
 #pragma unroll
@@ -211,6 +171,15 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
                     if (4 * ks + (int)opaque((uint32_t)krow) < c) b[ks] = gload<V>(row, lane_in);
                 }
                 row = step(row, 4 * p);
+            }
+        } else if (inside) {
+            const int lrow = (int)opaque((uint32_t)krow);
+#pragma unroll
+            for (int ks = 0; ks < KSE; ++ks) {
+                const int l = 4 * ks + lrow;
+                b[ks] = (VT)0.f;
+                if (EXC || l < c) b[ks] = gload<V>(src + (size_t)l * p + e0 + V * col, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             const int lrow = (int)opaque((uint32_t)krow), lcol = V * (int)opaque((uint32_t)col);
@@ -277,7 +246,7 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
         const PassInst &I = a.in[q];
         const size_t p = I.p, d = I.d, ps = I.pool_stride;
         const size_t e0 = (size_t)(g - I.blk0) * P;
-        const bool state = I.work != nullptr, full = p < kNarrow && e0 + P <= p;
+        const bool state = I.work != nullptr, full = e0 + P <= p, narrow = p < kNarrow;
         g += gridDim.x;
         const bool more = g < a.nblk;
         if (more) {                                       // in flight during the rounds and the decode
@@ -313,7 +282,7 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
         for (int ks = 0; ks < KSD; ++ks) {
             const int Nq = (int)opaque_s(N), Kq = (int)opaque_s(K);   // compared here, not held as masks
             VT y = (VT)0.f;                               // rows past L meet zero coefficients
-            if (4 * ks >= Nq && 4 * ks + 3 < Kq - 1) {      // most K-steps lie in the columns N..K-2 as a whole
+            if (narrow && 4 * ks >= Nq && 4 * ks + 3 < Kq - 1) {      // most K-steps lie in the columns N..K-2 as a whole
                 y = *reinterpret_cast<const VT *>(yin + 4 * ks * P);
                 if (state && full) gstore<V>(row4, lane_row, y);
             } else if (4 * ks < Kq) {
@@ -341,7 +310,8 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
             }
         }
         float *out = I.out + (size_t)w * a.ld_o;
-        if (full && (size_t)(c - 1) * p + e0 + P <= d) {
+        const bool inside = full && (size_t)(c - 1) * p + e0 + P <= d;
+        if (inside && narrow) {
             const uint32_t lane_out = opaque((uint32_t)(((size_t)(4 * krow) * p + V * (size_t)col) * sizeof(float)));
             float *row = out + e0;
             const bool ragged = a.ragged;
@@ -360,6 +330,20 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
                     row = step(row, r < 3 ? p : 13 * p);
                 }
             }
+        } else if (inside) {
+            const size_t pq = opaque_s(p);
+            const int lrow = 4 * (int)opaque((uint32_t)krow);
+#pragma unroll
+            for (int mt = 0; mt < MTC; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = 16 * mt + lrow + r;
+                    VT v;
+#pragma unroll
+                    for (int t = 0; t < V; ++t) v[t] = dacc[mt][t][r];
+                    if (EXC || m < c) gstore<V>(out + (size_t)m * pq + e0 + V * col, 0, v);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
         } else {
             const size_t pq = opaque_s(p);
             const int lrow = 4 * (int)opaque((uint32_t)krow), lcol = V * (int)opaque((uint32_t)col);

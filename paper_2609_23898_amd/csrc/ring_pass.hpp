@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <cstdint>
 
 namespace cerar {
 
@@ -12,7 +13,7 @@ struct PassInst {
     const float *grads;
     float *out, *work, *pool;      // work == nullptr: only `out` is written
     size_t d, p, pool_stride;
-    unsigned blk0;                 // first of its blocks in the call's numbering
+    unsigned blk0;                 // first of its blocks (or runs) in the call's numbering
 };
 
 constexpr int kPassInst = 32;
@@ -20,8 +21,10 @@ constexpr int kPassInst = 32;
 struct PassParams {
     size_t ld_g, ld_o, ld_w;
     const float *efrag, *dfrag;    // N x MT x KSe x 64 and N x MT x KSd x 64
+    const uint16_t *esplit, *dsplit;   // the split operands, N x 2 KC tiles
     int N, c, KSe, KSd, n;
-    unsigned nblk;                 // blocks of all instances
+    unsigned nblk;                 // blocks (split kernels: runs of blocks) of all instances
+    unsigned run;                  // split kernels: half-blocks per workgroup
     int ragged;                    // some row of grads or out does not start on a 128-byte line
     PassInst in[kPassInst];
 };
@@ -44,5 +47,12 @@ void launch_ring_pass(const PassParams &a, int cus, hipStream_t s);
 // (grads and out unused); 0 where N is too large for it.
 int rounds_positions(int N);
 void launch_rounds_pass(const PassParams &a, int cus, hipStream_t s);
+
+// Encode and decode on split operands (plans with KC = split_chunks > 0): the
+// half-blocks (32 positions) per workgroup for this many in all, and the
+// launches, of N nblk workgroups.
+unsigned split_run(int N, int KC, int cus, size_t half_blocks);
+void launch_encode_split(const PassParams &a, int KC, hipStream_t s);
+void launch_decode_split(const PassParams &a, int KC, hipStream_t s);
 
 }  // namespace cerar
