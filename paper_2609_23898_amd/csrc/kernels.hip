@@ -969,8 +969,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 
 // ---- K5: error norms ---------------------------------------------------------
 
-constexpr int kNormWorkers = 8;
-
 __global__ void k_fill_zero(double *x, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) x[i] = 0.0;
@@ -982,39 +980,74 @@ __device__ inline double wave_sum(double v) {
     return v;
 }
 
+// Four consecutive entries of a row that starts at any float.
+__device__ inline v4f row4(const float *row, size_t e, size_t d) {
+    typedef float U __attribute__((ext_vector_type(4), aligned(4)));
+    typedef __attribute__((address_space(1))) const U GU;
+    if (e + 3 < d) return __builtin_nontemporal_load((GU *)(row + e));
+    v4f v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (e + t < d) v[t] = load1_g(row + e + t);
+    return v;
+}
+
+// Squared errors of W workers per grid row (blockIdx.y) against S = sum_w
+// grads_w, in fp64.  Bound by memory on 2N rows: a thread takes four entries
+// of every row, and the loads of eight rows are under way at a time (one
+// entry per thread and row after row moved 3.8 TB/s at N = 8, d = 124M).
+// Entries past d load as zero in every row and add nothing.
+template <int W>
 __global__ __launch_bounds__(kThreads) void k_norms(int N, size_t d, const float *__restrict__ grads,
                                                    size_t ld_g, const float *__restrict__ out, size_t ld_o,
                                                    double *norms) {
-    __shared__ double red[kWaves][kNormWorkers + 1];
-    const int w0 = blockIdx.y * kNormWorkers;
-    double acc[kNormWorkers + 1];
+    __shared__ double red[kWaves][W + 1];
+    const int w0 = blockIdx.y * W;
+    double acc[W + 1];
 #pragma unroll
-    for (int q = 0; q <= kNormWorkers; ++q) acc[q] = 0.0;
-    for (size_t e = (size_t)blockIdx.x * kThreads + threadIdx.x; e < d; e += (size_t)gridDim.x * kThreads) {
-        double S = 0.0;
-        for (int w = 0; w < N; ++w) S += (double)grads[(size_t)w * ld_g + e];
-        acc[kNormWorkers] += S * S;
+    for (int q = 0; q <= W; ++q) acc[q] = 0.0;
+    for (size_t e = 4 * ((size_t)blockIdx.x * kThreads + threadIdx.x); e < d; e += (size_t)gridDim.x * kThreads * 4) {
+        double S[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int w = 0; w < N; w += 8) {
+            v4f g[8];
 #pragma unroll
-        for (int q = 0; q < kNormWorkers; ++q) {
-            const int w = w0 + q;
-            if (w < N) {
-                const double diff = (double)out[(size_t)w * ld_o + e] - S;
-                acc[q] += diff * diff;
-            }
+            for (int q = 0; q < 8; ++q)
+                g[q] = w + q < N ? row4(grads + (size_t)(w + q) * ld_g, e, d) : v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) S[t] += (double)g[q][t];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[W] += S[t] * S[t];
+#pragma unroll
+        for (int q0 = 0; q0 < W; q0 += 8) {
+            v4f o[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                o[q] = w0 + q0 + q < N ? row4(out + (size_t)(w0 + q0 + q) * ld_o, e, d) : v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (w0 + q0 + q < N)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const double diff = (double)o[q][t] - S[t];
+                        acc[q0 + q] += diff * diff;
+                    }
         }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int q = 0; q <= kNormWorkers; ++q) {
+    for (int q = 0; q <= W; ++q) {
         const double v = wave_sum(acc[q]);
         if (lane == 0) red[wave][q] = v;
     }
     __syncthreads();
-    if (threadIdx.x <= kNormWorkers) {
+    if (threadIdx.x <= W) {
         const int q = threadIdx.x;
         double v = 0.0;
         for (int w = 0; w < kWaves; ++w) v += red[w][q];
-        if (q < kNormWorkers) {
+        if (q < W) {
             if (w0 + q < N) atomicAdd(norms + w0 + q, v);
         } else if (blockIdx.y == 0) {
             atomicAdd(norms + N, v);
@@ -1887,10 +1920,13 @@ extern "C" int cerar_error_norms(int N, size_t d, const float *grads, size_t ld_
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k_fill_zero, dim3(1), dim3(128), 0, s, norms, N + 1);
     HIP_TRY(hipGetLastError(), "launch fill");
-    size_t blocks = (d + kThreads - 1) / kThreads;
-    blocks = std::min<size_t>(blocks, 4096);
-    const dim3 grid((unsigned)blocks, (unsigned)((N + kNormWorkers - 1) / kNormWorkers));
-    hipLaunchKernelGGL(k_norms, grid, dim3(kThreads), 0, s, N, d, grads, ld_grads, out, ld_out, norms);
+    const size_t blocks = std::min<size_t>((d + 4 * kThreads - 1) / (4 * kThreads), 4096);
+    // up to 16 workers read every gradient row once; more take a grid row per 16
+    if (N <= 8)
+        hipLaunchKernelGGL(k_norms<8>, dim3((unsigned)blocks), dim3(kThreads), 0, s, N, d, grads, ld_grads, out, ld_out, norms);
+    else
+        hipLaunchKernelGGL(k_norms<16>, dim3((unsigned)blocks, (unsigned)((N + 15) / 16)), dim3(kThreads), 0, s, N, d, grads,
+                           ld_grads, out, ld_out, norms);
     HIP_TRY(hipGetLastError(), "launch norms");
     return CERAR_OK;
 }

@@ -118,3 +118,19 @@ def test_infinities_and_nan_stay_in_their_columns(seed):
     np.testing.assert_array_equal(a, b)
     clean = ~np.isin(np.arange(d) % p, bad)
     assert np.all(np.isfinite(a[:, clean]))
+
+
+@pytest.mark.parametrize("N,d,off", [(1, 1, 0), (2, 3, 1), (8, 1023, 0), (8, 4 * 256 * 3 + 2, 3), (9, 4097, 2),
+                                     (16, 5000, 1), (17, 1025, 0), (64, 130, 0)])
+def test_error_norms_at_its_edges(N, d, off):
+    """Rows that start at any float, lengths around a thread's four entries and
+    a workgroup's, worker counts around a grid row's: fp64 sums of d squares,
+    within d units of fp64 rounding of each other in any order."""
+    torch, dev = torch_dev()
+    g, o = host_grads(N, d, seed=N + d), host_grads(N, d, seed=N + d + 1)
+    norms = torch.full((N + 1,), float("nan"), dtype=torch.float64, device=dev)
+    C.error_norms(N, d, to_device(g, ld=d + off, align_elems=off), to_device(o, ld=d + off, align_elems=off), norms)
+    torch.cuda.synchronize()
+    S = g.astype(np.float64).sum(axis=0)
+    ref = [np.sum((o[i].astype(np.float64) - S) ** 2) for i in range(N)] + [np.sum(S * S)]
+    np.testing.assert_allclose(norms.cpu().numpy(), ref, rtol=(d + 4 * N) * 2.0 ** -52)
