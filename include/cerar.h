@@ -32,9 +32,8 @@
  *    that share buffers must be ordered by the caller (one stream does
  *    that).
  *  - Data on the device (gradients, encoded chunks, messages, outputs) is
- *    IEEE fp32.  The encode and decode contractions accumulate in fp32; where
- *    c > 32 and the plan is beyond the one-pass kernel (cerar_ring_simulate)
- *    their fp32 operands are split exactly into three bf16 terms and six of
+ *    IEEE fp32.  The encode and decode contractions accumulate in fp32; with
+ *    c > 64, or N > 8 and c > 32, their fp32 operands are split exactly into three bf16 terms and six of
  *    the nine term products are summed on the bf16 matrix cores
  *    (within two units of fp32 rounding per product).  A round forms
  *    recv - delta_j + delta_{k+1} in fp64 and rounds the message to fp32
@@ -242,7 +241,7 @@ int cerar_decode(const cerar_plan *plan, size_t d, const float *work, size_t ld_
 
 /* Encode, L rounds and decode for all N workers: the whole approximate
  * all-reduce, enqueued on `stream`.  Where the plan fits the one-pass kernel
- * (N <= 8 with c <= 64, or N <= 16 with c <= 32) it is one launch that takes
+ * (N <= 16 with c <= 64) it is one launch that takes
  * a block of positions through the whole protocol on chip; otherwise the
  * launches of the step calls.  Either way `out`, `work` and the workspace
  * end as the step calls leave them: every message is written to the slot

@@ -16,11 +16,26 @@
 #include "device_util.hpp"
 #include "ring_pass.hpp"
 #include "rows.hpp"
+#include "split.hpp"
 
 namespace cerar {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
+// The blocks a workgroup takes.  Workgroups go to the 8 XCDs in turn.  Where
+// rows do not start on a line (a.ragged), each XCD takes a contiguous eighth
+// of the blocks, and the outputs are stored through the L2: the lines that two
+// blocks share are then put together there instead of going to memory in parts
+// (N = 4, c = 12, odd d = 48M: 730 -> 551 us; N = 8, c = 64, odd d = 60M: 2.62
+// -> 1.89 ms).  With rows on lines the plain order and streaming stores are
+// faster (c = 32: 2.70 against 2.74 ms).
+struct Sweep {
+    unsigned first, end, step;
+};
+__device__ inline Sweep sweep_of(const PassParams &a) {
+    if (!a.ragged || gridDim.x % 8 != 0) return {blockIdx.x, a.nblk, gridDim.x};
+    const unsigned share = (a.nblk + 7) / 8, xcd = blockIdx.x % 8;
+    return {xcd * share + blockIdx.x / 8, min(a.nblk, (xcd + 1) * share), gridDim.x / 8};
+}
 
 // The coefficients of a 16-row tile as MFMA A operands, one float per lane
 // and K-step; K-steps past the plan's repeat its last one (the B operands
@@ -226,15 +241,9 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
     auto locate = [&](unsigned g) {
         while (q + 1 < a.n && a.in[q + 1].blk0 <= g) ++q;
     };
-    // Workgroups go to the 8 XCDs in turn.  Where rows do not start on a line
-    // (a.ragged), each XCD takes a contiguous run of blocks within one sweep of
-    // the grid, and the outputs are stored through the L2: the lines that two
-    // blocks share are then put together there instead of going to memory in
-    // parts (N = 8, c = 16, d = 28.5M, rows 96 bytes off: 603 -> 488 us; c = 64,
-    // odd d: 2.62 -> 2.09 ms).  With rows on lines the plain order and
-    // streaming stores are faster (c = 32: 2.70 against 2.74 ms).
-    unsigned g = a.ragged && gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
-    if (g >= a.nblk) return;
+    const Sweep sw = sweep_of(a);
+    unsigned g = sw.first;
+    if (g >= sw.end) return;
     locate(g);
     load(a.in[q], (size_t)(g - a.in[q].blk0) * P);
 #pragma unroll
@@ -247,8 +256,8 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
         const size_t p = I.p, d = I.d, ps = I.pool_stride;
         const size_t e0 = (size_t)(g - I.blk0) * P;
         const bool state = I.work != nullptr, full = e0 + P <= p, narrow = p < kNarrow;
-        g += gridDim.x;
-        const bool more = g < a.nblk;
+        g += sw.step;
+        const bool more = g < sw.end;
         if (more) {                                       // in flight during the rounds and the decode
             locate(g);
             load(a.in[q], (size_t)(g - a.in[q].blk0) * P);
@@ -364,6 +373,221 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
     }
 }
 
+// The same for 8 < N <= 16 and 32 < c <= 64 (EXC: c = 64; K = c + N - 1 <= 80):
+// sixteen waves leave each 128 registers, too few for the coefficients, so
+// they come from the L2 for every block, split into bf16 terms (51 KB per
+// worker at c = 64), and the contractions run on split operands, at 3/8 of the
+// fp32 MFMA time.  Blocks of 32 positions.  N = 16, c = 60, odd d = 20M: 2.06
+// -> 1.43 ms against encode, rounds and decode in turn; N = 12, c = 48, d = 40M:
+// 2.88 -> 2.40 ms.  Not for N <= 8, where k_ring_pass keeps the coefficients
+// (N = 8, c = 64, d = 354M: 10.4 ms there, 11.8-13.4 ms here).
+__device__ inline Split3<v8bf> global_a32(const __bf16 *tile, int kc, uint32_t lane) {
+    typedef __attribute__((address_space(1))) const v8bf G;
+    const __bf16 *b = tile + (size_t)kc * 3 * 64 * 8 + lane * 8;
+    return {*(G *)b, *(G *)(b + 64 * 8), *(G *)(b + 2 * 64 * 8)};
+}
+__device__ inline Split3<v4bf> global_a16(const __bf16 *tile, int KC, uint32_t lane) {
+    typedef __attribute__((address_space(1))) const v4bf G;
+    const __bf16 *b = tile + (size_t)KC * 3 * 64 * 8 + lane * 4;
+    return {*(G *)b, *(G *)(b + 64 * 4), *(G *)(b + 2 * 64 * 4)};
+}
+
+template <bool EXC>
+__global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
+    constexpr int KC = 2, MTC = 4, P = 32, TE = split_tile_encode(KC), TD = split_tile_decode(KC);
+    extern __shared__ __align__(16) float sm[];
+    const int N = a.N, c = EXC ? 64 : a.c, K = c + N - 1;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, g4 = lane >> 4;
+    const int WS = pass_region(N, K, P);
+    const int pv = w == 0 ? N - 1 : w - 1;                // the worker whose messages w receives
+    float *mine = sm + w * WS;
+    const __bf16 *et = reinterpret_cast<const __bf16 *>(a.esplit) + (size_t)w * MTC * TE;
+    const __bf16 *dt = reinterpret_cast<const __bf16 *>(a.dsplit) + (size_t)w * MTC * TD;
+
+    v2f x[KC][8];                                         // rows 32 kc + 8 g4 + s at positions 2 col, 2 col + 1
+    auto load = [&](const PassInst &I, size_t e0) __attribute__((always_inline)) {
+        const size_t p = opaque_s(I.p), d = I.d;
+        const float *src = I.grads + (size_t)w * a.ld_g;
+        if (p < kNarrow / 2 && (size_t)(c - 1) * p + e0 + P <= d) {   // every row of it inside the gradient, short rows
+            const uint32_t lane_in = opaque((uint32_t)(((size_t)(8 * g4) * p + 2 * (size_t)col) * sizeof(float)));
+            const float *row = src + e0;
+#pragma unroll
+            for (int u = 0; u < 8 * KC; ++u) {
+                const int kc = u / 8, s = u % 8;
+                if (EXC || 32 * kc + 32 <= (int)opaque_s(c)) {
+                    x[kc][s] = gload<2>(row, lane_in);
+                } else {
+                    x[kc][s] = v2f{0.f, 0.f};
+                    if (32 * kc + s + 8 * (int)opaque((uint32_t)g4) < c) x[kc][s] = gload<2>(row, lane_in);
+                }
+                row = step(row, s < 7 ? p : 25 * p);
+            }
+        } else {
+            const int gq = (int)opaque((uint32_t)g4), cq = 2 * (int)opaque((uint32_t)col);
+#pragma unroll
+            for (int u = 0; u < 8 * KC; ++u) {
+                const int kc = u / 8, s = u % 8;
+                const int l = 32 * kc + 8 * gq + s;
+                const size_t flat = (size_t)l * p + e0 + cq;
+                x[kc][s] = v2f{0.f, 0.f};
+                if (l < c && flat + 1 < d) x[kc][s] = gload<2>(src + flat, 0);
+                else if (l < c && flat < d) x[kc][s][0] = gload1(src + flat);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    // delta_w on this block, rows j of P positions into LDS
+    auto encode = [&]() __attribute__((always_inline)) {
+        Split3<v8bf> b[KC][2];
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) b[kc][q] = split8([&](int s) { return x[kc][s][q]; });
+        Split3<v8bf> next = global_a32(et, 0, lane);
+#pragma unroll 1
+        for (int mt = 0; mt < MTC; ++mt) {
+            v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) {
+                const Split3<v8bf> A = next;
+                const bool last = kc + 1 == KC;           // then the next tile's first chunk (or this one's again)
+                next = global_a32(et + (size_t)(last ? min(mt + 1, MTC - 1) : mt) * TE, last ? 0 : kc + 1, lane);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) acc[q] = mma_split32(A, b[kc][q], acc[q]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int lrow = 16 * mt + 4 * (int)opaque((uint32_t)g4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (EXC || lrow + r < c)
+                    *reinterpret_cast<v2f *>(mine + (lrow + r) * P + 2 * col) = v2f{acc[0][r], acc[1][r]};
+        }
+    };
+
+    int q = 0;                                            // instance of the block in x
+    auto locate = [&](unsigned g) {
+        while (q + 1 < a.n && a.in[q + 1].blk0 <= g) ++q;
+    };
+    const Sweep sw = sweep_of(a);
+    unsigned g = sw.first;
+    if (g >= sw.end) return;
+    locate(g);
+    load(a.in[q], (size_t)(g - a.in[q].blk0) * P);
+    encode();
+    for (;;) {
+        const PassInst &I = a.in[q];
+        const size_t p = I.p, d = I.d, ps = I.pool_stride;
+        const size_t e0 = (size_t)(g - I.blk0) * P;       // p is a multiple of P: every block is a whole one
+        const bool state = I.work != nullptr;
+        g += sw.step;
+        const bool more = g < sw.end;
+        if (more) {                                       // in flight during the rounds and the decode
+            locate(g);
+            load(a.in[q], (size_t)(g - a.in[q].blk0) * P);
+        }
+        __syncthreads();
+        {
+            float *stale = state ? I.work + (size_t)(c - 2) * p + e0 : nullptr;
+            if (N == 16) rounds<16, P>(sm, WS, 16, c, w, lane, stale, a.ld_w, P);
+            else rounds<0, P>(sm, WS, N, c, w, lane, stale, a.ld_w, P);
+        }
+        __syncthreads();
+        // decode: ghat_w = Y_w R_w
+        v4f dacc[MTC][2];
+#pragma unroll
+        for (int mt = 0; mt < MTC; ++mt) dacc[mt][0] = dacc[mt][1] = v4f{0.f, 0.f, 0.f, 0.f};
+        auto column = [&](int kk) {                       // Y column kk at this lane's positions; none past L
+            const float *row = mine + (kk - (N - 1) + (kk < N - 1 ? K : 0)) * P + 2 * col;
+            return kk < K ? *reinterpret_cast<const v2f *>(row) : v2f{0.f, 0.f};
+        };
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) {
+            const int k0 = 32 * kc + 8 * (int)opaque((uint32_t)g4);
+            v2f y[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) y[s] = column(min(k0 + s, K));
+            const Split3<v8bf> b0 = split8([&](int s) { return y[s][0]; }), b1 = split8([&](int s) { return y[s][1]; });
+#pragma unroll
+            for (int mt = 0; mt < MTC; ++mt) {
+                const Split3<v8bf> A = global_a32(dt + (size_t)mt * TD, kc, opaque(lane));
+                dacc[mt][0] = mma_split32(A, b0, dacc[mt][0]);
+                dacc[mt][1] = mma_split32(A, b1, dacc[mt][1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (K > 32 * KC) {
+            const int k0 = 32 * KC + 4 * (int)opaque((uint32_t)g4);
+            v2f y[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) y[s] = column(min(k0 + s, K));
+            const Split3<v4bf> b0 = split4([&](int s) { return y[s][0]; }), b1 = split4([&](int s) { return y[s][1]; });
+#pragma unroll
+            for (int mt = 0; mt < MTC; ++mt) {
+                const Split3<v4bf> A = global_a16(dt + (size_t)mt * TD, KC, lane);
+                dacc[mt][0] = mma_split16(A, b0, dacc[mt][0]);
+                dacc[mt][1] = mma_split16(A, b1, dacc[mt][1]);
+            }
+        }
+        // the observations to their slots (see k_ring_pass), four rows at a time
+        if (state) {
+            float *own = I.work + (size_t)w * a.ld_w + (size_t)(c - 1) * p + e0;
+            float *rcv = I.work + (size_t)pv * a.ld_w + e0;
+            float *pool = I.pool + (size_t)pv * N * ps + e0;
+            const bool narrow = p < kNarrow;
+            const uint32_t lane_row = opaque((uint32_t)(((size_t)g4 * p + 2 * (size_t)col) * sizeof(float)));
+            float *row4 = step(rcv, (size_t)0) - (size_t)N * p;   // column 4 ks, for 4 ks >= N
+            const float *yin = mine + (g4 - (N - 1)) * P + 2 * col;
+#pragma unroll 4
+            for (int ks = 0; 4 * ks < K; ++ks) {
+                if (narrow && 4 * ks >= N && 4 * ks + 3 < K - 1) {
+                    gstore<2>(row4, lane_row, *reinterpret_cast<const v2f *>(yin + 4 * ks * P));
+                } else {
+                    const int kk = 4 * ks + (int)opaque((uint32_t)g4);
+                    if (kk < K)
+                        gstore<2>((kk < N ? pool + (size_t)kk * ps : (kk < K - 1 ? rcv + (size_t)(kk - N) * p : own)) + 2 * col,
+                                  0, column(kk));
+                }
+                row4 = step(row4, 4 * p);
+            }
+        }
+        float *out = I.out + (size_t)w * a.ld_o;
+        if (p < kNarrow && (size_t)(c - 1) * p + e0 + P <= d) {
+            const uint32_t lane_out = opaque((uint32_t)(((size_t)(4 * g4) * p + 2 * (size_t)col) * sizeof(float)));
+            float *row = out + e0;
+            const bool ragged = a.ragged;
+#pragma unroll
+            for (int mt = 0; mt < MTC; ++mt) {
+                const int lrow = EXC ? 0 : 4 * (int)opaque((uint32_t)g4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const v2f v = {dacc[mt][0][r], dacc[mt][1][r]};
+                    if (EXC || 16 * mt + lrow + r < c) {
+                        if (ragged) gstore_cached<2>(row, lane_out, v);
+                        else gstore<2>(row, lane_out, v);
+                    }
+                    row = step(row, r < 3 ? p : 13 * p);
+                }
+            }
+        } else {
+            const size_t pq = opaque_s(p);
+            const int lrow = 4 * (int)opaque((uint32_t)g4), lcol = 2 * (int)opaque((uint32_t)col);
+#pragma unroll
+            for (int mt = 0; mt < MTC; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = 16 * mt + lrow + r;
+                    const size_t flat = (size_t)m * pq + e0 + lcol;
+                    if (m < c && flat + 1 < d) gstore<2>(out + flat, 0, v2f{dacc[mt][0][r], dacc[mt][1][r]});
+                    else if (m < c && flat < d) gstore1(out + flat, dacc[mt][0][r]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        }
+        if (!more) break;
+        encode();                                         // reads and writes this wave's own rows only
+    }
+}
+
 // All rounds of Algorithm 1 in one launch, for the plans the kernel above does
 // not take: encoded chunks from `work`, observations to their slots.  N
 // waves; each loads its worker's chunk rows (four rows of 64 positions per
@@ -424,8 +648,8 @@ __global__ __launch_bounds__(1024) void k_rounds_pass(PassParams a) {
     const int pv = w == 0 ? N - 1 : w - 1;                // the worker whose messages w receives
     float *mine = sm + w * WS + 4 * col;
     int q = 0;
-    unsigned g = a.ragged && gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
-    for (; g < a.nblk; g += gridDim.x) {
+    const Sweep sw = sweep_of(a);
+    for (unsigned g = sw.first; g < sw.end; g += sw.step) {
         while (q + 1 < a.n && a.in[q + 1].blk0 <= g) ++q;
         const PassInst &I = a.in[q];
         const size_t p = I.p, ps = I.pool_stride;
@@ -488,48 +712,56 @@ int per_cu(Kernel k, int N, size_t lds) {
     return std::max(1, std::min((int)(kPassLds / lds), 4 * waves / N));
 }
 
+// sweeps: workgroups per one that the chip holds at a time.  More of them
+// level the end of the launch and keep the resident ones out of step; each
+// loads its coefficients and its first block with nothing to hide behind
+// (16 against 1: N = 8, c = 16 378 against 391 us, N = 2, c = 16 fused 306
+// against 333; 8 against 1: c = 32 2.68 against 2.70 ms, N = 2, c = 48 581 against
+// 617 us; c = 64 is best with 1, 10.37 against 10.48 ms).
+template <class Kernel>
+void start(Kernel kernel, const PassParams &a, int cus, size_t lds, int sweeps, hipStream_t s) {
+    const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
+    const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * per_cu(kernel, a.N, lds) * sweeps));
+    hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64u * (unsigned)a.N), lds, s, a);
+}
+
 template <int MTC, int KSD, int V, int MAXT, int WPE>
-void go(const PassParams &a, int cus, hipStream_t s) {
+void go(const PassParams &a, int cus, int sweeps, hipStream_t s) {
     const size_t lds = pass_lds(a.N, a.c, V);
-    auto start = [&](auto kernel) {
-        const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
-        const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * per_cu(kernel, a.N, lds)));
-        hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64u * (unsigned)a.N), lds, s, a);
-    };
-    if (a.c == 16 * MTC) start(k_ring_pass<MTC, KSD, V, true, MAXT, WPE>);
-    else start(k_ring_pass<MTC, KSD, V, false, MAXT, WPE>);
+    if (a.c == 16 * MTC) start(k_ring_pass<MTC, KSD, V, true, MAXT, WPE>, a, cus, lds, sweeps, s);
+    else start(k_ring_pass<MTC, KSD, V, false, MAXT, WPE>, a, cus, lds, sweeps, s);
 }
 
 }  // namespace
 
-// N <= 8: c <= 64; 8 < N <= 16: c <= 32, where sixteen waves leave each half
-// the registers.
+// N <= 16, c <= 64 (K = c + N - 1 <= 80 there, one split tail): beyond that a
+// block of all workers' rows does not fit the LDS, or the coefficients' way
+// through the L2 outgrows the gradient's through memory.
 int pass_positions(int N, int c) {
-    if (N > 16 || c > (N > 8 ? 32 : 64)) return 0;
-    return N > 8 ? 32 : (c <= 32 ? 64 : 32);
+    if (N > 16 || c > 64) return 0;
+    return N <= 8 && c <= 32 ? 64 : 32;
 }
 
 int rounds_positions(int N) { return N <= 16 ? 64 : 0; }
 
 void launch_rounds_pass(const PassParams &a, int cus, hipStream_t s) {
-    const size_t lds = (size_t)a.N * pass_region(a.N, a.N + kGroup, 64) * sizeof(float);
-    const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
-    const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * per_cu(k_rounds_pass, a.N, lds)));
-    hipLaunchKernelGGL(k_rounds_pass, dim3(wgs), dim3(64u * (unsigned)a.N), lds, s, a);
+    start(k_rounds_pass, a, cus, (size_t)a.N * pass_region(a.N, a.N + kGroup, 64) * sizeof(float), 4, s);
 }
 
 void launch_ring_pass(const PassParams &a, int cus, hipStream_t s) {
-    const int mt = (a.c + 15) / 16;
     if (a.N > 8) {
-        if (mt == 1) go<1, 8, 2, 1024, 4>(a, cus, s);
-        else go<2, 12, 2, 1024, 4>(a, cus, s);
+        const size_t lds = pass_lds(a.N, a.c, 2);
+        if (a.c <= 16) go<1, 8, 2, 1024, 4>(a, cus, 16, s);
+        else if (a.c <= 32) go<2, 12, 2, 1024, 4>(a, cus, 8, s);
+        else if (a.c < 64) start(k_ring_pass_split<false>, a, cus, lds, 1, s);
+        else start(k_ring_pass_split<true>, a, cus, lds, 1, s);
         return;
     }
-    switch (mt) {
-        case 1: go<1, 6, 4, 512, 4>(a, cus, s); break;
-        case 2: go<2, 10, 4, 512, 4>(a, cus, s); break;
-        case 3: go<3, 14, 2, 512, 2>(a, cus, s); break;
-        default: go<4, 18, 2, 512, 2>(a, cus, s); break;
+    switch ((a.c + 15) / 16) {
+        case 1: go<1, 6, 4, 512, 4>(a, cus, 16, s); break;
+        case 2: go<2, 10, 4, 512, 4>(a, cus, 8, s); break;
+        case 3: go<3, 14, 2, 512, 2>(a, cus, 8, s); break;
+        default: go<4, 18, 2, 512, 2>(a, cus, 1, s); break;
     }
 }
 

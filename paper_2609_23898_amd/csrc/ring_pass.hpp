@@ -40,6 +40,10 @@ inline size_t pass_lds(int N, int c, int V) { return (size_t)N * pass_region(N, 
 // Positions of one workgroup's block for this plan, or 0 where the one-pass
 // kernel does not take it.
 int pass_positions(int N, int c);
+// Whether it contracts on fp32 operands (else on split ones): eight waves can
+// keep the fp32 coefficients of c <= 64 in their registers, sixteen those of
+// c <= 32.
+inline bool pass_is_fp32(int N, int c) { return c <= (N <= 8 ? 64 : 32); }
 // One launch; cus: compute units of the current device.
 void launch_ring_pass(const PassParams &a, int cus, hipStream_t s);
 
