@@ -144,6 +144,7 @@ class Plan:
                  _handle=None):
         L = lib()
         self._h = _P()
+        self._geom = None
         if _handle is not None:
             self._h = _handle
         else:
@@ -211,6 +212,13 @@ class Plan:
         _check(lib().cerar_workspace_bytes(self._h, d, ctypes.byref(b)))
         return b.value
 
+    def _geometry(self, d):
+        """(p, workspace bytes) for gradient length d; the last length's is kept."""
+        last = self._geom
+        if last is None or last[0] != d:
+            last = self._geom = (d, self.chunk_len(d)[0], self.workspace_bytes(d))
+        return last[1:]
+
     def slot_map(self, step):
         out = np.empty(self.N * (self.c + self.N), dtype=np.int32)
         _check(lib().cerar_slot_map(self._h, step, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int))))
@@ -252,50 +260,61 @@ class Plan:
 # --- device calls (torch tensors) ----------------------------------------------
 
 def _stream(stream):
+    """The HIP stream to enqueue on: `stream`, else torch's current one (its
+    handle alone where torch offers that: the Stream object costs 2.7 us)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _ld(t):
     return t.stride(0)
 
 
-def _on_device(t, name):
-    """t must be a tensor in device memory of the current device: the kernels
-    read and write it directly."""
+def _on_device(t, name, current=None):
+    """t must be a tensor in device memory of the current device (`current`
+    where the caller has looked it up): the kernels read and write it
+    directly.  Returns the current device."""
     import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a tensor on the GPU")
-    if t.device.index != torch.cuda.current_device():
-        raise ValueError(f"{name} is on cuda:{t.device.index}, the current device is "
-                         f"cuda:{torch.cuda.current_device()}")
+    if current is None:
+        current = torch.cuda.current_device()
+    if t.device.index != current:
+        raise ValueError(f"{name} is on cuda:{t.device.index}, the current device is cuda:{current}")
+    return current
 
 
-def _rows(t, name, rows, cols, dtype="float32"):
-    """t must be an (at least rows x cols) row-major tensor of `dtype`, so
-    that every element the kernels touch through (pointer, row stride) lies
-    inside it."""
-    _on_device(t, name)
-    if str(t.dtype) != "torch." + dtype:
-        raise ValueError(f"{name} must be {dtype}, not {t.dtype}")
-    if t.dim() != 2 or t.stride(1) != 1:
+def _rows(t, name, rows, cols, current=None):
+    """t must be an (at least rows x cols) row-major float32 tensor, so that
+    every element the kernels touch through (pointer, row stride) lies inside
+    it."""
+    import torch
+    current = _on_device(t, name, current)
+    if t.dtype is not torch.float32:
+        raise ValueError(f"{name} must be float32, not {t.dtype}")
+    shape = t.shape
+    if len(shape) != 2 or t.stride(1) != 1:
         raise ValueError(f"{name} must be a 2-D row-major tensor (unit column stride)")
-    if t.shape[0] < rows or t.shape[1] < cols:
-        raise ValueError(f"{name} has shape {tuple(t.shape)}; at least ({rows}, {cols}) is needed")
+    if shape[0] < rows or shape[1] < cols:
+        raise ValueError(f"{name} has shape {tuple(shape)}; at least ({rows}, {cols}) is needed")
+    return current
 
 
-def _bytes(t, name, nbytes):
+def _bytes(t, name, nbytes, current=None):
     """t must be a contiguous device tensor of at least nbytes bytes."""
-    _on_device(t, name)
+    current = _on_device(t, name, current)
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if t.numel() * t.element_size() < nbytes:
         raise ValueError(f"{name} holds {t.numel() * t.element_size()} bytes; {nbytes} are needed")
+    return current
 
 
 def allocate(plan, d, device="cuda", work_like_grads=False):
@@ -310,15 +329,16 @@ def allocate(plan, d, device="cuda", work_like_grads=False):
 
 
 def _step_buffers(plan, d, grads=None, work=None, ws=None, out=None):
-    p, _ = plan.chunk_len(d)
+    p, ws_bytes = plan._geometry(d)
+    current = None
     if grads is not None:
-        _rows(grads, "grads", plan.N, d)
+        current = _rows(grads, "grads", plan.N, d, current)
     if work is not None:
-        _rows(work, "work", plan.N, plan.c * p)
+        current = _rows(work, "work", plan.N, plan.c * p, current)
     if ws is not None:
-        _bytes(ws, "ws", plan.workspace_bytes(d))
+        current = _bytes(ws, "ws", ws_bytes, current)
     if out is not None:
-        _rows(out, "out", plan.N, d)
+        current = _rows(out, "out", plan.N, d, current)
 
 
 def encode_round(plan, step, d, grads, work, ws, stream=None):
