@@ -895,7 +895,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <=
 }
 
 // Wide decode for c = 16 MTC > 64 with more observations (K > 144) than the
-// split-operand kernel below takes: at 2(L+1)c flops per position the
+// split-operand kernel (split.hip) takes: at 2(L+1)c flops per position the
 // contraction is bound by the fp32 MFMA rate, so one
 // wave per SIMD runs it with two register buffers of B operands: half-block
 // n+1's loads are in flight while half-block n's MTC M-tiles run, and each
@@ -1152,6 +1152,7 @@ int device_copy(const cerar_plan *plan, const DeviceCopy **out) {
         plan->dev.erase(dev);
         return st;
     }
+    prepare_passes(plan->N, plan->c);
     *out = &dc;
     return CERAR_OK;
 }

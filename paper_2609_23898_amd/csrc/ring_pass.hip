@@ -144,9 +144,10 @@ __device__ __forceinline__ void rounds(float *rows, int WS, int N, int c, int wa
 //
 // What bounds it: the memory system on 100-200 rows per worker, 100s of MB
 // apart.  The same loads and stores alone, with neither rounds nor
-// contraction, take 2.66 of 2.78 ms at N = 8, c = 32, d = 124M (4.8 TB/s) and
-// 0.36 of 0.38 ms at c = 16, d = 2^24; at c = 64 the rounds and the fp32 MFMAs
-// add up (they exclude each other on this chip) and bound it.
+// contraction, take 2.66 of 2.68 ms at N = 8, c = 32, d = 124M (4.8 TB/s; 6.03 ms
+// with a launch per round) and 0.36 of 0.38 ms at c = 16, d = 2^24 (0.88 ms);
+// at c = 64, d = 354M (16.3 -> 10.2 ms) the rounds and the fp32 MFMAs add up
+// (they exclude each other on this chip) and bound it.
 //  - The coefficients stay in registers over the whole sweep: a fragment
 //    load after the stores would wait for all of them to drain (memory
 //    operations of a wave complete in order).
@@ -599,7 +600,10 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
 // stored after the group, and the group after next loads into it.
 //
 // Bound by memory: reads every chunk and writes every observation once (2c + N
-// rows per worker) where one launch per round moves 4c + 2N.
+// rows per worker) where one launch per round moves 4c + 2N.  N = 16, c = 128,
+// d = 1e8: 4.78 -> 3.03 ms (4.5 TB/s).  Groups of 16 rounds: one load of four
+// rows per wave and K-quad, and at N = 16 the 32 rows of 64 positions fill 128 of
+// the 160 KB of LDS.
 constexpr int kGroup = 16;
 
 template <int NX>
@@ -720,6 +724,10 @@ int per_cu(Kernel k, int N, size_t lds) {
 // 617 us; c = 64 is best with 1, 10.37 against 10.48 ms).
 template <class Kernel>
 void start(Kernel kernel, const PassParams &a, int cus, size_t lds, int sweeps, hipStream_t s) {
+    if (a.nblk == 0) {                                    // prepare_passes: only what the first launch looks up
+        (void)per_cu(kernel, a.N, lds);
+        return;
+    }
     const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
     const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * per_cu(kernel, a.N, lds) * sweeps));
     hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64u * (unsigned)a.N), lds, s, a);
@@ -746,6 +754,14 @@ int rounds_positions(int N) { return N <= 16 ? 64 : 0; }
 
 void launch_rounds_pass(const PassParams &a, int cus, hipStream_t s) {
     start(k_rounds_pass, a, cus, (size_t)a.N * pass_region(a.N, a.N + kGroup, 64) * sizeof(float), 4, s);
+}
+
+void prepare_passes(int N, int c) {
+    PassParams a{};
+    a.N = N;
+    a.c = c;
+    if (pass_positions(N, c)) launch_ring_pass(a, 0, nullptr);
+    else if (rounds_positions(N)) launch_rounds_pass(a, 0, nullptr);
 }
 
 void launch_ring_pass(const PassParams &a, int cus, hipStream_t s) {

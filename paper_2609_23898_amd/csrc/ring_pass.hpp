@@ -44,6 +44,9 @@ int pass_positions(int N, int c);
 // keep the fp32 coefficients of c <= 64 in their registers, sixteen those of
 // c <= 32.
 inline bool pass_is_fp32(int N, int c) { return c <= (N <= 8 ? 64 : 32); }
+// Looks up what the plan's launches need of their kernels (registers), so that
+// the first launch, which may be under stream capture, only launches.
+void prepare_passes(int N, int c);
 // One launch; cus: compute units of the current device.
 void launch_ring_pass(const PassParams &a, int cus, hipStream_t s);
 
