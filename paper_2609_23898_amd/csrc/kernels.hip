@@ -39,7 +39,13 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 // the decode's row table) would be flat loads, which count against the LDS
 // wait counter too and so serialise the table reads with the data loads.
 // Every buffer here is global memory: say so.
-typedef __attribute__((address_space(1))) const v4f global_cv4f;
+// Rows may start at any float: vector accesses claim four-byte alignment only,
+// which the hardware takes at full width.  One float at a time, odd d at N = 8,
+// c = 64 (d = 60000001) ran a step-call ring in 4.06 ms against 3.48 so, the
+// encode 1416 us against 920; an odd work pointer at d = 64000000 6.00 ms against 3.60.
+typedef float v4u4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float v2u4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef __attribute__((address_space(1))) const v4u4 global_cv4f;
 typedef __attribute__((address_space(1))) const float global_cf;
 __device__ inline v4f nt_load_g(const float *ptr) { return __builtin_nontemporal_load((global_cv4f *)(ptr)); }
 __device__ inline v4f load_g(const float *ptr) { return *(global_cv4f *)(ptr); }
@@ -66,58 +72,39 @@ struct SlotBase {
 };
 
 // ---- position-tile I/O -------------------------------------------------------
-// A wave covers 64 consecutive positions e0..e0+63 of one p-float row.  In the
-// vector layout lane (krow, col) holds positions e0 + 4 col + t, t = 0..3, and
-// MFMA number t works on component t; in the scalar layout MFMA t works on
-// position e0 + 16 t + col.  Entries at or beyond `limit` (flat index
-// row_off + pos) read as zero.
+// A wave covers 64 consecutive positions e0..e0+63 of one p-float row: lane
+// (krow, col) holds positions e0 + 4 col + t, t = 0..3, and MFMA number t works
+// on component t.  Entries at or beyond `limit` (flat index row_off + pos) read
+// as zero.
 
-template <bool VEC>
 __device__ inline v4f load_tile(const float *__restrict__ row, size_t row_off, size_t e0, int col,
                                 size_t p, size_t limit) {
     v4f v = {0.f, 0.f, 0.f, 0.f};
-    if (VEC) {
-        const size_t pos = e0 + 4 * (size_t)col;
-        if (pos < p) {
-            const size_t flat = row_off + pos;
-            if (flat + 3 < limit) {
-                v = load_g(row + pos);
-            } else {
+    const size_t pos = e0 + 4 * (size_t)col;
+    if (pos < p) {
+        const size_t flat = row_off + pos;
+        if (flat + 3 < limit) {
+            v = load_g(row + pos);
+        } else {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (flat + t < limit) v[t] = load1_g(row + pos + t);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const size_t pos = e0 + 16 * (size_t)t + col;
-            if (pos < p && row_off + pos < limit) v[t] = load1_g(row + pos);
+            for (int t = 0; t < 4; ++t)
+                if (flat + t < limit) v[t] = load1_g(row + pos + t);
         }
     }
     return v;
 }
 
-template <bool VEC>
 __device__ inline void store_tile(float *__restrict__ row, size_t row_off, size_t e0, int col, size_t p,
                                   size_t limit, v4f v) {
-    if (VEC) {
-        const size_t pos = e0 + 4 * (size_t)col;
-        if (pos < p) {
-            const size_t flat = row_off + pos;
-            if (flat + 3 < limit) {
-                *reinterpret_cast<v4f *>(row + pos) = v;
-            } else {
+    const size_t pos = e0 + 4 * (size_t)col;
+    if (pos < p) {
+        const size_t flat = row_off + pos;
+        if (flat + 3 < limit) {
+            *reinterpret_cast<v4u4 *>(row + pos) = v;
+        } else {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (flat + t < limit) row[pos + t] = v[t];
-            }
-        }
-    } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const size_t pos = e0 + 16 * (size_t)t + col;
-            if (pos < p && row_off + pos < limit) row[pos] = v[t];
+            for (int t = 0; t < 4; ++t)
+                if (flat + t < limit) row[pos + t] = v[t];
         }
     }
 }
@@ -131,8 +118,8 @@ __device__ inline void store_tile(float *__restrict__ row, size_t row_off, size_
 constexpr int kMaxRegTiles = 4;
 constexpr int kMaxDecodeKS = 48;   // K = c + N - 1 <= 191 observations
 
-__device__ inline v4f nt_load(const float *ptr) { return __builtin_nontemporal_load(reinterpret_cast<const v4f *>(ptr)); }
-__device__ inline void nt_store(float *ptr, v4f v) { __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(ptr)); }
+__device__ inline v4f nt_load(const float *ptr) { return __builtin_nontemporal_load(reinterpret_cast<const v4u4 *>(ptr)); }
+__device__ inline void nt_store(float *ptr, v4f v) { __builtin_nontemporal_store((v4u4)v, reinterpret_cast<v4u4 *>(ptr)); }
 
 // Wave-uniform base pointer plus a 32-bit per-lane byte offset: the form of a
 // global access with a scalar base register, which keeps one VGPR of address
@@ -143,17 +130,32 @@ __device__ inline void nt_store(float *ptr, v4f v) { __builtin_nontemporal_store
 // streaming loads for its c-row access pattern (the decode and the rounds
 // stream with non-temporal loads, which measured faster for them).
 __device__ inline v4f load_off(const float *ubase, uint32_t lane_bytes) {
-    return *reinterpret_cast<const v4f *>(reinterpret_cast<const char *>(ubase) + lane_bytes);
+    return *reinterpret_cast<const v4u4 *>(reinterpret_cast<const char *>(ubase) + lane_bytes);
 }
 __device__ inline v2f nt_load2_g(const float *ptr) {
-    typedef __attribute__((address_space(1))) const v2f global_cv2f;
+    typedef __attribute__((address_space(1))) const v2u4 global_cv2f;
     return __builtin_nontemporal_load((global_cv2f *)(ptr));
 }
-__device__ inline void nt_store2_off(float *ubase, uint32_t lane_bytes, v2f v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<v2f *>(reinterpret_cast<char *>(ubase) + lane_bytes));
+// Stores of a row's entries: NT non-temporal, else through the caches.  (The
+// choice is a compile-time one: of two stores under a condition the compiler
+// makes a single cached one.)
+//
+// The interior encode and decode stream their rows out where these start on 16
+// bytes: cached, the decode itself is up to 6 % faster, but the encode after it
+// pays for the write-back (c = 16, p = 2.5M: 315 us + 389 against 332 + 334).
+// Elsewhere a lane's 16 bytes straddle cache lines that its neighbours complete
+// in the L2 (odd d, decode of c = 32 979 us against 1323 non-temporal, c = 64
+// 1054 against 1371; odd work pointer, step-call ring of c = 64 3.60 ms against
+// 4.05 with the encode non-temporal).
+__device__ inline bool rows_on_16(const float *first, size_t ld) { return ld % 4 == 0 && ((uintptr_t)first & 15) == 0; }
+template <bool NT>
+__device__ inline void store_off(float *ubase, uint32_t lane_bytes, v4f v) {
+    v4u4 *ptr = reinterpret_cast<v4u4 *>(reinterpret_cast<char *>(ubase) + lane_bytes);
+    if (NT) __builtin_nontemporal_store((v4u4)v, ptr);
+    else *ptr = v;
 }
-__device__ inline void nt_store_off(float *ubase, uint32_t lane_bytes, v4f v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(reinterpret_cast<char *>(ubase) + lane_bytes));
+__device__ inline void nt_store2_off(float *ubase, uint32_t lane_bytes, v2f v) {
+    __builtin_nontemporal_store((v2u4)v, reinterpret_cast<v2u4 *>(reinterpret_cast<char *>(ubase) + lane_bytes));
 }
 
 // Copies nmt M-tiles of fragments [mt][ks][lane] into LDS as [mt][ks/4][lane][ks%4].
@@ -307,8 +309,8 @@ struct EncBatch {
     }
 };
 
-// Masked encode: tails, c no multiple of 16, and the scalar layout.
-template <int KS, bool VEC>
+// Masked encode: tails, and c no multiple of 16.
+template <int KS>
 __device__ __forceinline__ void k_encode_body(const EncParams &a, unsigned bid) {
     const int worker = bid % a.N;           // workers interleaved across the grid
     const int wg = bid / a.N;
@@ -334,7 +336,7 @@ __device__ __forceinline__ void k_encode_body(const EncParams &a, unsigned bid) 
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const int l = ks * 4 + krow;
-            b[ks] = (ks < KSx && l < a.c) ? load_tile<VEC>(src + (size_t)l * p, (size_t)l * p, e0, col, p, a.d)
+            b[ks] = (ks < KSx && l < a.c) ? load_tile(src + (size_t)l * p, (size_t)l * p, e0, col, p, a.d)
                                           : v4f{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
@@ -349,8 +351,8 @@ __device__ __forceinline__ void k_encode_body(const EncParams &a, unsigned bid) 
                     const int j = jt + krow * 4 + r;
                     const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
                     if (j < a.c) {
-                        store_tile<VEC>(dst + (size_t)j * p, 0, e0, col, p, p, v);
-                        if (j == 0) store_tile<VEC>(x1, 0, e0, col, p, p, v);
+                        store_tile(dst + (size_t)j * p, 0, e0, col, p, p, v);
+                        if (j == 0) store_tile(x1, 0, e0, col, p, p, v);
                     }
                 }
             }
@@ -358,21 +360,21 @@ __device__ __forceinline__ void k_encode_body(const EncParams &a, unsigned bid) 
     }
 }
 
-template <int KS, bool VEC>
-__global__ __launch_bounds__(kThreads) void k_encode(EncParams a) { k_encode_body<KS, VEC>(a, blockIdx.x); }
+template <int KS>
+__global__ __launch_bounds__(kThreads) void k_encode(EncParams a) { k_encode_body<KS>(a, blockIdx.x); }
 
-template <int KS, bool VEC>
+template <int KS>
 __global__ __launch_bounds__(kThreads) void k_encode_batch(EncBatch b) {
     unsigned bid;
     const EncParams a = b.at(bid);
-    k_encode_body<KS, VEC>(a, bid);
+    k_encode_body<KS>(a, bid);
 }
 
 // Pipelined interior encode for c <= 64 (up to 4 M-tiles): the coefficients
 // stay in LDS, all M-tile accumulators stay in AGPRs, and the next block's
 // loads are issued before the current block's stores, so every wave keeps
 // loads in flight while its stores drain.
-template <int KS, int MTMAX, int NB>
+template <int KS, int MTMAX, int NB, bool NT>
 __device__ __forceinline__ void k_encode_pipe_body(const EncParams &a, unsigned bid) {
     extern __shared__ float sfrag[];
     const int worker = bid % a.N;           // workers interleaved across the grid
@@ -425,8 +427,8 @@ __device__ __forceinline__ void k_encode_pipe_body(const EncParams &a, unsigned 
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const v4f v = {acc[nb][mt][0][r], acc[nb][mt][1][r], acc[nb][mt][2][r], acc[nb][mt][3][r]};
-                        nt_store_off(dst + e0 + (size_t)(jt + r) * p, lane_out, v);   // 16 | c
-                        if (jt + krow * 4 + r == 0) nt_store_off(x1 + e0, (uint32_t)(4 * col * sizeof(float)), v);
+                        store_off<NT>(dst + e0 + (size_t)(jt + r) * p, lane_out, v);   // 16 | c
+                        if (jt + krow * 4 + r == 0) store_off<NT>(x1 + e0, (uint32_t)(4 * col * sizeof(float)), v);
                     }
                 }
             }
@@ -437,13 +439,17 @@ __device__ __forceinline__ void k_encode_pipe_body(const EncParams &a, unsigned 
 }
 
 template <int KS, int MTMAX, int NB>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_encode_pipe(EncParams a) { k_encode_pipe_body<KS, MTMAX, NB>(a, blockIdx.x); }
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_encode_pipe(EncParams a) {
+    if (rows_on_16(a.sb.work, a.sb.ld_work)) k_encode_pipe_body<KS, MTMAX, NB, true>(a, blockIdx.x);
+    else k_encode_pipe_body<KS, MTMAX, NB, false>(a, blockIdx.x);
+}
 
 template <int KS, int MTMAX, int NB>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_encode_pipe_batch(EncBatch b) {
     unsigned bid;
     const EncParams a = b.at(bid);
-    k_encode_pipe_body<KS, MTMAX, NB>(a, bid);
+    if (rows_on_16(a.sb.work, a.sb.ld_work)) k_encode_pipe_body<KS, MTMAX, NB, true>(a, bid);
+    else k_encode_pipe_body<KS, MTMAX, NB, false>(a, bid);
 }
 
 // Double-buffered interior encode for c = 16 MTC (up to 64): two register
@@ -455,7 +461,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
 // it: the compiler's wait counts at the header merge the prologue with the
 // back edge, and a header before the first tile made every other block wait
 // for all of the previous block's stores to drain.
-template <int KS, int MTC, bool ROT>
+template <int KS, int MTC, bool ROT, bool NT>
 __device__ __forceinline__ void k_encode_dbuf_body(const EncParams &a, unsigned bid) {
     extern __shared__ float sfrag[];
     const int worker = bid % a.N;           // workers interleaved across the grid
@@ -493,8 +499,8 @@ __device__ __forceinline__ void k_encode_dbuf_body(const EncParams &a, unsigned 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-            nt_store_off(dst + e0 + (size_t)(mt * 16 + r) * p, lane_out, v);
-            if (mt == 0 && krow * 4 + r == 0) nt_store_off(x1 + e0, (uint32_t)(4 * col * sizeof(float)), v);
+            store_off<NT>(dst + e0 + (size_t)(mt * 16 + r) * p, lane_out, v);
+            if (mt == 0 && krow * 4 + r == 0) store_off<NT>(x1 + e0, (uint32_t)(4 * col * sizeof(float)), v);
         }
     };
     load(b0, blk);
@@ -518,13 +524,17 @@ __device__ __forceinline__ void k_encode_dbuf_body(const EncParams &a, unsigned 
 }
 
 template <int KS, int MTC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <= 2 ? 4 : 2, MTC <= 2 ? 4 : 2))) void k_encode_dbuf(EncParams a) { k_encode_dbuf_body<KS, MTC, true>(a, blockIdx.x); }
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <= 2 ? 4 : 2, MTC <= 2 ? 4 : 2))) void k_encode_dbuf(EncParams a) {
+    if (rows_on_16(a.sb.work, a.sb.ld_work)) k_encode_dbuf_body<KS, MTC, true, true>(a, blockIdx.x);
+    else k_encode_dbuf_body<KS, MTC, true, false>(a, blockIdx.x);
+}
 
 template <int KS, int MTC>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <= 2 ? 4 : 2, MTC <= 2 ? 4 : 2))) void k_encode_dbuf_batch(EncBatch b) {
     unsigned bid;
     const EncParams a = b.at(bid);
-    k_encode_dbuf_body<KS, MTC, false>(a, bid);
+    if (rows_on_16(a.sb.work, a.sb.ld_work)) k_encode_dbuf_body<KS, MTC, false, true>(a, bid);
+    else k_encode_dbuf_body<KS, MTC, false, false>(a, bid);
 }
 
 // ---- K2/K3: one ring round ---------------------------------------------------
@@ -537,54 +547,44 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <=
 struct RoundParams {
     SlotBase sb;
     const RoundOp *ops;     // N entries of this round
-    int wg_per_worker;
+    int wg_per_worker;      // of this launch, from workgroup wg0 of every row on
+    size_t wg0;
 };
 
 constexpr int kRoundThreads = 256;
 
-// One workgroup's share of a round for one worker: positions
-// [wg, wg + 1) x 1024 (vector layout) or a grid-stride loop (scalar layout).
-// V 16-byte elements per thread in the vector layout: workgroup wg covers
-// [wg V, (wg + 1) V) x 1024 floats, V consecutive 1 KiB runs per wave.
-template <int MODE, bool VEC, int V = 1>
-__device__ inline void round_body(const SlotBase &sb, const RoundOp &op, unsigned wg, unsigned wgpw) {
+// One workgroup's share of a round for one worker, V 16-byte elements per
+// thread, stored non-temporally if V is 1: workgroup wg covers [wg V, (wg + 1) V) x 1024 floats, V consecutive
+// 1 KiB runs per wave.  p is a multiple of 4.
+template <int MODE, int V = 1>
+__device__ inline void round_body(const SlotBase &sb, const RoundOp &op, size_t wg) {
     const float *recv = sb.ptr(op.recv);
     const float *sub = MODE >= 1 ? sb.ptr(op.sub) : nullptr;   // aliases dst (in place)
     const float *add = MODE <= 1 ? sb.ptr(op.add) : nullptr;
     float *dst = sb.ptr(op.dst);
     const size_t p = sb.p;
-    if (VEC) {
 #pragma unroll
-        for (int u = 0; u < V; ++u) {
-            const size_t i = (((size_t)wg * V + u) * kRoundThreads + threadIdx.x) * 4;
-            if (i < p) {
-                v4f v = nt_load(recv + i);
-                if (MODE == 0) v = v + nt_load(add + i);
-                if (MODE == 2) v = v - nt_load(sub + i);
-                if (MODE == 1) {
-                    const v4f s = nt_load(sub + i), t = nt_load(add + i);
+    for (int u = 0; u < V; ++u) {
+        const size_t i = ((wg * V + u) * kRoundThreads + threadIdx.x) * 4;
+        if (i < p) {
+            v4f v = nt_load(recv + i);
+            if (MODE == 0) v = v + nt_load(add + i);
+            if (MODE == 2) v = v - nt_load(sub + i);
+            if (MODE == 1) {
+                const v4f s = nt_load(sub + i), t = nt_load(add + i);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = combine3(v[q], s[q], t[q]);
-                }
-                nt_store(dst + i, v);
+                for (int q = 0; q < 4; ++q) v[q] = combine3(v[q], s[q], t[q]);
             }
-        }
-    } else {
-        for (size_t i = (size_t)wg * kRoundThreads + threadIdx.x; i < p; i += (size_t)wgpw * kRoundThreads) {
-            float v = recv[i];
-            if (MODE == 0) v = v + add[i];
-            if (MODE == 2) v = v - sub[i];
-            if (MODE == 1) v = combine3(v, sub[i], add[i]);
-            dst[i] = v;
+            store_off<V == 1>(dst + i, 0, v);
         }
     }
 }
 
-template <int MODE, bool VEC, int V = 1>
+template <int MODE, int V = 1>
 __global__ __launch_bounds__(kRoundThreads) void k_round(RoundParams a) {
     const int worker = blockIdx.x / a.wg_per_worker;
     const int wg = blockIdx.x - worker * a.wg_per_worker;
-    round_body<MODE, VEC, V>(a.sb, a.ops[worker], wg, a.wg_per_worker);
+    round_body<MODE, V>(a.sb, a.ops[worker], a.wg0 + wg);
 }
 
 // The same round for a batch of independent instances (buckets) in one
@@ -606,13 +606,13 @@ struct BatchRoundParams {
     BatchInst b[kMaxBatch];
 };
 
-template <int MODE, bool VEC>
+template <int MODE>
 __global__ __launch_bounds__(kRoundThreads) void k_round_batch(BatchRoundParams a) {
     const BatchInst q = a.b[instance_of(a.b, a.nb, blockIdx.x)];
     const unsigned local = blockIdx.x - q.wg0;
     const int worker = (int)(local / q.wgpw);
     const SlotBase sb{q.work, a.ld_work, q.p, q.pool, q.pool_stride, a.Nc, a.c};
-    round_body<MODE, VEC>(sb, a.ops[worker], local - (unsigned)worker * q.wgpw, q.wgpw);
+    round_body<MODE>(sb, a.ops[worker], local - (unsigned)worker * q.wgpw);
 }
 
 // ---- K4: decode ----------------------------------------------------------------
@@ -661,7 +661,7 @@ struct DecBatch {
     }
 };
 
-template <int KS, bool VEC, bool AREG, bool FAST>
+template <int KS, bool FAST>
 __device__ __forceinline__ void k_decode_body(const DecParams &a, unsigned bid) {
     extern __shared__ float smem[];
     const int worker = bid % a.N;           // workers interleaved across the grid
@@ -670,20 +670,11 @@ __device__ __forceinline__ void k_decode_body(const DecParams &a, unsigned bid) 
     const int col = lane & 15, krow = lane >> 4;
     const int nmt = a.mt1 - a.mt0;
     const int KSx = a.KSd, KS4 = (KSx + 3) / 4;
-    const size_t nfrag = AREG ? 0 : (size_t)nmt * KS4 * 256;
+    const size_t nfrag = (size_t)nmt * KS4 * 256;
     float *sfrag = smem;
     const float **srow = reinterpret_cast<const float **>(smem + ((nfrag + 1) & ~(size_t)1));
     const float *gfrag = a.frag + ((size_t)worker * a.MT + a.mt0) * KSx * 64;
-    float av[AREG ? kMaxRegTiles : 1][KS];
-    if (AREG) {
-#pragma unroll
-        for (int mt = 0; mt < kMaxRegTiles; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                av[mt][ks] = (mt < nmt && ks < KSx) ? gfrag[((size_t)mt * KSx + ks) * 64 + lane] : 0.f;
-    } else {
-        stage_fragments(sfrag, gfrag, nmt, KSx);
-    }
+    stage_fragments(sfrag, gfrag, nmt, KSx);
     // rows K..4 KSx-1 of the last K-step repeat row K-1; their coefficients are zero
     for (int t = threadIdx.x; t < 4 * KS; t += kThreads)
         srow[t] = a.sb.ptr(a.ycols[(size_t)worker * a.K + min(t, a.K - 1)]);
@@ -703,46 +694,42 @@ __device__ __forceinline__ void k_decode_body(const DecParams &a, unsigned bid) 
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 const int k = ks * 4 + krow;
-                b[ks] = (ks < KSx && k < a.K) ? load_tile<VEC>(srow[k], 0, e0, col, p, p) : v4f{0.f, 0.f, 0.f, 0.f};
+                b[ks] = (ks < KSx && k < a.K) ? load_tile(srow[k], 0, e0, col, p, p) : v4f{0.f, 0.f, 0.f, 0.f};
             }
         }
         const uint32_t lane_out = opaque((uint32_t)(((size_t)(krow * 4) * p + 4 * (size_t)col) * sizeof(float)));
+        for (int m2 = 0; m2 < nmt; ++m2) {
+            v4f acc[4];
+            mtile_mma<KS, false>(acc, b, {}, sfrag + (size_t)m2 * KS4 * 256, KSx, lane);
+            const int mtile = (a.mt0 + m2) * 16;
 #pragma unroll
-        for (int mt = 0; mt < (AREG ? kMaxRegTiles : 1); ++mt) {
-            for (int m2 = mt; m2 < (AREG ? mt + 1 : nmt); ++m2) {
-                if (m2 >= nmt) break;
-                v4f acc[4];
-                mtile_mma<KS, AREG>(acc, b, av[AREG ? mt : 0], sfrag + (size_t)m2 * KS4 * 256, KSx, lane);
-                const int mtile = (a.mt0 + m2) * 16;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = mtile + krow * 4 + r;
-                    const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-                    if (FAST) {
-                        nt_store_off(out + e0 + (size_t)(mtile + r) * p, lane_out, v);   // m < c: 16 | c
-                    } else if (m < a.c) {
-                        store_tile<VEC>(out + (size_t)m * p, (size_t)m * p, e0, col, p, a.d, v);
-                    }
+            for (int r = 0; r < 4; ++r) {
+                const int m = mtile + krow * 4 + r;
+                const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+                if (FAST) {
+                    store_off<true>(out + e0 + (size_t)(mtile + r) * p, lane_out, v);   // m < c: 16 | c
+                } else if (m < a.c) {
+                    store_tile(out + (size_t)m * p, (size_t)m * p, e0, col, p, a.d, v);
                 }
             }
         }
     }
 }
 
-template <int KS, bool VEC, bool AREG, bool FAST>
-__global__ __launch_bounds__(kThreads) void k_decode(DecParams a) { k_decode_body<KS, VEC, AREG, FAST>(a, blockIdx.x); }
+template <int KS, bool FAST>
+__global__ __launch_bounds__(kThreads) void k_decode(DecParams a) { k_decode_body<KS, FAST>(a, blockIdx.x); }
 
-template <int KS, bool VEC, bool AREG, bool FAST>
+template <int KS, bool FAST>
 __global__ __launch_bounds__(kThreads) void k_decode_batch(DecBatch b) {
     unsigned bid;
     const DecParams a = b.at(bid);
-    k_decode_body<KS, VEC, AREG, FAST>(a, bid);
+    k_decode_body<KS, FAST>(a, bid);
 }
 
 // Pipelined interior decode for c <= 64: same scheme, B rows through the
 // per-worker table of observation slots; NB adjacent blocks per wave when
 // the M-tiles are few (MTMAX <= 2), as in the encode.
-template <int KS, int MTMAX, int NB>
+template <int KS, int MTMAX, int NB, bool NT>
 __device__ __forceinline__ void k_decode_pipe_body(const DecParams &a, unsigned bid) {
     extern __shared__ float smem[];
     const int worker = bid % a.N;           // workers interleaved across the grid
@@ -797,7 +784,7 @@ __device__ __forceinline__ void k_decode_pipe_body(const DecParams &a, unsigned 
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const v4f v = {acc[nb][mt][0][r], acc[nb][mt][1][r], acc[nb][mt][2][r], acc[nb][mt][3][r]};
-                        nt_store_off(out + e0 + (size_t)(mtile + r) * p, lane_out, v);   // 16 | c
+                        store_off<NT>(out + e0 + (size_t)(mtile + r) * p, lane_out, v);   // 16 | c
                     }
                 }
             }
@@ -808,19 +795,23 @@ __device__ __forceinline__ void k_decode_pipe_body(const DecParams &a, unsigned 
 }
 
 template <int KS, int MTMAX, int NB>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS * NB <= 20 ? 3 : (KS * NB <= 32 ? 2 : 1)))) void k_decode_pipe(DecParams a) { k_decode_pipe_body<KS, MTMAX, NB>(a, blockIdx.x); }
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS * NB <= 20 ? 3 : (KS * NB <= 32 ? 2 : 1)))) void k_decode_pipe(DecParams a) {
+    if (rows_on_16(a.out, a.ld_o)) k_decode_pipe_body<KS, MTMAX, NB, true>(a, blockIdx.x);
+    else k_decode_pipe_body<KS, MTMAX, NB, false>(a, blockIdx.x);
+}
 
 template <int KS, int MTMAX, int NB>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS * NB <= 20 ? 3 : (KS * NB <= 32 ? 2 : 1)))) void k_decode_pipe_batch(DecBatch b) {
     unsigned bid;
     const DecParams a = b.at(bid);
-    k_decode_pipe_body<KS, MTMAX, NB>(a, bid);
+    if (rows_on_16(a.out, a.ld_o)) k_decode_pipe_body<KS, MTMAX, NB, true>(a, bid);
+    else k_decode_pipe_body<KS, MTMAX, NB, false>(a, bid);
 }
 
 // Double-buffered interior decode for c = 16 MTC (up to 64), same scheme as
 // the double-buffered encode; the B rows come through the per-worker table of
 // observation slots.
-template <int KS, int MTC, bool ROT>
+template <int KS, int MTC, bool ROT, bool NT>
 __device__ __forceinline__ void k_decode_dbuf_body(const DecParams &a, unsigned bid) {
     extern __shared__ float smem[];
     const int worker = bid % a.N;           // workers interleaved across the grid
@@ -860,7 +851,7 @@ __device__ __forceinline__ void k_decode_dbuf_body(const DecParams &a, unsigned 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const v4f v = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-            nt_store_off(out + e0 + (size_t)(mt * 16 + r) * p, lane_out, v);   // 16 | c
+            store_off<NT>(out + e0 + (size_t)(mt * 16 + r) * p, lane_out, v);   // 16 | c
         }
     };
     // loop header after a first M-tile on every path (see k_encode_dbuf)
@@ -885,13 +876,17 @@ __device__ __forceinline__ void k_decode_dbuf_body(const DecParams &a, unsigned 
 }
 
 template <int KS, int MTC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <= 2 ? 3 : 2, MTC <= 2 ? 3 : 2))) void k_decode_dbuf(DecParams a) { k_decode_dbuf_body<KS, MTC, true>(a, blockIdx.x); }
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <= 2 ? 3 : 2, MTC <= 2 ? 3 : 2))) void k_decode_dbuf(DecParams a) {
+    if (rows_on_16(a.out, a.ld_o)) k_decode_dbuf_body<KS, MTC, true, true>(a, blockIdx.x);
+    else k_decode_dbuf_body<KS, MTC, true, false>(a, blockIdx.x);
+}
 
 template <int KS, int MTC>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MTC <= 2 ? 3 : 2, MTC <= 2 ? 3 : 2))) void k_decode_dbuf_batch(DecBatch b) {
     unsigned bid;
     const DecParams a = b.at(bid);
-    k_decode_dbuf_body<KS, MTC, false>(a, bid);
+    if (rows_on_16(a.out, a.ld_o)) k_decode_dbuf_body<KS, MTC, false, true>(a, bid);
+    else k_decode_dbuf_body<KS, MTC, false, false>(a, bid);
 }
 
 // Wide decode for c = 16 MTC > 64 with more observations (K > 144) than the
@@ -1218,8 +1213,8 @@ void wg_for(size_t nblk, int &wg_per_worker, size_t &blk_per_wg) {
     blk_per_wg = (nblk + w * kWaves - 1) / (w * kWaves) * kWaves;
 }
 
-// Launch flavours: interior blocks (FAST), masked 16-byte layout, scalar layout.
-enum class Path { kFast, kMaskedVec, kScalar };
+// Launch flavours: interior blocks, and the masked kernel for the rest.
+enum class Path { kFast, kMasked };
 
 // The shared fields of a single-instance launch or of a batch table.
 const EncParams &shared_of(const EncParams &a) { return a; }
@@ -1242,10 +1237,10 @@ void go_encode_dbuf(const P &a, dim3 g, size_t l, hipStream_t s) {
     if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_encode_dbuf_batch<KS, MTC>), g, dim3(kThreads), l, s, a);
     else hipLaunchKernelGGL((k_encode_dbuf<KS, MTC>), g, dim3(kThreads), l, s, a);
 }
-template <int KS, bool VEC, class P>
+template <int KS, class P>
 void go_encode(const P &a, dim3 g, hipStream_t s) {
-    if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_encode_batch<KS, VEC>), g, dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_encode<KS, VEC>), g, dim3(kThreads), 0, s, a);
+    if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_encode_batch<KS>), g, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_encode<KS>), g, dim3(kThreads), 0, s, a);
 }
 template <int KS, int MTMAX, int NB, class P>
 void go_decode_pipe(const P &a, dim3 g, size_t l, hipStream_t s) {
@@ -1257,10 +1252,10 @@ void go_decode_dbuf(const P &a, dim3 g, size_t l, hipStream_t s) {
     if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_decode_dbuf_batch<KS, MTC>), g, dim3(kThreads), l, s, a);
     else hipLaunchKernelGGL((k_decode_dbuf<KS, MTC>), g, dim3(kThreads), l, s, a);
 }
-template <int KS, bool VEC, bool AREG, bool FAST, class P>
+template <int KS, bool FAST, class P>
 void go_decode(const P &a, dim3 g, size_t l, hipStream_t s) {
-    if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_decode_batch<KS, VEC, AREG, FAST>), g, dim3(kThreads), l, s, a);
-    else hipLaunchKernelGGL((k_decode<KS, VEC, AREG, FAST>), g, dim3(kThreads), l, s, a);
+    if constexpr (kIsBatch<P>) hipLaunchKernelGGL((k_decode_batch<KS, FAST>), g, dim3(kThreads), l, s, a);
+    else hipLaunchKernelGGL((k_decode<KS, FAST>), g, dim3(kThreads), l, s, a);
 }
 
 template <int KS, class P>
@@ -1289,8 +1284,7 @@ void launch_encode_ks(const P &a, Path path, hipStream_t s, dim3 grid) {
         }
     }
     // (the interior blocks of a plan have c % 16 == 0, so KS >= 4)
-    if (path == Path::kMaskedVec) go_encode<KS, true>(a, grid, s);
-    else go_encode<KS, false>(a, grid, s);
+    go_encode<KS>(a, grid, s);
 }
 
 template <int KS, class P>
@@ -1321,9 +1315,8 @@ void launch_decode_ks(const P &a, Path path, size_t lds, hipStream_t s, dim3 gri
         }
         go_decode_pipe<KS, kMaxRegTiles, 1>(a, grid, l, s);
     }
-    else if (path == Path::kFast) go_decode<KS, true, false, true>(a, grid, lds, s);
-    else if (path == Path::kMaskedVec) go_decode<KS, true, false, false>(a, grid, lds, s);
-    else go_decode<KS, false, false, false>(a, grid, lds, s);
+    else if (path == Path::kFast) go_decode<KS, true>(a, grid, lds, s);
+    else go_decode<KS, false>(a, grid, lds, s);
 }
 
 // M-tiles per launch so that their staged fragments fit the LDS budget.
@@ -1340,20 +1333,18 @@ int mtiles_per_launch(int MT, int KS, size_t extra) {
 // zero pad of the last chunk remain (at most a few blocks).
 struct BlockSplit {
     size_t interior, total;
-    Path tail;
     bool skip_interior = false;   // the interior blocks were launched elsewhere
 };
 
-BlockSplit split_blocks(const cerar_plan *plan, size_t p, size_t d, bool vec) {
+BlockSplit split_blocks(const cerar_plan *plan, size_t p, size_t d) {
     BlockSplit b;
     b.total = (p + 63) / 64;
     b.interior = 0;
-    b.tail = vec ? Path::kMaskedVec : Path::kScalar;
     const size_t last_row = (size_t)(plan->c - 1) * p;
     // lane offsets of the fast path (up to 12 p + 64 floats) must fit 31 bits
     const bool small_rows = (12 * p + 64) * sizeof(float) < ((size_t)1 << 31);
     // the unmasked stores write all 16 rows of every M-tile: c must fill whole tiles
-    if (vec && small_rows && plan->c % 16 == 0 && d > last_row) b.interior = std::min(p, d - last_row) / 64;
+    if (small_rows && plan->c % 16 == 0 && d > last_row) b.interior = std::min(p, d - last_row) / 64;
     return b;
 }
 
@@ -1369,7 +1360,7 @@ int launch_split(Params a, const BlockSplit &bs, size_t lds, hipStream_t s, int 
         a.blk0 = bs.interior;
         a.blk1 = bs.total;
         wg_for(bs.total - bs.interior, a.wg_per_worker, a.blk_per_wg);
-        launch(a, bs.tail, lds, s, dim3((unsigned)(N * a.wg_per_worker)));
+        launch(a, Path::kMasked, lds, s, dim3((unsigned)(N * a.wg_per_worker)));
     }
     return CERAR_OK;
 }
@@ -1479,8 +1470,7 @@ int enqueue_encode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry 
     a.c = plan->c;
     a.MT = plan->MT;
     a.KSe = plan->KSe;
-    const bool vec = g.vec && (ld_grads % 4 == 0) && aligned16(grads);
-    const BlockSplit bs = split_blocks(plan, g.p, d, vec);
+    const BlockSplit bs = split_blocks(plan, g.p, d);
     const int N = plan->N, ks = plan->KSe;
     a.mt0 = 0;
     a.mt1 = plan->MT;
@@ -1490,12 +1480,9 @@ int enqueue_encode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry 
     return CERAR_OK;
 }
 
-// Workgroups per worker of a round: one 16-byte element per thread, or a
-// grid-stride loop in the scalar layout.
-unsigned round_wgs(size_t p, bool vec, int v = 1) {
-    const size_t w = vec ? (p / 4 + (size_t)v * kRoundThreads - 1) / ((size_t)v * kRoundThreads)
-                         : std::min<size_t>((p + kRoundThreads - 1) / kRoundThreads, 1 << 16);
-    return (unsigned)std::max<size_t>(1, w);
+// Workgroups per worker of a round of v 16-byte elements per thread.
+size_t round_wgs(size_t p, int v = 1) {
+    return std::max<size_t>(1, (p / 4 + (size_t)v * kRoundThreads - 1) / ((size_t)v * kRoundThreads));
 }
 
 int round_mode(const cerar_plan *plan, int k) {
@@ -1505,35 +1492,40 @@ int round_mode(const cerar_plan *plan, int k) {
 // Messages of at most 2^21 floats take two 16-byte elements per thread:
 // in-process A/B at N = 8, the rounds ran 8 % faster at p = 2^20 and 3-6 %
 // faster at p = 2^21, but 3-4 % slower at p = 3.9M and 4.2M and 8 % slower
-// at the Pythia-1.4B length (22.1M), where one element per thread stays.
+// at the Pythia-1.4B length (22.1M), where one element per thread stays.  The
+// short messages are also stored through the caches, the next round reads them
+// there (22.5 us against 23.5 at p = 1.0M, 41.1 against 43.8 at 2.0M; but 37.6
+// against 33.5 at 2.5M, 162 against 154 at 7.8M).  So are messages at any float.
 constexpr size_t kRoundTwoVectorMaxP = (size_t)1 << 21;
 
 int enqueue_round(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g, int k, float *work,
                   size_t ld_work, void *ws, hipStream_t s) {
-    const int N = plan->N, c = plan->c, L = plan->L;
+    const int N = plan->N, L = plan->L;
     if (k == L) return CERAR_OK;                     // the last round only relabels
     RoundParams a;
     a.sb = slot_base(plan, g, work, ld_work, ws);
     a.ops = dc->rounds + (size_t)k * N;
-    const bool two = g.vec && g.p <= kRoundTwoVectorMaxP;
-    a.wg_per_worker = (int)round_wgs(g.p, g.vec, two ? 2 : 1);
-    if (!fits_dispatch((uint64_t)N * a.wg_per_worker, kRoundThreads))
+    const bool two = g.p <= kRoundTwoVectorMaxP || !g.vec;
+    const size_t wgs = round_wgs(g.p, two ? 2 : 1);
+    const bool fits = fits_dispatch((uint64_t)N * wgs, kRoundThreads);
+    if (!fits && g.vec)
         return fail(CERAR_E_INVAL, "p=%zu is too long for one round launch over N=%d workers", g.p, N);
-    const dim3 grid((unsigned)(N * a.wg_per_worker));
-    (void)c;
+    // rows at any float have no such limit: slices of the positions
+    const size_t slice = fits ? wgs : ((size_t)1 << 20);
     const int mode = round_mode(plan, k);
-    if (two) {
-        if (mode == 0) hipLaunchKernelGGL((k_round<0, true, 2>), grid, dim3(kRoundThreads), 0, s, a);
-        else if (mode == 1) hipLaunchKernelGGL((k_round<1, true, 2>), grid, dim3(kRoundThreads), 0, s, a);
-        else hipLaunchKernelGGL((k_round<2, true, 2>), grid, dim3(kRoundThreads), 0, s, a);
-    } else if (g.vec) {
-        if (mode == 0) hipLaunchKernelGGL((k_round<0, true>), grid, dim3(kRoundThreads), 0, s, a);
-        else if (mode == 1) hipLaunchKernelGGL((k_round<1, true>), grid, dim3(kRoundThreads), 0, s, a);
-        else hipLaunchKernelGGL((k_round<2, true>), grid, dim3(kRoundThreads), 0, s, a);
-    } else {
-        if (mode == 0) hipLaunchKernelGGL((k_round<0, false>), grid, dim3(kRoundThreads), 0, s, a);
-        else if (mode == 1) hipLaunchKernelGGL((k_round<1, false>), grid, dim3(kRoundThreads), 0, s, a);
-        else hipLaunchKernelGGL((k_round<2, false>), grid, dim3(kRoundThreads), 0, s, a);
+    for (size_t w = 0; w < wgs; w += slice) {
+        a.wg0 = w;
+        a.wg_per_worker = (int)std::min(slice, wgs - w);
+        const dim3 grid((unsigned)(N * a.wg_per_worker));
+        if (two) {
+            if (mode == 0) hipLaunchKernelGGL((k_round<0, 2>), grid, dim3(kRoundThreads), 0, s, a);
+            else if (mode == 1) hipLaunchKernelGGL((k_round<1, 2>), grid, dim3(kRoundThreads), 0, s, a);
+            else hipLaunchKernelGGL((k_round<2, 2>), grid, dim3(kRoundThreads), 0, s, a);
+        } else {
+            if (mode == 0) hipLaunchKernelGGL((k_round<0>), grid, dim3(kRoundThreads), 0, s, a);
+            else if (mode == 1) hipLaunchKernelGGL((k_round<1>), grid, dim3(kRoundThreads), 0, s, a);
+            else hipLaunchKernelGGL((k_round<2>), grid, dim3(kRoundThreads), 0, s, a);
+        }
     }
     HIP_TRY(hipGetLastError(), "launch round");
     return CERAR_OK;
@@ -1557,8 +1549,7 @@ int enqueue_decode(const cerar_plan *plan, const DeviceCopy *dc, const Geometry 
     a.K = plan->L + 1;
     a.MT = plan->MT;
     a.KSd = plan->KSd;
-    const bool vec = g.vec && (ld_out % 4 == 0) && aligned16(out);
-    const BlockSplit bs = split_blocks(plan, g.p, d, vec);
+    const BlockSplit bs = split_blocks(plan, g.p, d);
     const int N = plan->N, ks = plan->KSd;
     const size_t rows_bytes = kDecodeRowsBytes;
     BlockSplit rest = bs;
@@ -2019,14 +2010,14 @@ int launch_bucket_batches(const cerar_plan *plan, const std::vector<BucketRef> &
         auto flush = [&]() -> int {
             if (b.n == 0) return CERAR_OK;
             if (!fits_dispatch(wgs, kThreads)) return fail(CERAR_E_INVAL, "bucket batch too large for one launch");
-            launch(b, pass == 0 ? Path::kFast : Path::kMaskedVec, dim3((unsigned)wgs));
+            launch(b, pass == 0 ? Path::kFast : Path::kMasked, dim3((unsigned)wgs));
             HIP_TRY(hipGetLastError(), "launch bucket batch");
             b.n = 0;
             wgs = 0;
             return CERAR_OK;
         };
         for (size_t q = 0; q < bk.size(); ++q) {
-            const BlockSplit bs = split_blocks(plan, bk[q].p, bk[q].d, true);
+            const BlockSplit bs = split_blocks(plan, bk[q].p, bk[q].d);
             const size_t lo = pass == 0 ? 0 : bs.interior, hi = pass == 0 ? bs.interior : bs.total;
             if (hi <= lo) continue;
             int wgpw;
@@ -2189,29 +2180,18 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
         return CERAR_OK;
     }
     std::vector<Geometry> geo(nbuckets);
-    bool all_vec = true;
-    for (int b = 0; b < nbuckets; ++b) {
-        const BucketLayout &B = lay[b];
-        Geometry &g = geo[b];
-        g.p = B.p;
-        g.pool_stride = B.stride;
-        g.vec = (g.p % 4 == 0) && (ld_work % 4 == 0) && aligned16(work + B.work_off) &&
-                aligned16((char *)ws + B.ws_off);
-        all_vec = all_vec && g.vec;
-    }
+    for (int b = 0; b < nbuckets; ++b) geo[b] = Geometry{lay[b].p, lay[b].stride, false};
     // every bucket's encode, then each round once for all buckets (up to
     // kMaxBatch per launch), then every bucket's decode: one stream orders them.
-    // With c <= 64 and 16-byte rows everywhere, the encode and the decode are
-    // batched too (interior blocks of up to kMaxInst buckets per launch, then
-    // their tails); otherwise each bucket gets its own launches.
-    bool batched = all_vec && plan->KC == 0 && ld_grads % 4 == 0 && ld_out % 4 == 0 &&
-                   mtiles_per_launch(plan->MT, plan->KSd, kDecodeRowsBytes) == plan->MT;
+    // With c <= 64 the encode and the decode are batched too (interior blocks of
+    // up to kMaxInst buckets per launch, then their tails); otherwise each bucket
+    // gets its own launches.
+    const bool batched = plan->KC == 0 && mtiles_per_launch(plan->MT, plan->KSd, kDecodeRowsBytes) == plan->MT;
     std::vector<BucketRef> bk(nbuckets);
     std::vector<PassInst> inst(nbuckets);
     for (int b = 0; b < nbuckets; ++b) {
         bk[b] = BucketRef{grads + bucket_off[b], out + bucket_off[b], work + lay[b].work_off,
                           (char *)ws + lay[b].ws_off, bucket_len[b], lay[b].p, lay[b].stride};
-        batched = batched && aligned16(bk[b].grads) && aligned16(bk[b].out);
         inst[b] = PassInst{bk[b].grads, bk[b].out, bk[b].work, (float *)bk[b].ws, bk[b].d, bk[b].p, bk[b].pool_stride, 0};
     }
     // f(first, count) for every launch's share of the buckets
@@ -2242,7 +2222,7 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
             // up to kMaxBatch buckets, as many as one dispatch holds
             for (; b0 < nbuckets && a.nb < kMaxBatch; ++b0) {
                 const BucketLayout &B = lay[b0];
-                const unsigned wgpw = round_wgs(B.p, all_vec);
+                const size_t wgpw = round_wgs(B.p);
                 if (!fits_dispatch(wgs + (size_t)N * wgpw, kRoundThreads)) {
                     if (a.nb == 0) return fail(CERAR_E_INVAL, "bucket of p=%zu is too long for one round launch", B.p);
                     break;
@@ -2252,21 +2232,15 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
                 I.pool = (float *)((char *)ws + B.ws_off);
                 I.p = B.p;
                 I.pool_stride = B.stride;
-                I.wgpw = wgpw;
+                I.wgpw = (unsigned)wgpw;
                 I.wg0 = (unsigned)wgs;
                 wgs += (size_t)N * wgpw;
             }
             const dim3 grid((unsigned)wgs);
             const int mode = round_mode(plan, k);
-            if (all_vec) {
-                if (mode == 0) hipLaunchKernelGGL((k_round_batch<0, true>), grid, dim3(kRoundThreads), 0, s, a);
-                else if (mode == 1) hipLaunchKernelGGL((k_round_batch<1, true>), grid, dim3(kRoundThreads), 0, s, a);
-                else hipLaunchKernelGGL((k_round_batch<2, true>), grid, dim3(kRoundThreads), 0, s, a);
-            } else {
-                if (mode == 0) hipLaunchKernelGGL((k_round_batch<0, false>), grid, dim3(kRoundThreads), 0, s, a);
-                else if (mode == 1) hipLaunchKernelGGL((k_round_batch<1, false>), grid, dim3(kRoundThreads), 0, s, a);
-                else hipLaunchKernelGGL((k_round_batch<2, false>), grid, dim3(kRoundThreads), 0, s, a);
-            }
+            if (mode == 0) hipLaunchKernelGGL((k_round_batch<0>), grid, dim3(kRoundThreads), 0, s, a);
+            else if (mode == 1) hipLaunchKernelGGL((k_round_batch<1>), grid, dim3(kRoundThreads), 0, s, a);
+            else hipLaunchKernelGGL((k_round_batch<2>), grid, dim3(kRoundThreads), 0, s, a);
             HIP_TRY(hipGetLastError(), "launch bucket round");
         }
     }

@@ -68,9 +68,33 @@ def test_one_pass_leaves_the_step_calls_bits(N, c, d, off, extra):
     assert torch.equal(got[2][:, :d], again[:, :d])
 
 
+@pytest.mark.parametrize("N,c,d", [(4, 12, 12 * 320 + 5), (3, 33, 33 * 97), (8, 16, 16 * 640 + 1), (8, 48, 48 * 160 - 65),
+                                   (8, 64, 64 * 333 + 9), (20, 32, 32 * 64 * 9 + 5), (18, 128, 128 * 96 - 1),
+                                   (24, 70, 70 * 130 + 3)])
+@pytest.mark.parametrize("off,extra", [(1, 1), (2, 2), (3, 4)])
+def test_step_calls_on_rows_at_any_float(N, c, d, off, extra):
+    """The same bits as on 16-byte aligned rows, in `out` and in every message
+    round's slots, and nothing written beside the rows."""
+    torch, _ = torch_dev()
+    U, R = orthogonal_plan(N, c, seed=N + c)
+    plan = C.Plan.explicit(U, R)
+    p, _ = plan.chunk_len(d)
+    host = host_grads(N, d, seed=c + d)
+    got = buffers(plan, d, ld_work=c * p + extra, ld_out=d + extra, work_offset=off, out_offset=off)
+    want = buffers(plan, d, ld_out=(d + 3) // 4 * 4)
+    _steps(plan, d, to_device(host, ld=d + extra, align_elems=off), *got)
+    _steps(plan, d, to_device(host, ld=(d + 3) // 4 * 4), *want)
+    torch.cuda.synchronize()
+    assert torch.equal(got[2][:, :d], want[2][:, :d])
+    assert bool(torch.isnan(got[2][:, d:]).all()) and bool(torch.isnan(got[0][:, c * p:]).all())
+    for a, b in zip(_state(plan, d, got[0], got[1]), _state(plan, d, want[0], want[1])):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("N,c,lens", [(8, 20, [20 * 64 * 5 + 3, 1, 20 * 63, 7777]), (3, 64, [64 * 33, 64 * 31 + 5]),
                                       (4, 12, [97 * (b + 1) for b in range(33)]),
-                                      (8, 70, [70 * 64 + 1, 70 * 200, 9]), (16, 64, [64 * 96] * 3)])
+                                      (8, 70, [70 * 64 + 1, 70 * 200, 9]), (16, 64, [64 * 96] * 3),
+                                      (18, 32, [32 * 64 * 5 + 3, 1, 32 * 97]), (17, 24, [24 * 65, 7, 24 * 64 + 5])])
 def test_buckets_equal_calls_of_their_own(N, c, lens):
     """Odd offsets and lengths, more buckets than one launch takes: each bucket
     has the bits of its own call."""
