@@ -240,10 +240,13 @@ int cerar_decode(const cerar_plan *plan, size_t d, const float *work, size_t ld_
                  const void *ws, float *out, size_t ld_out, cerar_stream stream);
 
 /* Encode, L rounds and decode for all N workers: the whole approximate
- * all-reduce, enqueued on `stream`.  Where the plan fits the one-pass kernel
- * (N <= 16 with c <= 64) it is one launch that takes
- * a block of positions through the whole protocol on chip; otherwise the
- * launches of the step calls.  Either way `out`, `work` and the workspace
+ * all-reduce, enqueued on `stream`.  out may share memory with grads in any
+ * way (all gradients are read before sums are written over them), but not
+ * with work or ws.  Where the plan fits the one-pass kernel (N <= 16 with
+ * c <= 64), and out is grads itself (same pointer and stride) or apart from
+ * it, it is one launch that takes a block of positions through the whole
+ * protocol on chip; otherwise encode, rounds and decode follow each other, with
+ * all rounds in one launch for N <= 16.  Either way `out`, `work` and the workspace
  * end as the step calls leave them: every message is written to the slot
  * that cerar_slot_map names (it is an observation of the worker that receives
  * it), so cerar_decode may be called on them again.  What the one-pass launch

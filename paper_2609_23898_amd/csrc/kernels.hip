@@ -1169,6 +1169,17 @@ bool overlap(const void *a, size_t abytes, const void *b, size_t bbytes) {
     return pa < pb + bbytes && pb < pa + abytes;
 }
 
+// Whether some row of a (N rows of n floats at stride lda) shares memory with
+// some row of b.  Rows at one stride are compared modulo it, so that column
+// slices of one array count as apart; other strides by their whole extents.
+bool rows_overlap(const float *a, size_t lda, const float *b, size_t ldb, size_t N, size_t n) {
+    if (!overlap(a, ((N - 1) * lda + n) * sizeof(float), b, ((N - 1) * ldb + n) * sizeof(float))) return false;
+    if (lda != ldb) return true;
+    const uintptr_t ld = lda * sizeof(float), len = n * sizeof(float);
+    const uintptr_t apart = (a < b ? (uintptr_t)b - (uintptr_t)a : (uintptr_t)a - (uintptr_t)b) % ld;
+    return apart < len || ld - apart < len;
+}
+
 struct Geometry {
     size_t p, pool_stride;
     bool vec;
@@ -1596,11 +1607,21 @@ int enqueue_rounds(const cerar_plan *plan, const DeviceCopy *dc, const PassInst 
     return CERAR_OK;
 }
 
-// Encode, rounds and decode of one instance: one pass where the one-pass
-// kernel takes the plan, else the launches of the step calls.
+// Positions of a one-pass block, or 0 where the call cannot go in one pass: the
+// plan does not fit, or a block's outputs lie where another block's gradients
+// are still to be read.  With `out` at `grads` itself a block reads and writes
+// the same positions.  n: floats of a row that the call touches.
+int one_pass_positions(const cerar_plan *plan, const float *grads, size_t ld_grads, const float *out, size_t ld_out,
+                       size_t n) {
+    if (!(grads == out && ld_grads == ld_out) && rows_overlap(grads, ld_grads, out, ld_out, plan->N, n)) return 0;
+    return pass_positions(plan->N, plan->c);
+}
+
+// Encode, rounds and decode of one instance: in one pass where that is
+// possible, else in turn.
 int enqueue_ring(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g, size_t d, const float *grads,
                  size_t ld_grads, float *work, size_t ld_work, void *ws, float *out, size_t ld_out, hipStream_t s) {
-    if (const int P = pass_positions(plan->N, plan->c)) {
+    if (const int P = one_pass_positions(plan, grads, ld_grads, out, ld_out, d)) {
         PassParams a = pass_params(plan, dc, ld_grads, ld_work, ld_out);
         add_instance(a, P, PassInst{grads, out, work, (float *)ws, d, g.p, g.pool_stride, 0});
         launch_ring_pass(a, dc->cus, s);
@@ -2165,7 +2186,7 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
     st = device_copy(plan, &dc);
     if (st) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (const int P = pass_positions(plan->N, plan->c)) {
+    if (const int P = one_pass_positions(plan, grads, ld_grads, out, ld_out, span)) {
         // every bucket's encode, rounds and decode in one launch for up to
         // kPassInst buckets
         for (int b0 = 0; b0 < nbuckets; b0 += kPassInst) {

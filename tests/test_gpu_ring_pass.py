@@ -158,3 +158,48 @@ def test_error_norms_at_its_edges(N, d, off):
     S = g.astype(np.float64).sum(axis=0)
     ref = [np.sum((o[i].astype(np.float64) - S) ** 2) for i in range(N)] + [np.sum(S * S)]
     np.testing.assert_allclose(norms.cpu().numpy(), ref, rtol=(d + 4 * N) * 2.0 ** -52)
+
+
+def _sharing(how, N, d, s):
+    """(grads, out) views of one allocation: out on grads itself, some floats
+    ahead of or behind it, at another row stride, or in the columns beside it."""
+    torch, dev = torch_dev()
+    if how == "columns":
+        both = torch.empty((N, 2 * d), dtype=torch.float32, device=dev)
+        return both[:, :d], both[:, d:]
+    flat = torch.empty(N * (d + s) + 2 * s, dtype=torch.float32, device=dev)
+    at, stride = {"itself": (s, d), "ahead": (2 * s, d), "behind": (0, d), "stride": (s, d + s)}[how]
+    return flat[s:].as_strided((N, d), (d, 1)), flat[at:].as_strided((N, d), (stride, 1))
+
+
+@pytest.mark.parametrize("how,s", [("itself", 32), ("ahead", 96), ("ahead", 7), ("behind", 4096), ("stride", 320),
+                                   ("columns", 0)])
+@pytest.mark.parametrize("N,c", [(4, 12), (8, 64), (12, 48)])
+def test_outputs_may_lie_on_the_gradients(N, c, how, s):
+    """Whatever memory `out` shares with `grads`, the sums are those of buffers
+    of their own, in the single, the no-alloc and the bucketed call."""
+    torch, dev = torch_dev()
+    U, R = orthogonal_plan(N, c, seed=N * c)
+    plan = C.Plan.explicit(U, R)
+    plan.prepare_device()
+    d = c * 64 * 1500 - 3
+    g = torch.randn((N, d), dtype=torch.float32, device=dev, generator=torch.Generator(dev).manual_seed(c))
+    work, ws, want = buffers(plan, d)
+    C.ring_simulate(plan, d, g, work, ws, want)
+    for call in (lambda gr, out: C.ring_simulate(plan, d, gr, work, ws, out),
+                 lambda gr, out: C.ring_simulate_noalloc(plan, d, gr, work, out)):
+        grads, out = _sharing(how, N, d, s)
+        grads.copy_(g)
+        call(grads, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    lens = [d // 3 + 1, 5, d - d // 3 - 6]
+    buckets = list(zip([0, lens[0], lens[0] + 5], lens))
+    wf, wsb = plan.bucketed_sizes(lens)
+    bwork, bws = torch.empty((N, wf), dtype=torch.float32, device=dev), torch.empty(wsb, dtype=torch.uint8, device=dev)
+    C.ring_simulate_bucketed(plan, buckets, g, bwork, bws, want)
+    grads, out = _sharing(how, N, d, s)
+    grads.copy_(g)
+    C.ring_simulate_bucketed(plan, buckets, grads, bwork, bws, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
