@@ -64,6 +64,12 @@ constexpr int split_tile_decode(int KC) { return KC * 3 * 64 * 8 + 3 * 64 * 4; }
 // writes in the same launch.  Returns an empty string or a diagnostic.
 std::string build_ring_tables(int N, int c, RingTables &t);
 
+// Workgroups that one compute unit holds at a time, of the plan's one-pass and
+// rounds kernels (0 where it has none).
+struct PassSize {
+    int ring = 0, rounds = 0;
+};
+
 struct DeviceCopy {
     float *enc_frag = nullptr;       // N x MT x KSe x 64 fp32 fragments of U_i
     float *dec_frag = nullptr;       // N x MT x KSd x 64 fp32 fragments of R_i
@@ -72,6 +78,7 @@ struct DeviceCopy {
     uint16_t *enc_split = nullptr;   // the split operands of U_i and R_i (plans with KC > 0)
     uint16_t *dec_split = nullptr;
     int cus = 0;                     // compute units of the device
+    PassSize size;
 };
 
 }  // namespace cerar

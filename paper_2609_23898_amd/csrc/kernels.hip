@@ -1131,6 +1131,8 @@ int device_copy(const cerar_plan *plan, const DeviceCopy **out) {
     int st = CERAR_OK;
     if (hipError_t e = hipDeviceGetAttribute(&dc.cus, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess)
         st = hip_fail(e, "hipDeviceGetAttribute");
+    if (!st)
+        if (hipError_t e = prepare_passes(plan->N, plan->c, &dc.size); e != hipSuccess) st = hip_fail(e, "hipFuncGetAttributes");
     if (!st) st = upload(&dc.enc_frag, plan->enc_frag.data(), plan->enc_frag.size());
     if (!st) st = upload(&dc.dec_frag, plan->dec_frag.data(), plan->dec_frag.size());
     if (!st && !plan->enc_split.empty()) st = upload(&dc.enc_split, plan->enc_split.data(), plan->enc_split.size());
@@ -1147,7 +1149,6 @@ int device_copy(const cerar_plan *plan, const DeviceCopy **out) {
         plan->dev.erase(dev);
         return st;
     }
-    prepare_passes(plan->N, plan->c);
     *out = &dc;
     return CERAR_OK;
 }
@@ -1602,7 +1603,7 @@ int enqueue_rounds(const cerar_plan *plan, const DeviceCopy *dc, const PassInst 
         r.grads = r.out = r.work;
         add_instance(a, rounds_positions(plan->N), r);
     }
-    launch_rounds_pass(a, dc->cus, s);
+    launch_rounds_pass(a, dc->cus, dc->size, s);
     HIP_TRY(hipGetLastError(), "launch rounds pass");
     return CERAR_OK;
 }
@@ -1624,7 +1625,7 @@ int enqueue_ring(const cerar_plan *plan, const DeviceCopy *dc, const Geometry &g
     if (const int P = one_pass_positions(plan, grads, ld_grads, out, ld_out, d)) {
         PassParams a = pass_params(plan, dc, ld_grads, ld_work, ld_out);
         add_instance(a, P, PassInst{grads, out, work, (float *)ws, d, g.p, g.pool_stride, 0});
-        launch_ring_pass(a, dc->cus, s);
+        launch_ring_pass(a, dc->cus, dc->size, s);
         HIP_TRY(hipGetLastError(), "launch ring pass");
         return CERAR_OK;
     }
@@ -1912,7 +1913,7 @@ static int ring_simulate_fused_impl(const cerar_plan *plan, size_t d, const floa
     if (N > 8 && c > 32) return fail(CERAR_E_INVAL, "the fused variant needs c <= 32 when N > 8");
     PassParams a = pass_params(plan, dc, ld_grads, 0, ld_out);
     add_instance(a, pass_positions(N, c), PassInst{grads, out, nullptr, nullptr, d, p, 0, 0});
-    launch_ring_pass(a, dc->cus, reinterpret_cast<hipStream_t>(stream));
+    launch_ring_pass(a, dc->cus, dc->size, reinterpret_cast<hipStream_t>(stream));
     HIP_TRY(hipGetLastError(), "launch fused");
     return CERAR_OK;
 }
@@ -2195,7 +2196,7 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
                 add_instance(a, P, PassInst{grads + bucket_off[b], out + bucket_off[b], work + lay[b].work_off,
                                             (float *)((char *)ws + lay[b].ws_off), bucket_len[b], lay[b].p,
                                             lay[b].stride, 0});
-            launch_ring_pass(a, dc->cus, s);
+            launch_ring_pass(a, dc->cus, dc->size, s);
             HIP_TRY(hipGetLastError(), "launch ring pass");
         }
         return CERAR_OK;

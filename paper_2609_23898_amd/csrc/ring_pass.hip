@@ -705,39 +705,60 @@ __global__ __launch_bounds__(1024) void k_rounds_pass(PassParams a) {
     }
 }
 
-// Workgroups of a kernel that one CU holds at a time.
-template <class Kernel>
-int per_cu(Kernel k, int N, size_t lds) {
-    static const int waves = [&] {                        // wavefronts per SIMD that its registers allow
-        hipFuncAttributes at;
-        if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(k)) != hipSuccess) return 1;
-        return std::max(1, std::min(8, 512 / std::max(8, (at.numRegs + 7) / 8 * 8)));
-    }();
-    return std::max(1, std::min((int)(kPassLds / lds), 4 * waves / N));
+// A kernel that takes PassParams, its LDS and its launch size.
+struct PassKernel {
+    void (*fn)(PassParams);
+    size_t lds;
+    int sweeps;
+};
+
+template <int MTC, int KSD, int V, int MAXT, int WPE>
+PassKernel one_pass(int N, int c, int sweeps) {
+    return {c == 16 * MTC ? k_ring_pass<MTC, KSD, V, true, MAXT, WPE> : k_ring_pass<MTC, KSD, V, false, MAXT, WPE>,
+            pass_lds(N, c, V), sweeps};
 }
 
 // sweeps: workgroups per one that the chip holds at a time.  More of them
 // level the end of the launch and keep the resident ones out of step; each
-// loads its coefficients and its first block with nothing to hide behind
-// (16 against 1: N = 8, c = 16 378 against 391 us, N = 2, c = 16 fused 306
-// against 333; 8 against 1: c = 32 2.68 against 2.70 ms, N = 2, c = 48 581 against
-// 617 us; c = 64 is best with 1, 10.37 against 10.48 ms).
-template <class Kernel>
-void start(Kernel kernel, const PassParams &a, int cus, size_t lds, int sweeps, hipStream_t s) {
-    if (a.nblk == 0) {                                    // prepare_passes: only what the first launch looks up
-        (void)per_cu(kernel, a.N, lds);
-        return;
+// loads its coefficients and its first block with nothing to hide behind.
+// Many pay while the coefficients are few (16 against 1: N = 8, c = 16 379
+// against 392 us, N = 4, c = 12 575 against 606; 8 against 1: N = 8, c = 32 2.66
+// against 2.68 ms), one is best beyond (1 against 8: N = 2, c = 48 319 against 345
+// us, N = 8, c = 48 1.63 against 1.66 ms, N = 4, c = 64 827 against 867 us, N = 16,
+// c = 32 2.08 against 2.14 ms).
+PassKernel ring_kernel(int N, int c) {
+    if (N > 8) {
+        if (c <= 16) return one_pass<1, 8, 2, 1024, 4>(N, c, 16);
+        if (c <= 32) return one_pass<2, 12, 2, 1024, 4>(N, c, 1);
+        return {c < 64 ? k_ring_pass_split<false> : k_ring_pass_split<true>, pass_lds(N, c, 2), 1};
     }
-    const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
-    const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * per_cu(kernel, a.N, lds) * sweeps));
-    hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64u * (unsigned)a.N), lds, s, a);
+    switch ((c + 15) / 16) {
+        case 1: return one_pass<1, 6, 4, 512, 4>(N, c, 16);
+        case 2: return one_pass<2, 10, 4, 512, 4>(N, c, 8);
+        case 3: return one_pass<3, 14, 2, 512, 2>(N, c, 1);
+        default: return one_pass<4, 18, 2, 512, 2>(N, c, 1);
+    }
 }
 
-template <int MTC, int KSD, int V, int MAXT, int WPE>
-void go(const PassParams &a, int cus, int sweeps, hipStream_t s) {
-    const size_t lds = pass_lds(a.N, a.c, V);
-    if (a.c == 16 * MTC) start(k_ring_pass<MTC, KSD, V, true, MAXT, WPE>, a, cus, lds, sweeps, s);
-    else start(k_ring_pass<MTC, KSD, V, false, MAXT, WPE>, a, cus, lds, sweeps, s);
+PassKernel rounds_kernel(int N) {
+    return {k_rounds_pass, (size_t)N * pass_region(N, N + kGroup, 64) * sizeof(float), 4};
+}
+
+// Workgroups of N waves that one CU holds at a time: what the LDS and the
+// kernel's own registers (512 per lane and SIMD, in eights) allow.
+hipError_t per_cu(const PassKernel &k, int N, int *wgs) {
+    hipFuncAttributes at;
+    const hipError_t e = hipFuncGetAttributes(&at, reinterpret_cast<const void *>(k.fn));
+    if (e != hipSuccess) return e;
+    const int waves = std::min(8, 512 / std::max(8, (at.numRegs + 7) / 8 * 8));
+    *wgs = std::max(1, std::min((int)(kPassLds / k.lds), 4 * waves / N));
+    return hipSuccess;
+}
+
+void start(const PassKernel &k, const PassParams &a, int cus, int wgs_per_cu, hipStream_t s) {
+    const unsigned blocks = a.ragged ? (a.nblk + 7) / 8 * 8 : a.nblk;
+    const unsigned wgs = std::min<unsigned>(blocks, (unsigned)(cus * wgs_per_cu * k.sweeps));
+    hipLaunchKernelGGL(k.fn, dim3(wgs), dim3(64u * (unsigned)a.N), k.lds, s, a);
 }
 
 }  // namespace
@@ -752,33 +773,19 @@ int pass_positions(int N, int c) {
 
 int rounds_positions(int N) { return N <= 16 ? 64 : 0; }
 
-void launch_rounds_pass(const PassParams &a, int cus, hipStream_t s) {
-    start(k_rounds_pass, a, cus, (size_t)a.N * pass_region(a.N, a.N + kGroup, 64) * sizeof(float), 4, s);
+hipError_t prepare_passes(int N, int c, PassSize *out) {
+    hipError_t e = hipSuccess;
+    if (pass_positions(N, c)) e = per_cu(ring_kernel(N, c), N, &out->ring);
+    if (e == hipSuccess && rounds_positions(N)) e = per_cu(rounds_kernel(N), N, &out->rounds);
+    return e;
 }
 
-void prepare_passes(int N, int c) {
-    PassParams a{};
-    a.N = N;
-    a.c = c;
-    if (pass_positions(N, c)) launch_ring_pass(a, 0, nullptr);
-    else if (rounds_positions(N)) launch_rounds_pass(a, 0, nullptr);
+void launch_rounds_pass(const PassParams &a, int cus, const PassSize &size, hipStream_t s) {
+    start(rounds_kernel(a.N), a, cus, size.rounds, s);
 }
 
-void launch_ring_pass(const PassParams &a, int cus, hipStream_t s) {
-    if (a.N > 8) {
-        const size_t lds = pass_lds(a.N, a.c, 2);
-        if (a.c <= 16) go<1, 8, 2, 1024, 4>(a, cus, 16, s);
-        else if (a.c <= 32) go<2, 12, 2, 1024, 4>(a, cus, 8, s);
-        else if (a.c < 64) start(k_ring_pass_split<false>, a, cus, lds, 1, s);
-        else start(k_ring_pass_split<true>, a, cus, lds, 1, s);
-        return;
-    }
-    switch ((a.c + 15) / 16) {
-        case 1: go<1, 6, 4, 512, 4>(a, cus, 16, s); break;
-        case 2: go<2, 10, 4, 512, 4>(a, cus, 8, s); break;
-        case 3: go<3, 14, 2, 512, 2>(a, cus, 8, s); break;
-        default: go<4, 18, 2, 512, 2>(a, cus, 1, s); break;
-    }
+void launch_ring_pass(const PassParams &a, int cus, const PassSize &size, hipStream_t s) {
+    start(ring_kernel(a.N, a.c), a, cus, size.ring, s);
 }
 
 }  // namespace cerar

@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "cerar_internal.hpp"
+
 namespace cerar {
 
 // One independent all-reduce (a bucket): its buffers and geometry.
@@ -44,16 +46,16 @@ int pass_positions(int N, int c);
 // keep the fp32 coefficients of c <= 64 in their registers, sixteen those of
 // c <= 32.
 inline bool pass_is_fp32(int N, int c) { return c <= (N <= 8 ? 64 : 32); }
-// Looks up what the plan's launches need of their kernels (registers), so that
-// the first launch, which may be under stream capture, only launches.
-void prepare_passes(int N, int c);
+// The workgroups per CU of the plan's own kernels on the current device, looked
+// up once, so that a launch, which may be under stream capture, only launches.
+hipError_t prepare_passes(int N, int c, PassSize *out);
 // One launch; cus: compute units of the current device.
-void launch_ring_pass(const PassParams &a, int cus, hipStream_t s);
+void launch_ring_pass(const PassParams &a, int cus, const PassSize &size, hipStream_t s);
 
-// The rounds alone, for the other plans: reads the encoded chunks in `work`
+// The rounds alone, where the call does not go in one pass: reads the encoded chunks in `work`
 // (grads and out unused); 0 where N is too large for it.
 int rounds_positions(int N);
-void launch_rounds_pass(const PassParams &a, int cus, hipStream_t s);
+void launch_rounds_pass(const PassParams &a, int cus, const PassSize &size, hipStream_t s);
 
 // Encode and decode on split operands (plans with KC = split_chunks > 0): the
 // half-blocks (32 positions) per workgroup for this many in all, and the

@@ -5,6 +5,8 @@ workspace must hold the same bits.  Shapes sit at the edges of its tiles (16
 chunks, blocks of 64 or 32 positions), its rules (N = 8 | 9, c = 32 | 33 and
 64 | 65) and its rows (any row start, odd lengths, pads of several chunks)."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -203,3 +205,52 @@ def test_outputs_may_lie_on_the_gradients(N, c, how, s):
     C.ring_simulate_bucketed(plan, buckets, grads, bwork, bws, out)
     torch.cuda.synchronize()
     assert torch.equal(out, want)
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [(a, ctypes.c_uint32) for a in "xyz"]
+
+
+class _KernelNode(ctypes.Structure):                # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def _one_launch_grid(call):
+    """Workgroups of the single kernel that call(stream) enqueues, from a
+    stream capture that is never run."""
+    torch, _ = torch_dev()
+    hip = ctypes.CDLL(sorted(C._hip_runtimes())[0])
+    s = torch.cuda.Stream()
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t(1)
+    nodes, node = (ctypes.c_void_p * 1)(), _KernelNode()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 1) == 0     # thread-local mode
+    try:
+        call(s)
+    finally:
+        assert hip.hipStreamEndCapture(ctypes.c_void_p(s.cuda_stream), ctypes.byref(graph)) == 0
+    try:
+        assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0 and n.value == 1
+        assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(nodes[0]), ctypes.byref(node)) == 0
+    finally:
+        hip.hipGraphDestroy(graph)
+    return node.grid.x
+
+
+def test_launch_size_is_the_plans_own():
+    """Every kernel's launch is sized by its own registers, whichever plan came
+    first in the process: at N = 8 a CU holds three workgroups of the c = 16
+    kernel (76 registers, 47 KB of LDS; sixteen sweeps of those) and one of the
+    c = 64 kernel (229 registers)."""
+    torch, dev = torch_dev()
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    grids = {}
+    for c in (16, 64, 16):
+        d = c * 64 * 14000
+        plan = C.Plan.explicit(*orthogonal_plan(8, c, seed=c))
+        plan.prepare_device()
+        grads = torch.zeros((8, d), dtype=torch.float32, device=dev)
+        out = torch.empty_like(grads)
+        grids[c] = _one_launch_grid(lambda s: C.ring_simulate_fused(plan, d, grads, out, stream=s))
+    assert grids == {16: 3 * 16 * cus, 64: cus}
