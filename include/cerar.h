@@ -33,9 +33,12 @@
  *    that).
  *  - Data on the device (gradients, encoded chunks, messages, outputs) is
  *    IEEE fp32.  The encode and decode contractions accumulate in fp32; with
- *    c > 64, or N > 8 and c > 32, their fp32 operands are split exactly into three bf16 terms and six of
- *    the nine term products are summed on the bf16 matrix cores
- *    (within two units of fp32 rounding per product).  A round forms
+ *    c > 64, or N > 8 and c > 32, their fp32 operands are split exactly into
+ *    three bf16 terms and six of the nine term products are summed on the bf16
+ *    matrix cores (within two units of fp32 rounding per product).  Blocks of
+ *    32 positions with an entry that the terms do not hold (nonzero and below
+ *    2^-110, or 2^127 and above), and plans with such a coefficient, are
+ *    contracted in fp32.  A round forms
  *    recv - delta_j + delta_{k+1} in fp64 and rounds the message to fp32
  *    once.  The error norms accumulate in fp64.  Plan construction is host
  *    fp64.

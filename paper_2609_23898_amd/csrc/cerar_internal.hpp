@@ -96,6 +96,7 @@ struct cerar_plan {
     std::vector<float> enc_frag, dec_frag;
     int KC = 0;                      // 32-step chunks of the split contraction, 0 where it is not used
     std::vector<uint16_t> enc_split, dec_split;   // bf16 bits, see split_tile_encode / split_tile_decode
+    bool split_wide = false;         // some coefficient is not the sum of its three terms
     mutable std::mutex dev_mu;
     mutable std::map<int, cerar::DeviceCopy> dev;   // per HIP device ordinal
 };

@@ -379,8 +379,8 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WPE))) voi
 // they come from the L2 for every block, split into bf16 terms (51 KB per
 // worker at c = 64), and the contractions run on split operands, at 3/8 of the
 // fp32 MFMA time.  Blocks of 32 positions.  N = 16, c = 60, odd d = 20M: 2.06
-// -> 1.43 ms against encode, rounds and decode in turn; N = 12, c = 48, d = 40M:
-// 2.88 -> 2.40 ms.  Not for N <= 8, where k_ring_pass keeps the coefficients
+// -> 1.42 ms against encode, rounds and decode in turn; N = 12, c = 48, d = 40M:
+// 2.88 -> 2.27 ms.  Not for N <= 8, where k_ring_pass keeps the coefficients
 // (N = 8, c = 64, d = 354M: 10.4 ms there, 11.8-13.4 ms here).
 __device__ inline Split3<v8bf> global_a32(const __bf16 *tile, int kc, uint32_t lane) {
     typedef __attribute__((address_space(1))) const v8bf G;
@@ -393,11 +393,30 @@ __device__ inline Split3<v4bf> global_a16(const __bf16 *tile, int KC, uint32_t l
     return {*(G *)b, *(G *)(b + 64 * 4), *(G *)(b + 2 * 64 * 4)};
 }
 
+// The encode of a block that the split does not hold (split.hpp): its gradient
+// rows are read again, and the chunks go to LDS.
+CERAR_RARE void encode_rare(const float *src, size_t p, size_t d, size_t e0, int c, const float *frag, int KS, float *mine,
+                            int lane) {
+    const size_t e = e0 + 2 * (lane & 15);
+#pragma unroll 1
+    for (int mt = 0; 16 * mt < c; ++mt) {
+        v4f acc[2];
+        tile_f32<2, 1>(acc, frag + (size_t)mt * KS * 64, KS, lane, [&](int kc, int s, int t) {
+            const int l = 32 * kc + 8 * (lane >> 4) + s;
+            return l < c && (size_t)l * p + e + t < d ? gload1(src + (size_t)l * p + e + t) : 0.f;
+        });
+        const int row0 = 16 * mt + 4 * (lane >> 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (row0 + r < c) *reinterpret_cast<v2f *>(mine + (row0 + r) * 32 + 2 * (lane & 15)) = v2f{acc[0][r], acc[1][r]};
+    }
+}
+
 template <bool EXC>
 __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
     constexpr int KC = 2, MTC = 4, P = 32, TE = split_tile_encode(KC), TD = split_tile_decode(KC);
     extern __shared__ __align__(16) float sm[];
-    const int N = a.N, c = EXC ? 64 : a.c, K = c + N - 1;
+    const int N = a.N, c = EXC ? 64 : a.c, K = c + N - 1, MT = (c + 15) / 16;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, g4 = lane >> 4;
     const int WS = pass_region(N, K, P);
@@ -419,7 +438,7 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
                 if (EXC || 32 * kc + 32 <= (int)opaque_s(c)) {
                     x[kc][s] = gload<2>(row, lane_in);
                 } else {
-                    x[kc][s] = v2f{0.f, 0.f};
+                    x[kc][s] = kNoRow;
                     if (32 * kc + s + 8 * (int)opaque((uint32_t)g4) < c) x[kc][s] = gload<2>(row, lane_in);
                 }
                 row = step(row, s < 7 ? p : 25 * p);
@@ -431,7 +450,7 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
                 const int kc = u / 8, s = u % 8;
                 const int l = 32 * kc + 8 * gq + s;
                 const size_t flat = (size_t)l * p + e0 + cq;
-                x[kc][s] = v2f{0.f, 0.f};
+                x[kc][s] = l < c ? v2f{0.f, 0.f} : kNoRow;
                 if (l < c && flat + 1 < d) x[kc][s] = gload<2>(src + flat, 0);
                 else if (l < c && flat < d) x[kc][s][0] = gload1(src + flat);
                 __builtin_amdgcn_sched_barrier(0);
@@ -439,7 +458,22 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
         }
     };
     // delta_w on this block, rows j of P positions into LDS
-    auto encode = [&]() __attribute__((always_inline)) {
+    auto encode = [&](const PassInst &I, size_t e0) __attribute__((always_inline)) {
+        SplitRange range;
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) range.add(x[kc][s]);
+        const bool rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+                              for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                                  for (int s = 0; s < 8; ++s) f(x[kc][s]);
+                          });
+        if (rare) {
+            encode_rare(I.grads + (size_t)w * a.ld_g, I.p, I.d, e0, c, a.efrag + (size_t)w * MT * a.KSe * 64, a.KSe, mine, lane);
+            return;
+        }
         Split3<v8bf> b[KC][2];
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc)
@@ -475,7 +509,7 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
     if (g >= sw.end) return;
     locate(g);
     load(a.in[q], (size_t)(g - a.in[q].blk0) * P);
-    encode();
+    encode(a.in[q], (size_t)(g - a.in[q].blk0) * P);
     for (;;) {
         const PassInst &I = a.in[q];
         const size_t p = I.p, d = I.d, ps = I.pool_stride;
@@ -498,16 +532,20 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
         v4f dacc[MTC][2];
 #pragma unroll
         for (int mt = 0; mt < MTC; ++mt) dacc[mt][0] = dacc[mt][1] = v4f{0.f, 0.f, 0.f, 0.f};
-        auto column = [&](int kk) {                       // Y column kk at this lane's positions; none past L
+        auto column = [&](int kk) {                       // Y column kk at this lane's positions
             const float *row = mine + (kk - (N - 1) + (kk < N - 1 ? K : 0)) * P + 2 * col;
-            return kk < K ? *reinterpret_cast<const v2f *>(row) : v2f{0.f, 0.f};
+            return kk < K ? *reinterpret_cast<const v2f *>(row) : kNoRow;
         };
+        SplitRange range;
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc) {
             const int k0 = 32 * kc + 8 * (int)opaque((uint32_t)g4);
             v2f y[8];
 #pragma unroll
-            for (int s = 0; s < 8; ++s) y[s] = column(min(k0 + s, K));
+            for (int s = 0; s < 8; ++s) {
+                y[s] = column(min(k0 + s, K));
+                range.add(y[s]);
+            }
             const Split3<v8bf> b0 = split8([&](int s) { return y[s][0]; }), b1 = split8([&](int s) { return y[s][1]; });
 #pragma unroll
             for (int mt = 0; mt < MTC; ++mt) {
@@ -521,7 +559,10 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
             const int k0 = 32 * KC + 4 * (int)opaque((uint32_t)g4);
             v2f y[4];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) y[s] = column(min(k0 + s, K));
+            for (int s = 0; s < 4; ++s) {
+                y[s] = column(min(k0 + s, K));
+                range.add(y[s]);
+            }
             const Split3<v4bf> b0 = split4([&](int s) { return y[s][0]; }), b1 = split4([&](int s) { return y[s][1]; });
 #pragma unroll
             for (int mt = 0; mt < MTC; ++mt) {
@@ -530,6 +571,13 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
                 dacc[mt][1] = mma_split16(A, b1, dacc[mt][1]);
             }
         }
+        const bool rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+#pragma unroll 1
+                              for (int kk = (int)opaque((uint32_t)g4); kk < K; kk += 4) f(column(kk));
+                          });
+        if (rare)
+            tiles_f32(dacc, MT, a.dfrag + (size_t)w * MT * a.KSd * 64, a.KSd, (int)opaque((uint32_t)lane),
+                      [&](int k, int t) { return column(min(k, K))[t]; });
         // the observations to their slots (see k_ring_pass), four rows at a time
         if (state) {
             float *own = I.work + (size_t)w * a.ld_w + (size_t)(c - 1) * p + e0;
@@ -585,7 +633,7 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
                 }
         }
         if (!more) break;
-        encode();                                         // reads and writes this wave's own rows only
+        encode(a.in[q], (size_t)(g - a.in[q].blk0) * P);  // reads and writes this wave's own rows only
     }
 }
 

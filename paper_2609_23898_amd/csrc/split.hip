@@ -6,9 +6,9 @@
 // sweeps a run of half-blocks (32 positions), one per wave at a time; rows
 // may start at any float, c need be no multiple of 16, and the blocks that
 // reach past the gradient's end take masked accesses in the same launch.
-// Measured: N = 16, c = 128, d = 1e8 encode 2.83 ms, decode 2.95 ms (4.5 TB/s; a
+// Measured: N = 16, c = 128, d = 1e8 encode 2.74 ms, decode 2.98 ms (4.6 TB/s; a
 // tail launch of 0.25 ms each is gone); N = 3, c = 100, d = 1e8 the whole ring
-// 3.41 -> 1.78 ms against masked fp32 kernels.
+// 3.41 -> 1.73 ms against masked fp32 kernels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,6 +58,24 @@ __device__ inline void tile_pair(v4f (&acc)[2][2], const Split3<v8bf> (&b)[KC][2
         for (int q = 0; q < 2; ++q) {
             acc[0][q] = mma_split16(s0, bt[q], acc[0][q]);
             acc[1][q] = mma_split16(s1, bt[q], acc[1][q]);
+        }
+    }
+}
+
+// The decode of a half-block that the split does not hold (split.hpp).
+CERAR_RARE void decode_rare(const float **srow, size_t p, size_t d, size_t e0, int c, int K, const float *frag, int KS,
+                            float *out, int lane) {
+    const size_t e = e0 + 2 * (lane & 15);
+#pragma unroll 1
+    for (int mt = 0; 16 * mt < c; ++mt) {
+        v4f acc[1][2];
+        tiles_f32(acc, 1, frag + (size_t)mt * KS * 64, KS, lane, [&](int k, int t) { return k < K ? gload1(srow[k] + e + t) : 0.f; });
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = 16 * mt + 4 * (lane >> 4) + r;
+            const size_t flat = (size_t)j * p + e;
+            if (j < c && flat < d) gstore1(out + flat, acc[0][0][r]);
+            if (j < c && flat + 1 < d) gstore1(out + flat + 1, acc[0][1][r]);
         }
     }
 }
@@ -118,7 +136,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
                     if (EXC || 32 * kc + 32 <= (int)opaque_s(c)) {
                         x[kc][s] = gload<2>(row, lane_in);
                     } else {
-                        x[kc][s] = v2f{0.f, 0.f};
+                        x[kc][s] = kNoRow;
                         if (32 * kc + s + 8 * (int)opaque((uint32_t)g) < c) x[kc][s] = gload<2>(row, lane_in);
                     }
                     row = step(row, s < 7 ? ps : 25 * ps);
@@ -130,7 +148,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
                     const int kc = u / 8, s = u % 8;
                     const int l = 32 * kc + 8 * gq + s;
                     const size_t flat = (size_t)l * ps + e0 + cq;
-                    x[kc][s] = v2f{0.f, 0.f};
+                    x[kc][s] = l < c ? v2f{0.f, 0.f} : kNoRow;
                     if (l < c && flat + 1 < d) x[kc][s] = gload<2>(src + flat, 0);
                     else if (l < c && flat < d) x[kc][s][0] = gload1(src + flat);
                     __builtin_amdgcn_sched_barrier(0);
@@ -139,11 +157,37 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
     };
     Split3<v8bf> b[KC][2];
     const Split3<v4bf> none[2] = {};
+    bool rare;                                            // the half-block was contracted on fp32 MFMAs
     auto split = [&]() __attribute__((always_inline)) {
+        SplitRange range;
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
+        for (int kc = 0; kc < KC; ++kc) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) range.add(x[kc][s]);
 #pragma unroll
             for (int q = 0; q < 2; ++q) b[kc][q] = split8([&](int s) { return x[kc][s][q]; });
+        }
+        rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+                   for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                       for (int s = 0; s < 8; ++s) f(x[kc][s]);
+               });
+        if (!rare) return;
+        const size_t ps = opaque_s(p), e = hb * 32 + 2 * opaque((uint32_t)col);
+        const int MT = (c + 15) / 16, gq = (int)opaque((uint32_t)g);
+#pragma unroll 1
+        for (int mt = 0; mt < MT; ++mt) {                 // all rows are in x: in place, a tile's stores overwrite none it needs
+            v4f acc[2];
+            tile_f32<KC, 8 * KC>(acc, a.efrag + (size_t)(w * MT + mt) * a.KSe * 64, a.KSe, lane,
+                                 [&](int kc, int s, int t) { return x[kc][s][t]; });
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = 16 * mt + 4 * gq + r;
+                if (j < c) gstore<2>(dst + (size_t)j * ps + e, 0, v2f{acc[0][r], acc[1][r]});
+                if (j == 0) gstore<2>(x1 + e, 0, v2f{acc[0][r], acc[1][r]});
+            }
+        }
     };
     load(hb);
     split();
@@ -154,25 +198,29 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
         const uint32_t lane_out = opaque((uint32_t)(((size_t)(g * 4) * p + 2 * (size_t)col) * sizeof(float)));
         float *row = dst + e0;
         const bool narrow = p < kNarrow;
+        if (!rare) {
 #pragma unroll
-        for (int mt = 0; mt < 2 * KC; mt += 2) {
-            if (EXC || 16 * mt < (int)opaque_s(c)) {
-            v4f acc[2][2];
-            tile_pair<KC, false>(acc, b, none, sa + mt * TE, sa + (mt + 1) * TE, lane);
-            const int lrow = EXC ? 0 : 16 * mt + 4 * (int)opaque((uint32_t)g);
+            for (int mt = 0; mt < 2 * KC; mt += 2) {
+                if (EXC || 16 * mt < (int)opaque_s(c)) {
+                    v4f acc[2][2];
+                    tile_pair<KC, false>(acc, b, none, sa + mt * TE, sa + (mt + 1) * TE, lane);
+                    const int lrow = EXC ? 0 : 16 * mt + 4 * (int)opaque((uint32_t)g);
 #pragma unroll
-            for (int m = 0; m < 2; ++m)
+                    for (int m = 0; m < 2; ++m)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const v2f v = {acc[m][0][r], acc[m][1][r]};
-                    if (EXC || lrow + 16 * m + r < c) {
-                        if (narrow) gstore<2>(row, lane_out, v);
-                        else gstore<2>(row + (size_t)(4 * (int)opaque((uint32_t)g)) * p + 2 * col, 0, v);
-                        if (mt + m == 0 && r == 0 && g == 0) gstore<2>(x1 + e0, (uint32_t)(2 * col * sizeof(float)), v);
-                    }
-                    row = step(row, r < 3 ? p : 13 * p);
+                        for (int r = 0; r < 4; ++r) {
+                            const v2f v = {acc[m][0][r], acc[m][1][r]};
+                            if (EXC || lrow + 16 * m + r < c) {
+                                if (narrow) gstore<2>(row, lane_out, v);
+                                else gstore<2>(row + (size_t)(4 * (int)opaque((uint32_t)g)) * p + 2 * col, 0, v);
+                                if (mt + m == 0 && r == 0 && g == 0) gstore<2>(x1 + e0, (uint32_t)(2 * col * sizeof(float)), v);
+                            }
+                            row = step(row, r < 3 ? p : 13 * p);
+                        }
                 }
             }
+        } else {
+            wait_all();
         }
         if (next >= R.end) break;
         hb = next;
@@ -228,13 +276,28 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
     };
     Split3<v8bf> b[KC][2];
     Split3<v4bf> bt[2];
+    bool rare;                                            // the half-block in b goes on fp32 MFMAs
     auto split = [&]() __attribute__((always_inline)) {
+        SplitRange range;
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
+        for (int kc = 0; kc < KC; ++kc) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) range.add(x[kc][s]);
 #pragma unroll
             for (int q = 0; q < 2; ++q) b[kc][q] = split8([&](int s) { return x[kc][s][q]; });
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) range.add(xt[s]);
 #pragma unroll
         for (int q = 0; q < 2; ++q) bt[q] = split4([&](int s) { return xt[s][q]; });
+        rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+                   for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                       for (int s = 0; s < 8; ++s) f(x[kc][s]);
+#pragma unroll
+                   for (int s = 0; s < 4; ++s) f(xt[s]);
+               });
     };
     load(hb);
     split();
@@ -244,36 +307,41 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
         const size_t e0 = hb * 32;
         const bool fast = p < kNarrow && (size_t)(c - 1) * p + e0 + 32 <= d;
         const uint32_t lane_out = opaque((uint32_t)(((size_t)(g * 4) * p + 2 * (size_t)col) * sizeof(float)));
+        if (rare) {
+            decode_rare(srow, p, d, e0, c, K, a.dfrag + (size_t)w * ((c + 15) / 16) * a.KSd * 64, a.KSd, out, lane);
+            wait_all();
+        } else {
 #pragma unroll
-        for (int mt = 0; mt < 2 * KC; mt += 2) {
-            if (EXC || 16 * mt < (int)opaque_s(c)) {
-                v4f acc[2][2];
-                tile_pair<KC, true>(acc, b, bt, sa + mt * TD, sa + (mt + 1) * TD, lane);
-                const size_t ps = opaque_s(p);
-                float *row = out + e0 + (size_t)(16 * mt) * ps;
-                if (fast) {
-                    const int lrow = EXC ? 0 : 16 * mt + 4 * (int)opaque((uint32_t)g);
+            for (int mt = 0; mt < 2 * KC; mt += 2) {
+                if (EXC || 16 * mt < (int)opaque_s(c)) {
+                    v4f acc[2][2];
+                    tile_pair<KC, true>(acc, b, bt, sa + mt * TD, sa + (mt + 1) * TD, lane);
+                    const size_t ps = opaque_s(p);
+                    float *row = out + e0 + (size_t)(16 * mt) * ps;
+                    if (fast) {
+                        const int lrow = EXC ? 0 : 16 * mt + 4 * (int)opaque((uint32_t)g);
 #pragma unroll
-                    for (int m = 0; m < 2; ++m)
+                        for (int m = 0; m < 2; ++m)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (EXC || lrow + 16 * m + r < c) {
-                                const v2f v = {acc[m][0][r], acc[m][1][r]};
-                                if (a.ragged) gstore_cached<2>(row + (size_t)(16 * m + r) * ps, lane_out, v);
-                                else gstore<2>(row + (size_t)(16 * m + r) * ps, lane_out, v);
+                            for (int r = 0; r < 4; ++r)
+                                if (EXC || lrow + 16 * m + r < c) {
+                                    const v2f v = {acc[m][0][r], acc[m][1][r]};
+                                    if (a.ragged) gstore_cached<2>(row + (size_t)(16 * m + r) * ps, lane_out, v);
+                                    else gstore<2>(row + (size_t)(16 * m + r) * ps, lane_out, v);
+                                }
+                    } else {
+                        const int lrow = 16 * mt + 4 * (int)opaque((uint32_t)g);
+#pragma unroll
+                        for (int m = 0; m < 2; ++m)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const int j = lrow + 16 * m + r;
+                                const size_t flat = (size_t)j * ps + e0 + 2 * (int)opaque((uint32_t)col);
+                                if (j < c && flat + 1 < d) gstore<2>(out + flat, 0, v2f{acc[m][0][r], acc[m][1][r]});
+                                else if (j < c && flat < d) gstore1(out + flat, acc[m][0][r]);
+                                __builtin_amdgcn_sched_barrier(0);
                             }
-                } else {
-                    const int lrow = 16 * mt + 4 * (int)opaque((uint32_t)g);
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int j = lrow + 16 * m + r;
-                            const size_t flat = (size_t)j * ps + e0 + 2 * (int)opaque((uint32_t)col);
-                            if (j < c && flat + 1 < d) gstore<2>(out + flat, 0, v2f{acc[m][0][r], acc[m][1][r]});
-                            else if (j < c && flat < d) gstore1(out + flat, acc[m][0][r]);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
+                    }
                 }
             }
         }

@@ -13,14 +13,24 @@
 // one takes for 4, so the six products cost 3/8 of the fp32 MFMA time, and
 // other waves' vector instructions run beside it, which the fp32 MFMA excludes
 // (measured: 4 MFMAs and 32 FMAs of two waves take 130 + 180 -> 313 cycles with
-// fp32, 80 + 175 -> 210 with bf16).  Values must lie in bf16's range (|x| <
-// 3.39e38); terms below fp32's normal range lose their low bits.
+// fp32, 80 + 175 -> 210 with bf16).
+//
+// The terms hold an entry exactly from 2^-110 (below that the last one falls
+// under bf16's smallest subnormal, 2^-133) up to 2^127 (beyond, the first could
+// round to infinity).  A half-block of 32 positions with another entry in it
+// (SplitRange: nonzero and smaller, larger or infinite) is contracted on fp32
+// MFMAs instead (tiles_f32), and so is every half-block of a plan that has such a
+// coefficient: no input loses digits to the split.  The test costs one vector
+// instruction per entry beside five and a half of the split (encode of N = 16,
+// c = 128, d = 60M 1.740 -> 1.751 ms, N = 20, c = 40, d = 20M 740 -> 774 us); zeros
+// take a second look.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include "cerar_internal.hpp"
 #include "device_util.hpp"
+#include "rows.hpp"
 
 namespace cerar {
 namespace {
@@ -36,6 +46,10 @@ typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
 template <class V>
 struct Split3 { V h, m, l; };
+
+// What stands in for a reduction row that the plan does not have; its
+// coefficients are zero.  No zero, which SplitRange would look at twice.
+constexpr v2f kNoRow = {1.f, 1.f};
 
 // acc += A B for split A and B with the six kept products, the small ones first.
 __device__ inline v4f mma_split32(const Split3<v8bf> &a, const Split3<v8bf> &b, v4f acc) {
@@ -107,6 +121,76 @@ __device__ inline Split3<v4bf> split4(X x) {
     }
     return {__builtin_bit_cast(v4bf, h), __builtin_bit_cast(v4bf, m), __builtin_bit_cast(v4bf, l)};
 }
+
+// Whether the wave has met an entry that its three terms do not hold exactly.
+// (A NaN makes NaNs of its position either way.)
+struct SplitRange {
+    float lo = 1.f, hi = 1.f;                             // least and largest magnitude
+    __device__ void add(v2f x) {                          // as asm, or the compiler quiets each operand first
+        asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(lo) : "v"(x[0]), "v"(x[1]));
+        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(hi) : "v"(x[0]), "v"(x[1]));
+    }
+    // each(f) calls f on every entry again, to tell zeros from small ones
+    template <class Each>
+    __device__ bool left(Each each) const {
+        if (__builtin_amdgcn_ballot_w64(lo < 0x1p-110f || hi >= 0x1p127f) == 0) return false;
+        if (__builtin_amdgcn_ballot_w64(hi >= 0x1p127f) != 0) return true;
+        uint32_t least = 0xffffffffu;                     // of 2 bits - 1: a zero wraps to the largest
+        each([&](v2f x) { least = min(least, min((__float_as_uint(x[0]) << 1) - 1, (__float_as_uint(x[1]) << 1) - 1)); });
+        return __builtin_amdgcn_ballot_w64(least < 2u * (17u << 23) - 1) != 0;
+    }
+};
+
+// The contraction of a rare half-block on fp32 MFMAs: the first `tiles` of TILES
+// tiles at W positions a lane.  frag has their fp32 coefficients, KS K-steps of
+// 64 lanes a tile; row(k, t) gives reduction row k at the lane's position t.
+// Where it costs the usual path registers it is called out of line (the one-pass
+// encode: N = 9, c = 64, d = 40M 1.80 ms so, 1.90 inline); the step encode is
+// faster with its own inline (N = 12, c = 48, d = 40M: 844 against 890 us).
+#define CERAR_RARE __device__ __attribute__((noinline))
+template <int TILES, int W, class Row>
+__device__ inline void tiles_f32(v4f (&acc)[TILES][W], int tiles, const float *frag, int KS, int lane, Row row) {
+#pragma unroll
+    for (int mt = 0; mt < TILES; ++mt)
+#pragma unroll
+        for (int t = 0; t < W; ++t) acc[mt][t] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int ks = 0; ks < KS; ++ks) {
+        float y[W];
+#pragma unroll
+        for (int t = 0; t < W; ++t) y[t] = row(4 * ks + (lane >> 4), t);
+#pragma unroll
+        for (int mt = 0; mt < TILES; ++mt)
+            if (mt < tiles) {
+                const float coef = gload1(frag + (size_t)(mt * KS + ks) * 64 + lane);
+#pragma unroll
+                for (int t = 0; t < W; ++t) acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(coef, y[t], acc[mt][t], 0, 0, 0);
+            }
+    }
+}
+
+// The same for the encode, one tile with the K-steps in the order of its
+// registers: x(kc, s, t) gives row 32 kc + 8 g + s of lane group g.  UNROLL: all
+// 8 KC of them where x is in registers, else 1.
+template <int KC, int UNROLL, class X>
+__device__ inline void tile_f32(v4f (&acc)[2], const float *frag, int KS, int lane0, X x) {
+    const uint32_t lane = opaque((uint32_t)lane0), ks0 = 2 * (lane >> 4);
+    const float *a = frag + ks0 * 64 + (lane & 15);
+    acc[0] = acc[1] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll(UNROLL)
+    for (int u = 0; u < 8 * KC; ++u) {
+        const int kc = u / 8, s = u % 8, ks = 8 * kc + s / 4;
+        const float coef = (int)ks0 + ks < KS ? gload1(a + ks * 64 + s % 4 * 16) : 0.f;
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(coef, x(kc, s, 0), acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(coef, x(kc, s, 1), acc[1], 0, 0, 0);
+    }
+}
+
+// The end of a rare half-block's path, where loads for the next one are under
+// way: waits for all of them.  Where it meets the usual path the compiler would
+// otherwise take the fewer stores issued here after those loads for both, and
+// wait for the usual path's stores as well.
+__device__ inline void wait_all() { __builtin_amdgcn_s_waitcnt(0); }
 
 }  // namespace
 }  // namespace cerar

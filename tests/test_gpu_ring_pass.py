@@ -122,13 +122,13 @@ def test_buckets_equal_calls_of_their_own(N, c, lens):
         at += cp
 
 
-@pytest.mark.parametrize("seed", [0, 1])
+@pytest.mark.parametrize("seed", range(5))
 def test_infinities_and_nan_stay_in_their_columns(seed):
     """A position whose gradients hold an infinity or NaN gives the step calls'
     results, and no other position sees it (zero padding of the tiles and the
     rows past K meets no such value)."""
     torch, _ = torch_dev()
-    N, c = (8, 20) if seed == 0 else (3, 33)
+    N, c = [(8, 20), (3, 33), (12, 48), (16, 64), (8, 80)][seed]
     d = c * 192 - 11
     U, R = orthogonal_plan(N, c, seed=5)
     plan = C.Plan.explicit(U, R)
@@ -144,6 +144,110 @@ def test_infinities_and_nan_stay_in_their_columns(seed):
     np.testing.assert_array_equal(a, b)
     clean = ~np.isin(np.arange(d) % p, bad)
     assert np.all(np.isfinite(a[:, clean]))
+
+
+# Entries that three bf16 terms do not hold, alone and among others: below
+# 2^-110 (subnormals of bf16 and of fp32 too), at the top of the range, and
+# zeros, which they do hold.
+MAGNITUDES = {"usual": (-20, 1), "small": (-148, -105), "large": (127, 128), "mixed": (-140, 128), "sparse": (-20, 1)}
+
+
+def _entries(kind, shape, seed):
+    rng = np.random.default_rng(seed)
+    lo, hi = MAGNITUDES[kind]
+    x = rng.choice([-1.0, 1.0], size=shape) * rng.uniform(1, 2, size=shape) * 2.0 ** rng.integers(lo, hi, size=shape)
+    if kind == "sparse":
+        x[rng.random(shape) < 0.9] = 0.0
+    return np.clip(x, -np.finfo(np.float32).max, np.finfo(np.float32).max).astype(np.float32)
+
+
+SPLIT_PLANS = [(9, 33), (12, 48), (16, 64), (20, 40), (17, 63), (3, 65), (8, 96), (5, 97), (16, 128)]
+
+
+@pytest.mark.parametrize("kind", MAGNITUDES)
+@pytest.mark.parametrize("N,c", SPLIT_PLANS)
+def test_split_contractions_keep_every_fp32_entry(N, c, kind):
+    """Encoders that permute the chunks and decoders that pick observations:
+    every output is one input, whatever its magnitude, bit for bit."""
+    torch, _ = torch_dev()
+    rng = np.random.default_rng(N + c)
+    K, d = c + N - 1, c * 96 - 37
+    perm = [rng.permutation(c) for _ in range(N)]
+    pick = [rng.integers(0, K, size=c) for _ in range(N)]
+    U, R = np.zeros((N, c, c)), np.zeros((N, K, c))
+    for i in range(N):
+        U[i, perm[i], np.arange(c)] = 1.0
+        R[i, pick[i], np.arange(c)] = 1.0
+    plan = C.Plan.explicit(U, R)
+    p, stride = plan.chunk_len(d)
+    g = _entries(kind, (N, d), seed=c)
+    grads = to_device(g)
+    work, ws, out = buffers(plan, d)
+    for k in range(plan.L + 1):
+        C.encode_round(plan, k, d, grads, work, ws)
+        if k == 0:
+            chunks = work.cpu().numpy().reshape(N, c, p)
+    G = np.zeros((N, c * p), np.float32)
+    G[:, :d] = g
+    for i in range(N):
+        np.testing.assert_array_equal(chunks[i], G[i].reshape(c, p)[perm[i]])
+    y = _entries(kind, (N * c + N * N, p), seed=c + 1)
+    work.copy_(torch.from_numpy(y[:N * c].reshape(N, c * p)))
+    ws.view(torch.float32).view(N * N, stride)[:, :p].copy_(torch.from_numpy(y[N * c:]))
+    C.decode(plan, d, work, ws, out)
+    slots = plan.slot_map(plan.L)
+    cols = np.concatenate([slots[:, c:c + N - 1], slots[:, :c]], axis=1)       # Y_i = [B | D]
+    for i in range(N):
+        np.testing.assert_array_equal(out[i].cpu().numpy(), y[cols[i][pick[i]]].reshape(-1)[:d])
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -122, 2.0 ** 127])
+@pytest.mark.parametrize("N,c", [(12, 48), (3, 65), (16, 128)])
+def test_split_contractions_keep_every_fp32_coefficient(N, c, scale):
+    """Coefficients beyond the split's range: one product per output, so within
+    one rounding of it."""
+    rng = np.random.default_rng(c)
+    d = c * 64
+    coef = (rng.uniform(1, 1.99, size=(N, c)) * scale).astype(np.float32).astype(np.float64)
+    U = np.stack([np.diag(coef[i]) for i in range(N)])
+    plan = C.Plan.explicit(U, np.zeros((N, c + N - 1, c)))
+    g = (_entries("usual", (N, d), seed=c) * (1.0 / scale)).astype(np.float32)
+    work, ws, _ = buffers(plan, d)
+    C.encode_round(plan, 0, d, to_device(g), work, ws)
+    want = np.repeat(coef, d // c, axis=1) * g.astype(np.float64)
+    np.testing.assert_allclose(work.double().cpu().numpy(), want, rtol=2.0 ** -24, atol=0)
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("N,c", [(9, 33), (12, 48), (16, 64), (8, 96), (16, 128)])
+def test_one_pass_and_steps_agree_on_entries_beyond_the_split(N, c, in_place):
+    """Half-blocks of every magnitude beside ordinary ones: the whole ring and
+    the step calls take the same arithmetic for each."""
+    torch, _ = torch_dev()
+    U, R = orthogonal_plan(N, c, seed=c)
+    plan = C.Plan.explicit(U, R)
+    d = c * 32 * 37 - 5
+    p, _ = plan.chunk_len(d)
+    g = np.zeros((N, c * p), np.float32)
+    g[:, :d] = _entries("usual", (N, d), seed=c)
+    rng = np.random.default_rng(c)
+    for kind in ("small", "large", "mixed", "sparse"):
+        for h in rng.choice(p // 32, size=4, replace=False):
+            i, l = rng.integers(N), rng.integers(c - 2)
+            at = l * p + 32 * h
+            g[i, at:at + 32] = _entries(kind, 32, seed=int(h))
+    g[0, 5], g[1, p + 70], g[N - 1, 2 * p + 200] = np.inf, -np.inf, np.nan
+    res = []
+    for call in (lambda *b: C.ring_simulate(plan, d, *b), lambda *b: _steps(plan, d, *b)):
+        work, ws, out = buffers(plan, d)
+        grads = to_device(g)
+        if in_place:
+            work = grads
+        call(grads, work, ws, out)
+        torch.cuda.synchronize()
+        res.append([t.cpu().numpy() for t in (out, *_state(plan, d, work, ws))])
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(a, b)
 
 
 @pytest.mark.parametrize("N,d,off", [(1, 1, 0), (2, 3, 1), (8, 1023, 0), (8, 4 * 256 * 3 + 2, 3), (9, 4097, 2),

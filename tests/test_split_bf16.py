@@ -1,13 +1,14 @@
-"""The arithmetic of the c = 128 encode and decode kernels, which run their
-fp32 contraction on bf16 MFMAs: each fp32 operand x is split into three
-bf16 terms, x = h + m + l, each the rounding to nearest even of what the
-earlier terms leave, and six of the nine term products are summed.  Here the
-split is emulated bit by bit on the host and its claims are checked: the
-split is exact, the terms shrink by 2^-8 each, every kept product is exact
-in fp32, and the dropped products of a dot product sum to less than
-2^-23 sum |a_k b_k| (two units of fp32 rounding).  The kernels themselves are
-checked against the oracle on the GPU (dot-product bounds of the encode and
-decode at c = 128)."""
+"""The arithmetic of the split-operand encode and decode (plans with c > 64, and
+with c > 32 where N > 8), which run their fp32 contraction on bf16 MFMAs: each
+fp32 operand x is split into three bf16 terms, x = h + m + l, each the
+rounding to nearest even of what the earlier terms leave, and six of the
+nine term products are summed.  Here the split is emulated bit by bit on the
+host and its claims are checked: the split is exact between 2^-110 and 2^127
+and loses digits below (there the kernels contract on fp32 MFMAs), the terms
+shrink by 2^-8 each, every kept product is exact in fp32, and the dropped
+products of a dot product sum to less than 2^-23 sum |a_k b_k| (two units of
+fp32 rounding).  The kernels themselves are checked against the oracle on the
+GPU (dot-product bounds, and entries of every magnitude)."""
 
 import numpy as np
 
@@ -65,6 +66,22 @@ def test_split_is_exact_and_each_term_is_a_bf16():
     ax = np.abs(x.astype(np.float64))
     assert np.all(np.abs(m) <= 2.0 ** -8 * (1 + 2.0 ** -8) * ax)
     assert np.all(np.abs(l) <= 2.0 ** -16 * ax)
+
+
+def test_split_is_exact_over_the_range_that_the_kernels_take():
+    """SplitRange's bounds: exact from 2^-110 up to 2^127; just below 2^-110
+    the last term falls under bf16's smallest subnormal, and the largest fp32
+    values round to infinity in the first."""
+    rng = np.random.default_rng(4)
+    mant = np.concatenate([rng.integers(1 << 23, 1 << 24, size=20_000), [1 << 23, (1 << 24) - 1, (1 << 23) + 1]])
+    for e in (-110, -109, -103, 0, 126):
+        x = (mant.astype(np.float64) * 2.0 ** (e - 23)).astype(np.float32)
+        h, m, l = split3(x)
+        assert np.array_equal(h.astype(np.float64) + m + l, x.astype(np.float64)), e
+    x = (mant.astype(np.float64) * 2.0 ** (-111 - 23)).astype(np.float32)
+    h, m, l = split3(x)
+    assert not np.array_equal(h.astype(np.float64) + m + l, x.astype(np.float64))
+    assert np.isinf(bf16(np.finfo(np.float32).max))
 
 
 def test_six_products_are_exact_and_the_dropped_three_are_below_two_units():
