@@ -48,12 +48,16 @@ struct RingTables {
     int pool_slots() const { return N * N; }
 };
 
-// Chunks of 32 K-steps of the split contraction (bf16 matrix cores, six
-// products), or 0 where c <= 32 and the fp32 one stays: 2, 3 or 4 for the
-// encode, and that many and a 16-step tail for the decode where its K = c + N -
-// 1 observations fit them.
-inline int split_chunks(int c) { return c <= 32 ? 0 : (c <= 64 ? 2 : (c <= 96 ? 3 : 4)); }
-inline bool split_decode_fits(int N, int c) { return c > 32 && c + N - 1 <= 32 * split_chunks(c) + 16; }
+// Whether the plan contracts on fp32 operands (else on split ones, see
+// split.hpp): where the one-pass kernel's waves keep the coefficients in their
+// registers, eight waves those of c <= 64 and sixteen those of c <= 32.  The step
+// calls follow the one-pass kernel, so that both give the same bits.
+inline bool contracts_fp32(int N, int c) { return c <= (N <= 8 ? 64 : 32); }
+// Chunks of 32 K-steps of the split contraction, or 0 where the fp32 one stays:
+// 2, 3 or 4 for the encode, and that many and a 16-step tail for the decode
+// where its K = c + N - 1 observations fit them.
+inline int split_chunks(int N, int c) { return contracts_fp32(N, c) ? 0 : (c <= 64 ? 2 : (c <= 96 ? 3 : 4)); }
+inline bool split_decode_fits(int N, int c) { return c + N - 1 <= 32 * split_chunks(N, c) + 16; }
 // bf16 of one 16-row tile of a worker's split operands: per chunk and term 64
 // lanes of 8, and for the decode per term 64 lanes of 4 of the tail.  A worker
 // has 2 KC tiles (zero beyond c rows).

@@ -1449,10 +1449,9 @@ void add_instance(PassParams &a, size_t P, const PassInst &in) {
     if (((uintptr_t)in.grads | (uintptr_t)in.out) % 128) a.ragged = 1;
 }
 
-// Whether the encode (decode) runs on split operands.  The step calls follow
-// the one-pass kernel of the plan, so that both give the same bits.
-bool split_encode(const cerar_plan *plan) { return plan->KC > 0 && !pass_is_fp32(plan->N, plan->c); }
-bool split_decode(const cerar_plan *plan) { return split_encode(plan) && !plan->dec_split.empty(); }
+// Whether the encode (decode) runs on split operands.
+bool split_encode(const cerar_plan *plan) { return plan->KC > 0; }
+bool split_decode(const cerar_plan *plan) { return !plan->dec_split.empty(); }
 
 // One launch of the split encode or decode for up to kPassInst instances.
 template <class Launch>

@@ -568,7 +568,7 @@ void build_fragments(cerar_plan *p) {
                     if (m < c && k <= L) v = (float)p->R[((size_t)i * (L + 1) + k) * c + m];
                     p->dec_frag[(((size_t)i * p->MT + mt) * p->KSd + ks) * kLanes + lane] = v;
                 }
-    const int KC = p->KC = split_chunks(c);
+    const int KC = p->KC = split_chunks(N, c);
     if (!KC) return;
     const size_t te = split_tile_encode(KC), td = split_tile_decode(KC);
     p->enc_split.assign((size_t)N * 2 * KC * te, 0);

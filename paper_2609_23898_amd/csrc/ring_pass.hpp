@@ -43,10 +43,6 @@ inline size_t pass_lds(int N, int c, int V) { return (size_t)N * pass_region(N, 
 // Positions of one workgroup's block for this plan, or 0 where the one-pass
 // kernel does not take it.
 int pass_positions(int N, int c);
-// Whether it contracts on fp32 operands (else on split ones): eight waves can
-// keep the fp32 coefficients of c <= 64 in their registers, sixteen those of
-// c <= 32.
-inline bool pass_is_fp32(int N, int c) { return c <= (N <= 8 ? 64 : 32); }
 // The workgroups per CU of the plan's own kernels on the current device, looked
 // up once, so that a launch, which may be under stream capture, only launches.
 hipError_t prepare_passes(int N, int c, PassSize *out);

@@ -63,3 +63,20 @@ def test_plan_builder_is_race_free_under_tsan(tmp_path):
     assert run.returncode == 0, (run.stdout + run.stderr)[-4000:]
     assert "ThreadSanitizer" not in run.stderr, run.stderr[-4000:]
     assert "threads done, failures 0" in run.stdout, run.stdout
+
+
+def test_plan_builder_prepares_only_operands_that_a_kernel_reads(tmp_path):
+    """Split operands for the plans that contract on them and no others: c > 32
+    beyond N = 8, c > 64 up to it; the decode's where its observations fit."""
+    exe = _build(tmp_path, "operands_driver.cpp", ["-fsanitize=undefined"], "ubsan")
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert run.returncode == 0, run.stderr[-2000:]
+    rows = [tuple(map(int, line.split())) for line in run.stdout.splitlines()]
+    assert len(rows) > 60
+    for N, c, KC, enc, dec, enc_split, dec_split in rows:
+        split = c > (64 if N <= 8 else 32)
+        tail = c + N - 1 <= 32 * KC + 16
+        assert enc > 0 and dec > 0
+        assert KC == (0 if not split else 2 if c <= 64 else 3 if c <= 96 else 4), (N, c)
+        assert enc_split == N * 2 * KC * (KC * 3 * 64 * 8), (N, c)
+        assert dec_split == (N * 2 * KC * (KC * 3 * 64 * 8 + 3 * 64 * 4) if split and tail else 0), (N, c)
