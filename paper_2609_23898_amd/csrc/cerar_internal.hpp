@@ -51,7 +51,12 @@ struct RingTables {
 // Whether the plan contracts on fp32 operands (else on split ones, see
 // split.hpp): where the one-pass kernel's waves keep the coefficients in their
 // registers, eight waves those of c <= 64 and sixteen those of c <= 32.  The step
-// calls follow the one-pass kernel, so that both give the same bits.
+// calls follow the one-pass kernel, so that both give the same bits.  Beyond
+// N = 16 there is none; there the split pays where c is no multiple of 16 (N =
+// 24, d = 200000 c: c = 40 encode 391 us and decode 505 against 566 and 541 on
+// masked fp32 tiles), is even at c = 64 (516 and 664 against 521 and 668), and at c =
+// 48 the step decode loses what the bucketed call wins (493 against 465 us, 17
+// buckets 2.13 against 2.20 ms), so one rule holds for all.
 inline bool contracts_fp32(int N, int c) { return c <= (N <= 8 ? 64 : 32); }
 // Chunks of 32 K-steps of the split contraction, or 0 where the fp32 one stays:
 // 2, 3 or 4 for the encode, and that many and a 16-step tail for the decode

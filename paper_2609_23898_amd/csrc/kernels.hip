@@ -2201,14 +2201,11 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
         }
         return CERAR_OK;
     }
-    std::vector<Geometry> geo(nbuckets);
-    for (int b = 0; b < nbuckets; ++b) geo[b] = Geometry{lay[b].p, lay[b].stride, false};
-    // every bucket's encode, then each round once for all buckets (up to
-    // kMaxBatch per launch), then every bucket's decode: one stream orders them.
-    // With c <= 64 the encode and the decode are batched too (interior blocks of
-    // up to kMaxInst buckets per launch, then their tails); otherwise each bucket
-    // gets its own launches.
-    const bool batched = plan->KC == 0 && mtiles_per_launch(plan->MT, plan->KSd, kDecodeRowsBytes) == plan->MT;
+    // every bucket's encode, then each round once for all buckets, then every
+    // bucket's decode: one stream orders them.  Up to kPassInst buckets share a
+    // launch on split operands, up to kMaxInst one on fp32 operands with c <= 64
+    // (interior blocks, then their tails); the fp32 decode of a wider plan gets
+    // its own launches for each bucket.
     std::vector<BucketRef> bk(nbuckets);
     std::vector<PassInst> inst(nbuckets);
     for (int b = 0; b < nbuckets; ++b) {
@@ -2224,11 +2221,8 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
         each_launch([&](const PassInst *in, int n) {
             return split_launch(plan, dc, pass_params(plan, dc, ld_grads, ld_work, ld_out), in, n, launch_encode_split, s);
         });
-    else if (batched) st = enqueue_encode_buckets(plan, dc, bk, ld_grads, ld_work, s);
     else
-        for (int b = 0; b < nbuckets && !st; ++b)
-            st = enqueue_encode(plan, dc, geo[b], bucket_len[b], grads + bucket_off[b], ld_grads,
-                                work + lay[b].work_off, ld_work, (char *)ws + lay[b].ws_off, s);
+        st = enqueue_encode_buckets(plan, dc, bk, ld_grads, ld_work, s);
     const int P = rounds_positions(plan->N);
     if (P)
         each_launch([&](const PassInst *in, int n) { return enqueue_rounds(plan, dc, in, n, ld_work, s); });
@@ -2271,10 +2265,10 @@ static int ring_simulate_bucketed_impl(const cerar_plan *plan, int nbuckets, con
         each_launch([&](const PassInst *in, int n) {
             return split_launch(plan, dc, pass_params(plan, dc, ld_grads, ld_work, ld_out), in, n, launch_decode_split, s);
         });
-    else if (batched) st = enqueue_decode_buckets(plan, dc, bk, ld_work, ld_out, s);
+    else if (plan->MT <= kMaxRegTiles) st = enqueue_decode_buckets(plan, dc, bk, ld_work, ld_out, s);
     else
         for (int b = 0; b < nbuckets && !st; ++b)
-            st = enqueue_decode(plan, dc, geo[b], bucket_len[b], work + lay[b].work_off, ld_work,
+            st = enqueue_decode(plan, dc, Geometry{lay[b].p, lay[b].stride, false}, bucket_len[b], work + lay[b].work_off, ld_work,
                                 (char *)ws + lay[b].ws_off, out + bucket_off[b], ld_out, s);
     return st;
 }

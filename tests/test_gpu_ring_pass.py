@@ -96,7 +96,9 @@ def test_step_calls_on_rows_at_any_float(N, c, d, off, extra):
 @pytest.mark.parametrize("N,c,lens", [(8, 20, [20 * 64 * 5 + 3, 1, 20 * 63, 7777]), (3, 64, [64 * 33, 64 * 31 + 5]),
                                       (4, 12, [97 * (b + 1) for b in range(33)]),
                                       (8, 70, [70 * 64 + 1, 70 * 200, 9]), (16, 64, [64 * 96] * 3),
-                                      (18, 32, [32 * 64 * 5 + 3, 1, 32 * 97]), (17, 24, [24 * 65, 7, 24 * 64 + 5])])
+                                      (18, 32, [32 * 64 * 5 + 3, 1, 32 * 97]), (17, 24, [24 * 65, 7, 24 * 64 + 5]),
+                                      (18, 64, [64 * 200 + 1, 9, 64 * 64]), (24, 63, [63 * 200 + 1, 9, 63 * 64]),
+                                      (20, 48, [48 * 64 * 3 - 1, 48 * 65])])
 def test_buckets_equal_calls_of_their_own(N, c, lens):
     """Odd offsets and lengths, more buckets than one launch takes: each bucket
     has the bits of its own call."""
@@ -320,26 +322,30 @@ class _KernelNode(ctypes.Structure):                # hipKernelNodeParams
                 ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
 
 
-def _one_launch_grid(call):
-    """Workgroups of the single kernel that call(stream) enqueues, from a
-    stream capture that is never run."""
+def _launch_grids(call):
+    """Workgroups of every kernel that call(stream) enqueues, from a stream
+    capture that is never run."""
     torch, _ = torch_dev()
     hip = ctypes.CDLL(sorted(C._hip_runtimes())[0])
     s = torch.cuda.Stream()
-    graph, n = ctypes.c_void_p(), ctypes.c_size_t(1)
-    nodes, node = (ctypes.c_void_p * 1)(), _KernelNode()
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
     assert hip.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 1) == 0     # thread-local mode
     try:
         call(s)
     finally:
         assert hip.hipStreamEndCapture(ctypes.c_void_p(s.cuda_stream), ctypes.byref(graph)) == 0
+    grids = []
     try:
-        assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0 and n.value == 1
+        assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+        nodes = (ctypes.c_void_p * n.value)()
         assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
-        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(nodes[0]), ctypes.byref(node)) == 0
+        for q in nodes:
+            node = _KernelNode()
+            assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(q), ctypes.byref(node)) == 0
+            grids.append(node.grid.x)
     finally:
         hip.hipGraphDestroy(graph)
-    return node.grid.x
+    return grids
 
 
 def test_launch_size_is_the_plans_own():
@@ -356,5 +362,24 @@ def test_launch_size_is_the_plans_own():
         plan.prepare_device()
         grads = torch.zeros((8, d), dtype=torch.float32, device=dev)
         out = torch.empty_like(grads)
-        grids[c] = _one_launch_grid(lambda s: C.ring_simulate_fused(plan, d, grads, out, stream=s))
+        grids[c], = _launch_grids(lambda s: C.ring_simulate_fused(plan, d, grads, out, stream=s))
     assert grids == {16: 3 * 16 * cus, 64: cus}
+
+
+@pytest.mark.parametrize("N,c", [(8, 64), (16, 48), (16, 128), (17, 32), (17, 40), (18, 64), (24, 63), (20, 48), (18, 80)])
+def test_buckets_share_their_launches(N, c):
+    """A call launches as often for thirty buckets as for three."""
+    torch, dev = torch_dev()
+    rng = np.random.default_rng(c)
+    plan = C.Plan.explicit(rng.standard_normal((N, c, c)), rng.standard_normal((N, c + N - 1, c)))
+    plan.prepare_device()
+    counts = []
+    for nb in (3, 30):
+        lens = [c * 96 + 7] * nb
+        grads = torch.zeros((N, sum(lens)), dtype=torch.float32, device=dev)
+        wf, wsb = plan.bucketed_sizes(lens)
+        work = torch.empty((N, wf), dtype=torch.float32, device=dev)
+        ws, out = torch.empty(wsb, dtype=torch.uint8, device=dev), torch.empty_like(grads)
+        buckets = [(b * lens[0], lens[0]) for b in range(nb)]
+        counts.append(len(_launch_grids(lambda s: C.ring_simulate_bucketed(plan, buckets, grads, work, ws, out, stream=s))))
+    assert counts[0] == counts[1]
