@@ -2131,9 +2131,10 @@ int enqueue_decode_buckets(const cerar_plan *plan, const DeviceCopy *dc, const s
     };
     int st = CERAR_OK;
     with_decode_ks(ks, [&](auto K) {
-        st = launch_bucket_batches(plan, bk, b, set, [&](const DecBatch &x, Path path, dim3 grid) {
-            launch_decode_ks<decltype(K)::value>(x, path, lds, s, grid);
-        });
+        if constexpr (decltype(K)::value <= 32)      // c <= 64: K = c + N - 1 <= 127
+            st = launch_bucket_batches(plan, bk, b, set, [&](const DecBatch &x, Path path, dim3 grid) {
+                launch_decode_ks<decltype(K)::value>(x, path, lds, s, grid);
+            });
     });
     return st;
 }
