@@ -18,9 +18,10 @@ algorithmic bytes are the bytes moved.  A second loop makes the same calls
 with HIP events between the phases on the launch stream; those events give
 each kernel's average duration.  The single-call forms, which hand the
 messages over on chip where one device holds all workers, are reported beside
-them (one_pass, fused_variant) and never as the value.  The fp64 CPU oracle is timed on sampled positions of the same
-workload and plan (cpu_baseline), and the timed run's outputs are compared
-with its results (parity_vs_oracle).
+them (one_pass, fused_variant) and never as the value.  The fp64 CPU oracle
+is timed on sampled positions of the same workload and plan (cpu_baseline), and
+the outputs of the step calls are compared with its results
+(parity_vs_oracle), those of the single call with theirs (one_pass).
 """
 
 import argparse
@@ -61,6 +62,9 @@ def parse():
                     help="sampled positions per oracle process (0 = skip cpu_baseline)")
     ap.add_argument("--cpu-seconds", type=float, default=10.0,
                     help="seconds each oracle process runs its sample (repeating it)")
+    ap.add_argument("--single-call", action="store_true",
+                    help="make only cerar_ring_simulate calls (and the reference copy), for traces and counters of "
+                         "their kernels alone; prints its own line, not the bench's")
     ap.add_argument("--copy-floats", type=int, default=1 << 30, help="size of the copy reference")
     ap.add_argument("--summarize-trace", nargs=3, metavar=("TRACE_DIR", "BENCH_LOG", "OUT"),
                     help="write the summary of a rocprofv3 --kernel-trace --stats run of this bench")
@@ -85,7 +89,9 @@ TRAFFIC_FILES = {"pythia-1.4b": TRAFFIC_FILE,
 FAMILIES = (("k_encode", "k_encode (K1)"), ("k_round<0,", "k_round<0> (K2: recv + delta)"),
             ("k_round<1,", "k_round<1> (K3: recv - delta + delta)"),
             ("k_round<2,", "k_round<2> (K3: recv - delta)"), ("k_decode", "k_decode (K4)"),
+            ("k_ring_pass", "k_ring_pass (single call)"), ("k_rounds_pass", "k_rounds_pass (single call, all rounds)"),
             ("k_copy4", "k_copy4 (copy reference)"))
+SINGLE_CALL = ("k_ring_pass (single call)", "k_rounds_pass (single call, all rounds)")
 
 
 def kernel_source_hash():
@@ -98,12 +104,15 @@ def kernel_source_hash():
 
 
 def contraction_peak(stage, c, K):
-    """Peak of a stage's contraction in fp32 TFLOP/s and how it runs.  At
-    c = 128 the interior encode and the interior decode with K <= 144
-    observations run on bf16 MFMAs with operands split into three bf16 terms,
-    six products per fp32 product: their fp32-equivalent peak is the bf16 peak
-    over six.  Every other encode and decode runs fp32 MFMAs."""
-    if c == 128 and (stage == "encode" or K <= 144):
+    """Peak of a stage's contraction in fp32 TFLOP/s and how it runs.  Plans
+    with c > 64, or with N > 8 workers and c > 32, run their encode, and their
+    decode of K <= 32 KC + 16 observations (KC 32-step chunks cover c), on bf16
+    MFMAs with operands split into three bf16 terms, six products per fp32
+    product: their fp32-equivalent peak is the bf16 peak over six.  Every other
+    encode and decode runs fp32 MFMAs."""
+    N = K - c + 1
+    chunks = 2 if c <= 64 else 3 if c <= 96 else 4
+    if c > (64 if N <= 8 else 32) and (stage == "encode" or K <= 32 * chunks + 16):
         return BF16_MFMA_PEAK_TFLOPS / SPLIT_PRODUCTS, "bf16 MFMA on three-term splits (6 products)"
     return FP32_MFMA_PEAK_TFLOPS, "fp32 MFMA"
 
@@ -143,6 +152,17 @@ def _launch_bytes(workload=None):
             "k_round<0> (K2: recv + delta)": N * bw["rounds"][1],
             "k_round<1> (K3: recv - delta + delta)": N * bw["rounds"][N],
             "k_round<2> (K3: recv - delta)": N * bw["rounds"][c]}
+
+
+def _single_call_bytes(workload=None):
+    """The same for the kernels of cerar_ring_simulate."""
+    from paper_2609_23898_amd import synth
+    wl = synth.workload(workload or synth.HEADLINE)
+    N, c = wl.N, wl.c
+    p = -(-(-(-wl.d // c)) // 32) * 32
+    # gradients read, outputs and the c + N - 1 observations written; chunks
+    # read and the messages of rounds 1..L written
+    return dict(zip(SINGLE_CALL, (N * 4 * (2 * wl.d + (c + N - 1) * p), N * 4 * p * (2 * c + N - 2))))
 
 
 def summarize_trace(trace_dir, bench_log, out_path, bench_args=()):
@@ -186,12 +206,12 @@ def summarize_trace(trace_dir, bench_log, out_path, bench_args=()):
         # the bucketed call's batch kernels are listed but kept out of the
         # per-family comparison with the single-instance step's events
         fam = None if "_batch" in name else family_of_name(name)
-        if fam:
+        if fam and fam not in SINGLE_CALL:         # listed above; the bench's calls of these kernels differ
             fam_ns.setdefault(fam, []).append((calls, tot))
     lines += ["", "# per family: trace average vs the bench's HIP-event average on the launch stream",
               f"{'family':<42s} {'trace_avg_ms':>12s} {'event_avg_ms':>12s} {'ratio':>7s}"]
     for fam, parts in fam_ns.items():
-        ev = bench["kernels"].get(fam, {}).get("avg_ms") if bench else None
+        ev = bench.get("kernels", {}).get(fam, {}).get("avg_ms") if bench else None
         if fam in ("k_encode (K1)", "k_decode (K4)") and len({n for n, _ in parts}) == 1:
             # one encode or decode is every listed kernel once (interior blocks,
             # then the masked tail), and the events bracket all of them
@@ -200,7 +220,9 @@ def summarize_trace(trace_dir, bench_log, out_path, bench_args=()):
             ta = sum(t for _, t in parts) / sum(n for n, _ in parts) / 1e6
         lines.append(f"{fam:<42s} {ta:12.4f} {ev if ev is not None else float('nan'):12.4f} "
                      f"{(ev / ta) if ev else float('nan'):7.3f}")
-    if bench:
+    if bench and "single_call" in bench:
+        lines += ["", f"# cerar_ring_simulate alone: {bench['single_call']['ms_per_step']} ms per call"]
+    elif bench:
         rf = bench["roofline"]
         lines += ["", f"# bench line: {bench['ms_per_step']} ms/step, {bench['value']} GB/s "
                       f"({bench['config']['pct_hbm_peak']}% of 8 TB/s); roofline kernel "
@@ -245,16 +267,20 @@ def summarize_pmc(fetch_dir, write_dir, out_path, copy_floats=1 << 30, workload=
     copy_kib = copy_floats * 4 / 1024.0
     f_scale = fetch[copy][0] / copy_kib
     w_scale = write[copy][0] / copy_kib
-    algo = _launch_bytes(workload)
+    algo = {**_launch_bytes(workload), **_single_call_bytes(workload)}
     wl = synth.workload(workload or synth.HEADLINE)
     wflag = f" --workload {workload}" if workload else ""
+    regex = "k_(encode|round|decode|copy4)"
+    if any(f in fetch for f in SINGLE_CALL):
+        wflag += " --single-call"
+        regex = "k_(ring_pass|encode|rounds_pass|decode|copy4)"
     lines = ["# HBM traffic per launch from rocprofv3 counters (FETCH_SIZE, WRITE_SIZE in KiB; an encode or "
              "decode launch is its interior and tail dispatches)",
              f"# workload: {wl.name} (N={wl.N}, c={wl.c}, d={wl.d}, fp32)",
              "# commands (repo root, MI355X), one counter per run:",
-             "#   rocprofv3 --pmc FETCH_SIZE --kernel-include-regex 'k_(encode|round|decode|copy4)' -f csv "
+             f"#   rocprofv3 --pmc FETCH_SIZE --kernel-include-regex '{regex}' -f csv "
              f"-d {fetch_dir} -o pmc -- python3 bench.py{wflag} --steps 1 --warmup 0 --cpu-positions 0",
-             "#   rocprofv3 --pmc WRITE_SIZE --kernel-include-regex 'k_(encode|round|decode|copy4)' -f csv "
+             f"#   rocprofv3 --pmc WRITE_SIZE --kernel-include-regex '{regex}' -f csv "
              f"-d {write_dir} -o pmc -- python3 bench.py{wflag} --steps 1 --warmup 0 --cpu-positions 0",
              f"#   python3 bench.py --summarize-pmc {fetch_dir} {write_dir} {out_path}"
              + (f" --pmc-workload {workload}" if workload else ""),
@@ -540,6 +566,22 @@ def main():
         if ev is not None:
             ev[L + 2].record()
 
+    if args.single_call:
+        for _ in range(args.warmup):
+            C.ring_simulate(plan, d, grads, work, ws, out)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(args.steps):
+            C.ring_simulate(plan, d, grads, work, ws, out)
+        torch.cuda.synchronize()
+        ms = (time.perf_counter() - t) * 1e3 / args.steps
+        nf = min(args.copy_floats, grads.numel())
+        C.copy_f32(out.view(-1)[:nf], grads.view(-1)[:nf])
+        torch.cuda.synchronize()
+        print(json.dumps({"single_call": {"ms_per_step": round(ms, 4), "steps": args.steps},
+                          "config": {"workload": wl.name, "workload_name": args.workload, "plan": plan_desc}}), flush=True)
+        return
+
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
@@ -704,8 +746,9 @@ def main():
     spread = encode_spread(C, plan, d, grads, work, ws, 10)
     log(f"encode on two gradient allocations: {spread}")
 
-    # approximation error of the decoded sums (K5, not timed)
-    C.ring_simulate(plan, d, grads, work, ws, out)
+    # approximation error of the decoded sums (K5, not timed), of the step calls
+    # that the value counts; the single call's outputs are compared with them
+    step()
     norms = torch.empty(N + 1, dtype=torch.float64, device=dev)
     C.error_norms(N, d, grads, out, norms)
     nm = norms.cpu().numpy()
@@ -725,13 +768,17 @@ def main():
         parity = {"max_rel_l2": max(math.sqrt(pv[2 * i] / pv[2 * i + 1]) for i in range(N)),
                   "outputs": int(ok.sum()) * N, "kappa_M": info["kappa_M"],
                   "fp64_reliable": bool(info["fp64_reliable"]),
-                  "note": "the GPU line's outputs against the fp64 oracle of cpu_baseline on the same plan and "
+                  "note": "the step calls' outputs against the fp64 oracle of cpu_baseline on the same plan and "
                           "inputs, at its kept positions; squared sums by K5 (cerar_sampled_norms)"}
         if not info["fp64_reliable"]:
             parity["note"] += ("; the plan is singular even in fp64 (fp64_reliable = 0), so the oracle's own "
                                "output is not meaningful and this figure is reported only")
         log(f"parity vs oracle: {parity['max_rel_l2']:.3g} over {parity['outputs']} outputs"
             + ("" if info["fp64_reliable"] else " (plan singular in fp64: reported only)"))
+    single = torch.empty_like(out)
+    C.ring_simulate(plan, d, grads, work, ws, single)
+    one_pass["outputs_equal_step_calls"] = all(torch.equal(out[w], single[w]) for w in range(N))
+    del single
 
     step_bytes = N * C.algorithmic_bytes_per_worker(N, c, p)
     value = step_bytes / (ms_per_step * 1e-3) / 1e9

@@ -172,6 +172,12 @@ def test_contraction_peak_names_the_split_kernels():
     assert bench.contraction_peak("decode", 128, 144)[0] == peak
     assert bench.contraction_peak("decode", 128, 145)[0] == bench.FP32_MFMA_PEAK_TFLOPS
     assert bench.contraction_peak("encode", 64, 71)[0] == bench.FP32_MFMA_PEAK_TFLOPS
+    # K = c + N - 1: every c > 64, and c > 32 where N > 8
+    for stage, c, K in (("encode", 96, 98), ("decode", 96, 112), ("encode", 65, 66), ("encode", 64, 79), ("decode", 64, 79),
+                        ("encode", 33, 41), ("encode", 64, 90)):
+        assert bench.contraction_peak(stage, c, K)[0] == peak, (stage, c, K)
+    for stage, c, K in (("encode", 32, 47), ("encode", 33, 40), ("decode", 64, 71), ("decode", 64, 81), ("decode", 96, 113)):
+        assert bench.contraction_peak(stage, c, K)[0] == bench.FP32_MFMA_PEAK_TFLOPS, (stage, c, K)
     assert 32 < peak * 1e12 / (bench.HBM_PEAK_GBS * 1e9)
 
 

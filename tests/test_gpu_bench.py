@@ -41,6 +41,8 @@ def test_bench_line_on_the_tiny_workload():
     assert ip["ms_per_step_events"]["median"] > 0 and ip["encode_ms"]["median"] > 0
     sp = b["encode_spread"]
     assert 0 < sp["min_ms"] <= sp["max_ms"] and "fresh_buffer" in sp
+    assert b["one_pass"]["outputs_equal_step_calls"] is True
+    assert "step calls' outputs" in b["parity_vs_oracle"]["note"]
     # the tiny workload's Vandermonde plan (tau = 0.5, Sec. II-B) is a poor
     # approximation by construction (Phi about 185), so only finiteness is checked
     assert math.isfinite(b["approx_rel_err_max"])
