@@ -70,6 +70,40 @@ def test_one_pass_leaves_the_step_calls_bits(N, c, d, off, extra):
     assert torch.equal(got[2][:, :d], again[:, :d])
 
 
+# Several blocks for every workgroup of the launch: the loop with the next
+# block's loads under way, LDS used again, and the XCD order of ragged rows.
+LONG = [(2, 16, 110_000_000, 0), (4, 12, 40_000_007, 1), (8, 32, 34_000_000, 0), (8, 20, 21_000_001, 0), (3, 48, 9_000_000, 0),
+        (8, 64, 3_000_000, 0), (8, 60, 3_000_001, 3), (16, 16, 4_800_000, 0), (9, 25, 7_500_003, 1), (12, 48, 2_000_000, 0),
+        (16, 64, 2_000_000, 0), (16, 60, 2_000_001, 1), (4, 100, 90_000_000, 0), (16, 128, 25_000_000, 0), (7, 90, 30_000_001, 2)]
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("N,c,d,off", LONG)
+def test_workgroups_with_many_blocks_leave_the_step_calls_bits(N, c, d, off, in_place):
+    torch, dev = torch_dev()
+    rng = np.random.default_rng(N * 1000 + c)
+    U, R = rng.standard_normal((N, c, c)) / c ** 0.5, rng.standard_normal((N, c + N - 1, c)) / c
+    plan = C.Plan.explicit(U, R)
+    p, _ = plan.chunk_len(d)
+    ld = c * p + off
+    gen = torch.Generator(dev).manual_seed(c)
+    g = torch.randn((N, d), dtype=torch.float32, device=dev, generator=gen)
+    res = []
+    for call in (lambda *b: C.ring_simulate(plan, d, *b), lambda *b: _steps(plan, d, *b)):
+        work = torch.empty(N * ld + off, dtype=torch.float32, device=dev)[off:].view(N, ld)
+        ws = torch.zeros(plan.workspace_bytes(d), dtype=torch.uint8, device=dev)
+        out = torch.empty(N * (d + off) + off, dtype=torch.float32, device=dev)[off:].view(N, d + off)
+        grads = torch.empty(N * ld + off, dtype=torch.float32, device=dev)[off:].view(N, ld)
+        grads[:, :d] = g
+        if in_place:
+            work = grads
+        call(grads, work, ws, out)
+        torch.cuda.synchronize()
+        res.append((out[:, :d], work[:, :c * p], ws))
+    for a, b in zip(*res):
+        assert all(torch.equal(x, y) for x, y in zip(a, b)) if a.dim() == 2 else torch.equal(a, b)
+
+
 @pytest.mark.parametrize("N,c,d", [(4, 12, 12 * 320 + 5), (3, 33, 33 * 97), (8, 16, 16 * 640 + 1), (8, 48, 48 * 160 - 65),
                                    (8, 64, 64 * 333 + 9), (20, 32, 32 * 64 * 9 + 5), (18, 128, 128 * 96 - 1),
                                    (24, 70, 70 * 130 + 3)])
@@ -97,6 +131,8 @@ def test_step_calls_on_rows_at_any_float(N, c, d, off, extra):
                                       (4, 12, [97 * (b + 1) for b in range(33)]),
                                       (8, 70, [70 * 64 + 1, 70 * 200, 9]), (16, 64, [64 * 96] * 3),
                                       (18, 32, [32 * 64 * 5 + 3, 1, 32 * 97]), (17, 24, [24 * 65, 7, 24 * 64 + 5]),
+                                      (8, 64, [64 * 32 * 400, 64 * 32 * 300 + 5, 64 * 32 * 200 - 1, 70]),
+                                      (16, 64, [64 * 32 * 300, 9, 64 * 32 * 350 + 1]), (2, 48, [48 * 32 * 2500, 48 * 32 * 1000 + 1]),
                                       (18, 64, [64 * 200 + 1, 9, 64 * 64]), (24, 63, [63 * 200 + 1, 9, 63 * 64]),
                                       (20, 48, [48 * 64 * 3 - 1, 48 * 65])])
 def test_buckets_equal_calls_of_their_own(N, c, lens):

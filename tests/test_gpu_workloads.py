@@ -326,3 +326,27 @@ def test_chunks_longer_than_the_fast_path_offsets():
     run_stepwise(plan, wl.d, grads, work, ws, out)
     torch.cuda.synchronize()
     check_sampled("2^32 floats per worker", wl, U, R, grads, out, sample_positions(p, 8192, 6), kappa)
+    out.fill_(float("nan"))
+    C.ring_simulate(plan, wl.d, grads, work, ws, out)          # the one-pass kernel, addressed in 64 bits
+    torch.cuda.synchronize()
+    check_sampled("2^32 floats per worker, single call", wl, U, R, grads, out, sample_positions(p, 8192, 6), kappa)
+
+
+@pytest.mark.parametrize("N,c,p", [(2, 3, (1 << 26) + 96),       # k_ring_pass with blocks of 64 positions
+                                   (9, 33, (1 << 25) + 64),      # k_ring_pass_split: 24 rows no longer fit 32 bits
+                                   (3, 65, (1 << 26) + 64)])     # split encode and decode, k_rounds_pass
+def test_single_call_on_rows_beyond_32_bit_offsets(N, c, p):
+    """Chunks long enough that the kernels of the single call address their
+    rows in 64 bits, odd lengths."""
+    torch, dev = torch_dev()
+    d = c * p - 37
+    wl = synth.Workload(f"N={N} c={c} d={d} iid N(0,1)", N, c, d, seed=7)
+    U, R = orthogonal_plan(N, c, seed=77)
+    plan = C.Plan.explicit(U, R)
+    assert OR.chunk_len(d, c, CHUNK_ALIGN) == p
+    grads = device_grads(wl, torch, dev)
+    work, ws, out = C.allocate(plan, d, dev)
+    out.fill_(float("nan"))
+    C.ring_simulate(plan, d, grads, work, ws, out)
+    torch.cuda.synchronize()
+    check_sampled(wl.name, wl, U, R, grads, out, sample_positions(p, 4096, 7), OP.max_kappa_M(U))
