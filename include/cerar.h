@@ -298,10 +298,12 @@ int cerar_ring_simulate_fused(const cerar_plan *plan, size_t d, const float *gra
  * bucket_off[b] + bucket_len[b]) of every worker's gradient and gets its own
  * p_b (cerar_chunk_len of bucket_len[b]).  work holds, per worker, the buckets' c*p_b
  * slots back to back (stride ld_work >= sum_b c*p_b); ws is
- * cerar_bucketed_workspace_bytes.  Enqueued on `stream`: where the plan fits
- * the one-pass kernel (cerar_ring_simulate), one launch for up to 32 buckets;
- * otherwise every bucket's encode, then each round as one launch for up to 64
- * buckets and all workers, then every bucket's decode.
+ * cerar_bucketed_workspace_bytes.  Enqueued on `stream`: where the call goes in
+ * one pass (cerar_ring_simulate), one launch for up to 32 buckets; otherwise
+ * every bucket's encode (up to 32 to a launch), then all rounds as one launch
+ * for up to 32 buckets (N <= 16) or each round as one for up to 64, then every
+ * bucket's decode (up to 32 to a launch, or by bucket where c > 64 and the
+ * observations do not fit the split decode).
  * bucket_off/bucket_len are host arrays; buckets may not overlap in out.
  * Errors: E_INVAL (NULL plan or buffers, nbuckets < 1, an empty bucket,
  * overlapping buckets, ld_work below the slot total, ld_grads or ld_out below

@@ -3,7 +3,7 @@
 //  k_encode  (K1)  delta_{i,j} = sum_l U_i[l][j] chunk_l(g_i), all workers,
 //                  as fp32 MFMA 16x16x4 tiles: delta^T = U^T G^T, positions
 //                  on the MFMA N axis, coefficients (A operand) from LDS (plans
-//                  with c > 32 beyond the one-pass kernel: split.hip).
+//                  that contract on split operands: split.hip).
 //  k_round   (K2/K3) one ring round for all workers: next message =
 //                  received (- returning own term) (+ next own term).
 //  k_decode  (K4)  g_hat_i = Y_i R_i, the same MFMA tiling over the L+1
@@ -13,9 +13,9 @@
 //                  and on sampled positions against given reference values.
 //  k_copy          plain streaming copy (bandwidth reference).
 //
-// The whole-ring entry points take the one-pass kernel (ring_pass.hip) where
-// it fits the plan; the kernels here are the step calls, and the whole ring
-// for the other plans.
+// The whole-ring entry points go in one pass (ring_pass.hip) where the plan
+// and the buffers allow it; the kernels here are the step calls, and the
+// contractions of the whole ring otherwise (its rounds too beyond N = 16).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -25,7 +25,7 @@ namespace {
 // rows do not start on a line (a.ragged), each XCD takes a contiguous eighth
 // of the blocks, and the outputs are stored through the L2: the lines that two
 // blocks share are then put together there instead of going to memory in parts
-// (N = 4, c = 12, odd d = 48M: 730 -> 551 us; N = 8, c = 64, odd d = 60M: 2.62
+// (N = 4, c = 12, odd d = 48M: 730 -> 575 us; N = 8, c = 64, odd d = 60M: 2.62
 // -> 1.89 ms).  With rows on lines the plain order and streaming stores are
 // faster (c = 32: 2.70 against 2.74 ms).
 struct Sweep {
@@ -637,8 +637,8 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
     }
 }
 
-// All rounds of Algorithm 1 in one launch, for the plans the kernel above does
-// not take: encoded chunks from `work`, observations to their slots.  N
+// All rounds of Algorithm 1 in one launch, where the call does not go in one
+// pass: encoded chunks from `work`, observations to their slots.  N
 // waves; each loads its worker's chunk rows (four rows of 64 positions per
 // instruction) and stores the observations of the worker it receives for.
 //

@@ -1,5 +1,6 @@
-// Encode and decode of the plans with c > 32 (N <= 17) on split operands: the
-// step calls, and the whole ring where the one-pass kernel does not take it.
+// Encode and decode on split operands (contracts_fp32 says for which plans not):
+// the step calls, and the whole ring where it does not go in one pass.  The
+// encode takes any N, the decode those whose observations fit its K-steps.
 //
 // Bound by memory on 2c + 1 (encode) and 2c + N - 1 (decode) rows per worker.
 // A workgroup of eight waves holds its worker's split coefficients in LDS and

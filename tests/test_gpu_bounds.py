@@ -66,7 +66,7 @@ IN_PLACE_CASES = [
     (4, 5, 5 * 300 + 2, 0),
     (8, 16, 16 * 1024 + 9, 4),
     (8, 64, 64 * 700 + 33, 0),
-    (4, 64, 64 * 300 + 5, 1),            # odd stride: the scalar layout
+    (4, 64, 64 * 300 + 5, 1),            # odd stride: rows at any float
     (3, 128, 128 * 640 - 17, 4),         # the wide c = 128 encode and its tail
 ]
 

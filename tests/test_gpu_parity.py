@@ -1,6 +1,6 @@
 """Parity of the HIP path (through the C ABI) with the fp64 oracle on the same
 seeded inputs: each kernel step, the per-round buffer state, and the whole
-all-reduce, over vector and scalar layouts, ragged tails, in-place encode,
+all-reduce, over aligned and unaligned rows, ragged tails, in-place encode,
 N = 2 and c = N edge cases, error norms, buckets and the copy kernel."""
 
 import numpy as np
@@ -397,12 +397,12 @@ def test_host_threads_share_one_fresh_plan():
 
 
 IN_PLACE = [
-    # name, N, c, d, extra floats of row stride (odd: the scalar layout)
+    # name, N, c, d, extra floats of row stride (odd: rows at any float)
     ("c16", 4, 16, 16 * 1000, 0),              # the pipelined encode
     ("c5-ragged", 3, 5, 5 * 333 + 2, 0),       # c not a multiple of 16: the masked kernels
     ("c64-ragged", 8, 64, 64 * 1536 + 61, 0),  # the double-buffered c = 64 encode, then the tail
     ("c128-ragged", 4, 128, 128 * 320 + 7, 0), # the wide c = 128 encode, then the generic tail
-    ("c64-scalar", 4, 64, 64 * 500 + 3, 1),    # misaligned rows: the scalar layout
+    ("c64-unaligned", 4, 64, 64 * 500 + 3, 1), # rows at any float
 ]
 
 
@@ -431,8 +431,8 @@ def test_in_place_encode_matches_out_of_place(name, N, c, d, extra):
     assert max_rel_l2(out2.double().cpu().numpy(), ref) <= gate(OP.max_kappa_M(U))
 
 
-def test_scalar_layout_matches_vector_layout():
-    """Misaligned strides force the scalar kernels; same values as vector ones."""
+def test_unaligned_rows_match_aligned_rows():
+    """Rows that start at any float give the values of 16-byte aligned ones."""
     N, c, d = 4, 8, 8 * 512
     U, R = mpc_plan(N, c, 0.3, seed=10)
     plan = C.Plan.explicit(U, R)
