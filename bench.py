@@ -270,6 +270,8 @@ def summarize_pmc(fetch_dir, write_dir, out_path, copy_floats=1 << 30, workload=
     algo = {**_launch_bytes(workload), **_single_call_bytes(workload)}
     wl = synth.workload(workload or synth.HEADLINE)
     wflag = f" --workload {workload}" if workload else ""
+    if copy_floats != 1 << 30:
+        wflag += f" --copy-floats {copy_floats}"
     regex = "k_(encode|round|decode|copy4)"
     if any(f in fetch for f in SINGLE_CALL):
         wflag += " --single-call"
