@@ -38,7 +38,7 @@
  *    matrix cores (within two units of fp32 rounding per product).  Blocks of
  *    32 positions with an entry that the terms do not hold (nonzero and below
  *    2^-110, or 2^127 and above), and plans with such a coefficient, are
- *    contracted in fp32.  A round forms
+ *    scaled by a power of two for it or contracted in fp32.  A round forms
  *    recv - delta_j + delta_{k+1} in fp64 and rounds the message to fp32
  *    once.  The error norms accumulate in fp64.  Plan construction is host
  *    fp64.

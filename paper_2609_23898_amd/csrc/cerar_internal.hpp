@@ -62,6 +62,10 @@ inline bool contracts_fp32(int N, int c) { return c <= (N <= 8 ? 64 : 32); }
 // 2, 3 or 4 for the encode, and that many and a 16-step tail for the decode
 // where its K = c + N - 1 observations fit them.
 inline int split_chunks(int N, int c) { return contracts_fp32(N, c) ? 0 : (c <= 64 ? 2 : (c <= 96 ? 3 : 4)); }
+// What a plan's coefficients allow on split operands: everything; no scaling of
+// half-blocks with small entries (some are 2^40 or more); nothing (some are not
+// the sum of their three terms).
+enum SplitCoefs { kCoefsUsual, kCoefsLarge, kCoefsFp32 };
 inline bool split_decode_fits(int N, int c) { return c + N - 1 <= 32 * split_chunks(N, c) + 16; }
 // bf16 of one 16-row tile of a worker's split operands: per chunk and term 64
 // lanes of 8, and for the decode per term 64 lanes of 4 of the tail.  A worker
@@ -105,7 +109,7 @@ struct cerar_plan {
     std::vector<float> enc_frag, dec_frag;
     int KC = 0;                      // 32-step chunks of the split contraction, 0 where it is not used
     std::vector<uint16_t> enc_split, dec_split;   // bf16 bits, see split_tile_encode / split_tile_decode
-    bool split_wide = false;         // some coefficient is not the sum of its three terms
+    int split_coefs = 0;             // SplitCoefs of its coefficients
     mutable std::mutex dev_mu;
     mutable std::map<int, cerar::DeviceCopy> dev;   // per HIP device ordinal
 };

@@ -1434,7 +1434,7 @@ PassParams pass_params(const cerar_plan *plan, const DeviceCopy *dc, size_t ld_g
     a.KSd = plan->KSd;
     a.esplit = dc->enc_split;
     a.dsplit = dc->dec_split;
-    a.wide = plan->split_wide;
+    a.coefs = plan->split_coefs;
     a.run = 0;
     a.n = 0;
     a.nblk = 0;

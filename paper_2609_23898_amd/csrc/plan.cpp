@@ -508,21 +508,22 @@ float bf16_value(uint16_t b) {
 // bf16 terms: for chunk kc, term t and lane l, A[row = l % 16][k = 32 kc +
 // 8 (l / 16) + s], s = 0..7, and of the tail A[row][k = 32 KC + 4 (l / 16) + s],
 // s = 0..3.  coef(row, k) gives the fp32 coefficient of the tile.  Returns
-// whether every coefficient is the sum of its terms (not so beyond bf16's range
-// of exponents).
+// what they allow (a coefficient beyond bf16's range of exponents is not the sum
+// of its terms).
 template <class Coef>
-bool split_tile(uint16_t *tile, int KC, bool tail, Coef coef) {
-    bool exact = true;
+int split_tile(uint16_t *tile, int KC, bool tail, Coef coef) {
+    int allow = kCoefsUsual;
     auto put = [&](uint16_t *at, size_t term, float x) {
         if (!std::isfinite(x)) {
-            exact = false;
+            allow = kCoefsFp32;
             return;
         }
         const uint16_t h = bf16_bits(x);
         const float r = x - bf16_value(h);
         const uint16_t m = std::isfinite(r) ? bf16_bits(r) : 0;
         const uint16_t l = std::isfinite(r) ? bf16_bits(r - bf16_value(m)) : 0;
-        if (bf16_value(h) + (bf16_value(m) + bf16_value(l)) != x) exact = false;
+        if (bf16_value(h) + (bf16_value(m) + bf16_value(l)) != x) allow = kCoefsFp32;
+        if (std::fabs(x) >= 0x1p40f) allow = std::max<int>(allow, kCoefsLarge);
         at[0] = h;
         at[term] = m;
         at[2 * term] = l;
@@ -535,7 +536,7 @@ bool split_tile(uint16_t *tile, int KC, bool tail, Coef coef) {
         for (int lane = 0; lane < 64; ++lane)
             for (int s = 0; s < 4; ++s)
                 put(tile + (size_t)KC * 3 * 64 * 8 + lane * 4 + s, 64 * 4, coef(lane % 16, 32 * KC + 4 * (lane / 16) + s));
-    return exact;
+    return allow;
 }
 
 }  // namespace
@@ -575,15 +576,15 @@ void build_fragments(cerar_plan *p) {
     if (split_decode_fits(N, c)) p->dec_split.assign((size_t)N * 2 * KC * td, 0);
     for (int i = 0; i < N; ++i)
         for (int mt = 0; mt < 2 * KC; ++mt) {
-            bool exact = split_tile(&p->enc_split[((size_t)i * 2 * KC + mt) * te], KC, false, [&](int row, int k) {
+            int allow = split_tile(&p->enc_split[((size_t)i * 2 * KC + mt) * te], KC, false, [&](int row, int k) {
                 const int j = 16 * mt + row;
                 return j < c && k < c ? (float)p->U[((size_t)i * c + k) * c + j] : 0.0f;
             });
-            if (!p->dec_split.empty()) exact &= split_tile(&p->dec_split[((size_t)i * 2 * KC + mt) * td], KC, true, [&](int row, int k) {
+            if (!p->dec_split.empty()) allow = std::max(allow, split_tile(&p->dec_split[((size_t)i * 2 * KC + mt) * td], KC, true, [&](int row, int k) {
                 const int m = 16 * mt + row;
                 return m < c && k <= L ? (float)p->R[((size_t)i * (L + 1) + k) * c + m] : 0.0f;
-            });
-            if (!exact) p->split_wide = true;
+            }));
+            p->split_coefs = std::max(p->split_coefs, allow);
         }
 }
 

@@ -464,16 +464,22 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
         for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
             for (int s = 0; s < 8; ++s) range.add(x[kc][s]);
-        const bool rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+        const Contract how = range.contract(a.coefs, [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
-                              for (int kc = 0; kc < KC; ++kc)
+            for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-                                  for (int s = 0; s < 8; ++s) f(x[kc][s]);
-                          });
-        if (rare) {
+                for (int s = 0; s < 8; ++s) f(x[kc][s]);
+        });
+        if (how == kFp32) {
             encode_rare(I.grads + (size_t)w * a.ld_g, I.p, I.d, e0, c, a.efrag + (size_t)w * MT * a.KSe * 64, a.KSe, mine, lane);
             return;
         }
+        if (how == kScaled)
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                for (int s = 0; s < 8; ++s) x[kc][s] *= kScale;
+        const float back = how == kScaled ? 1.f / kScale : 1.f;
         Split3<v8bf> b[KC][2];
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc)
@@ -496,7 +502,7 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (EXC || lrow + r < c)
-                    *reinterpret_cast<v2f *>(mine + (lrow + r) * P + 2 * col) = v2f{acc[0][r], acc[1][r]};
+                    *reinterpret_cast<v2f *>(mine + (lrow + r) * P + 2 * col) = v2f{back * acc[0][r], back * acc[1][r]};
         }
     };
 
@@ -571,11 +577,11 @@ __global__ __launch_bounds__(1024) void k_ring_pass_split(PassParams a) {
                 dacc[mt][1] = mma_split16(A, b1, dacc[mt][1]);
             }
         }
-        const bool rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+        const Contract how = range.contract(a.coefs, [&](auto f) __attribute__((always_inline)) {
 #pragma unroll 1
-                              for (int kk = (int)opaque((uint32_t)g4); kk < K; kk += 4) f(column(kk));
-                          });
-        if (rare)
+            for (int kk = (int)opaque((uint32_t)g4); kk < K; kk += 4) f(column(kk));
+        });
+        if (how != kUsual)
             tiles_f32(dacc, MT, a.dfrag + (size_t)w * MT * a.KSd * 64, a.KSd, (int)opaque((uint32_t)lane),
                       [&](int k, int t) { return column(min(k, K))[t]; });
         // the observations to their slots (see k_ring_pass), four rows at a time

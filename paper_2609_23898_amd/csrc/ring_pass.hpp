@@ -27,7 +27,7 @@ struct PassParams {
     int N, c, KSe, KSd, n;
     unsigned nblk;                 // blocks (split kernels: runs of blocks) of all instances
     unsigned run;                  // split kernels: half-blocks per workgroup
-    int wide;                      // split kernels: the plan has coefficients that only fp32 holds (see split.hpp)
+    int coefs;                     // split kernels: SplitCoefs of the plan
     int ragged;                    // some row of grads or out does not start on a 128-byte line
     PassInst in[kPassInst];
 };

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
     };
     Split3<v8bf> b[KC][2];
     const Split3<v4bf> none[2] = {};
-    bool rare;                                            // the half-block was contracted on fp32 MFMAs
+    Contract how;                                         // kFp32: the half-block is done
     auto split = [&]() __attribute__((always_inline)) {
         SplitRange range;
 #pragma unroll
@@ -168,13 +168,18 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
 #pragma unroll
             for (int q = 0; q < 2; ++q) b[kc][q] = split8([&](int s) { return x[kc][s][q]; });
         }
-        rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+        how = range.contract(a.coefs, [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
                    for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
                        for (int s = 0; s < 8; ++s) f(x[kc][s]);
                });
-        if (!rare) return;
+        if (how == kScaled)
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) b[kc][q] = split8([&](int s) { return kScale * x[kc][s][q]; });
+        if (how != kFp32) return;
         const size_t ps = opaque_s(p), e = hb * 32 + 2 * opaque((uint32_t)col);
         const int MT = (c + 15) / 16, gq = (int)opaque((uint32_t)g);
 #pragma unroll 1
@@ -199,7 +204,8 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
         const uint32_t lane_out = opaque((uint32_t)(((size_t)(g * 4) * p + 2 * (size_t)col) * sizeof(float)));
         float *row = dst + e0;
         const bool narrow = p < kNarrow;
-        if (!rare) {
+        const float back = how == kScaled ? 1.f / kScale : 1.f;
+        if (how != kFp32) {
 #pragma unroll
             for (int mt = 0; mt < 2 * KC; mt += 2) {
                 if (EXC || 16 * mt < (int)opaque_s(c)) {
@@ -210,7 +216,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
                     for (int m = 0; m < 2; ++m)
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            const v2f v = {acc[m][0][r], acc[m][1][r]};
+                            const v2f v = {back * acc[m][0][r], back * acc[m][1][r]};
                             if (EXC || lrow + 16 * m + r < c) {
                                 if (narrow) gstore<2>(row, lane_out, v);
                                 else gstore<2>(row + (size_t)(4 * (int)opaque((uint32_t)g)) * p + 2 * col, 0, v);
@@ -277,7 +283,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
     };
     Split3<v8bf> b[KC][2];
     Split3<v4bf> bt[2];
-    bool rare;                                            // the half-block in b goes on fp32 MFMAs
+    Contract how;
     auto split = [&]() __attribute__((always_inline)) {
         SplitRange range;
 #pragma unroll
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
         for (int s = 0; s < 4; ++s) range.add(xt[s]);
 #pragma unroll
         for (int q = 0; q < 2; ++q) bt[q] = split4([&](int s) { return xt[s][q]; });
-        rare = a.wide || range.left([&](auto f) __attribute__((always_inline)) {
+        how = range.contract(a.coefs, [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
                    for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
@@ -308,7 +314,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(WPE
         const size_t e0 = hb * 32;
         const bool fast = p < kNarrow && (size_t)(c - 1) * p + e0 + 32 <= d;
         const uint32_t lane_out = opaque((uint32_t)(((size_t)(g * 4) * p + 2 * (size_t)col) * sizeof(float)));
-        if (rare) {
+        if (how != kUsual) {
             decode_rare(srow, p, d, e0, c, K, a.dfrag + (size_t)w * ((c + 15) / 16) * a.KSd * 64, a.KSd, out, lane);
             wait_all();
         } else {

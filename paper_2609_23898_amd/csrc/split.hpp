@@ -18,12 +18,20 @@
 // The terms hold an entry exactly from 2^-110 (below that the last one falls
 // under bf16's smallest subnormal, 2^-133) up to 2^127 (beyond, the first could
 // round to infinity).  A half-block of 32 positions with another entry in it
-// (SplitRange: nonzero and smaller, larger or infinite) is contracted on fp32
-// MFMAs instead (tiles_f32), and so is every half-block of a plan that has such a
-// coefficient: no input loses digits to the split.  The test costs one vector
-// instruction per entry beside five and a half of the split (encode of N = 16,
-// c = 128, d = 60M 1.740 -> 1.751 ms, N = 20, c = 40, d = 20M 740 -> 774 us); zeros
-// take a second look.
+// (SplitRange) loses no digit either:
+//  - The encode, with small entries and none of 2^40 or more, scales all of them
+//    by 2^40 (fp32's smallest subnormal becomes 2^-109) and its chunks back.
+//    Plans with coefficients of 2^40 or more, whose sums could overflow so, do
+//    not scale.
+//  - Any other such half-block, and every one of a plan that has a coefficient
+//    like that, is contracted on fp32 MFMAs (tiles_f32).  In the decode, whose
+//    rows are sums over workers and chunks, small ones are that rare.
+// The test costs one vector instruction per entry beside five and a half of the
+// split (us, without and with: encode N = 16, c = 128, d = 1e8 2759 and 2759, N = 20,
+// c = 40, d = 20M 743 and 731, N = 3, c = 100, d = 1e8 623 and 638; single call N = 16, c =
+// 64, d = 40M 2359 and 2415, N = 12, c = 48 2374 and 2250); zeros take a second look.
+// Entries of 1e-36, d = 20M: one in a thousand N = 16, c = 64 encode 530 us as without,
+// 1022 on fp32 MFMAs; all of them, decode 3.3 ms against 0.6.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -122,6 +130,10 @@ __device__ inline Split3<v4bf> split4(X x) {
     return {__builtin_bit_cast(v4bf, h), __builtin_bit_cast(v4bf, m), __builtin_bit_cast(v4bf, l)};
 }
 
+// How a half-block is contracted.
+enum Contract { kUsual, kScaled, kFp32 };
+constexpr float kScale = 0x1p40f;
+
 // Whether the wave has met an entry that its three terms do not hold exactly.
 // (A NaN makes NaNs of its position either way.)
 struct SplitRange {
@@ -130,14 +142,17 @@ struct SplitRange {
         asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(lo) : "v"(x[0]), "v"(x[1]));
         asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(hi) : "v"(x[0]), "v"(x[1]));
     }
-    // each(f) calls f on every entry again, to tell zeros from small ones
+    // coefs: see PassParams; each(f) calls f on every entry again, to tell zeros
+    // from small ones
     template <class Each>
-    __device__ bool left(Each each) const {
-        if (__builtin_amdgcn_ballot_w64(lo < 0x1p-110f || hi >= 0x1p127f) == 0) return false;
-        if (__builtin_amdgcn_ballot_w64(hi >= 0x1p127f) != 0) return true;
+    __device__ Contract contract(int coefs, Each each) const {
+        if (coefs == kCoefsFp32) return kFp32;
+        if (__builtin_amdgcn_ballot_w64(lo < 0x1p-110f || hi >= 0x1p127f) == 0) return kUsual;
+        if (__builtin_amdgcn_ballot_w64(hi >= 0x1p127f) != 0) return kFp32;
         uint32_t least = 0xffffffffu;                     // of 2 bits - 1: a zero wraps to the largest
         each([&](v2f x) { least = min(least, min((__float_as_uint(x[0]) << 1) - 1, (__float_as_uint(x[1]) << 1) - 1)); });
-        return __builtin_amdgcn_ballot_w64(least < 2u * (17u << 23) - 1) != 0;
+        if (__builtin_amdgcn_ballot_w64(least < 2u * (17u << 23) - 1) == 0) return kUsual;
+        return coefs == kCoefsUsual && __builtin_amdgcn_ballot_w64(hi >= 0x1p40f) == 0 ? kScaled : kFp32;
     }
 };
 
@@ -177,7 +192,7 @@ __device__ inline void tile_f32(v4f (&acc)[2], const float *frag, int KS, int la
     const uint32_t lane = opaque((uint32_t)lane0), ks0 = 2 * (lane >> 4);
     const float *a = frag + ks0 * 64 + (lane & 15);
     acc[0] = acc[1] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll(UNROLL)
+#pragma unroll UNROLL
     for (int u = 0; u < 8 * KC; ++u) {
         const int kc = u / 8, s = u % 8, ks = 8 * kc + s / 4;
         const float coef = (int)ks0 + ks < KS ? gload1(a + ks * 64 + s % 4 * 16) : 0.f;

@@ -187,13 +187,16 @@ def test_infinities_and_nan_stay_in_their_columns(seed):
 # Entries that three bf16 terms do not hold, alone and among others: below
 # 2^-110 (subnormals of bf16 and of fp32 too), at the top of the range, and
 # zeros, which they do hold.
-MAGNITUDES = {"usual": (-20, 1), "small": (-148, -105), "large": (127, 128), "mixed": (-140, 128), "sparse": (-20, 1)}
+MAGNITUDES = {"usual": (-20, 1), "small": (-148, -105), "few": (-20, 1), "large": (127, 128), "mixed": (-140, 128),
+              "sparse": (-20, 1)}
 
 
 def _entries(kind, shape, seed):
     rng = np.random.default_rng(seed)
     lo, hi = MAGNITUDES[kind]
     x = rng.choice([-1.0, 1.0], size=shape) * rng.uniform(1, 2, size=shape) * 2.0 ** rng.integers(lo, hi, size=shape)
+    if kind == "few":                               # small ones among usual ones
+        x = np.where(rng.random(shape) < 0.01, x * 2.0 ** -125, x)
     if kind == "sparse":
         x[rng.random(shape) < 0.9] = 0.0
     return np.clip(x, -np.finfo(np.float32).max, np.finfo(np.float32).max).astype(np.float32)
@@ -256,6 +259,20 @@ def test_split_contractions_keep_every_fp32_coefficient(N, c, scale):
     np.testing.assert_allclose(work.double().cpu().numpy(), want, rtol=2.0 ** -24, atol=0)
 
 
+@pytest.mark.parametrize("N,c", [(12, 48), (3, 65), (16, 128)])
+def test_small_entries_are_not_scaled_under_large_coefficients(N, c):
+    """Sums of scaled entries would overflow under coefficients of 2^100."""
+    rng = np.random.default_rng(c)
+    d = c * 64
+    coef = (rng.uniform(1, 1.99, size=(N, c)) * 2.0 ** 100).astype(np.float32).astype(np.float64)
+    plan = C.Plan.explicit(np.stack([np.diag(coef[i]) for i in range(N)]), np.zeros((N, c + N - 1, c)))
+    g = _entries("few", (N, d), seed=c)
+    work, ws, _ = buffers(plan, d)
+    C.encode_round(plan, 0, d, to_device(g), work, ws)
+    want = np.repeat(coef, d // c, axis=1) * g.astype(np.float64)
+    np.testing.assert_allclose(work.double().cpu().numpy(), want, rtol=2.0 ** -22, atol=0)
+
+
 @pytest.mark.parametrize("in_place", [False, True])
 @pytest.mark.parametrize("N,c", [(9, 33), (12, 48), (16, 64), (8, 96), (16, 128)])
 def test_one_pass_and_steps_agree_on_entries_beyond_the_split(N, c, in_place):
@@ -269,7 +286,7 @@ def test_one_pass_and_steps_agree_on_entries_beyond_the_split(N, c, in_place):
     g = np.zeros((N, c * p), np.float32)
     g[:, :d] = _entries("usual", (N, d), seed=c)
     rng = np.random.default_rng(c)
-    for kind in ("small", "large", "mixed", "sparse"):
+    for kind in ("small", "few", "large", "mixed", "sparse"):
         for h in rng.choice(p // 32, size=4, replace=False):
             i, l = rng.integers(N), rng.integers(c - 2)
             at = l * p + 32 * h

@@ -4,7 +4,8 @@ fp32 operand x is split into three bf16 terms, x = h + m + l, each the
 rounding to nearest even of what the earlier terms leave, and six of the
 nine term products are summed.  Here the split is emulated bit by bit on the
 host and its claims are checked: the split is exact between 2^-110 and 2^127
-and loses digits below (there the kernels contract on fp32 MFMAs), the terms
+and loses digits below (there the kernels scale, or contract on fp32 MFMAs;
+scaled by 2^40 every smaller entry is exact), the terms
 shrink by 2^-8 each, every kept product is exact in fp32, and the dropped
 products of a dot product sum to less than 2^-23 sum |a_k b_k| (two units of
 fp32 rounding).  The kernels themselves are checked against the oracle on the
@@ -82,6 +83,10 @@ def test_split_is_exact_over_the_range_that_the_kernels_take():
     h, m, l = split3(x)
     assert not np.array_equal(h.astype(np.float64) + m + l, x.astype(np.float64))
     assert np.isinf(bf16(np.finfo(np.float32).max))
+    small = np.concatenate([x, np.float32([2.0 ** -149, 3 * 2.0 ** -149, 2.0 ** -126, -2.0 ** -130])])
+    up = small * np.float32(2.0 ** 40)
+    h, m, l = split3(up)
+    assert np.array_equal(h.astype(np.float64) + m + l, small.astype(np.float64) * 2.0 ** 40)
 
 
 def test_six_products_are_exact_and_the_dropped_three_are_below_two_units():
